@@ -83,13 +83,25 @@ inline int check_method(int scheme, int limiter, double C_T, double gamma, bool 
   return TENOM_OK;
 }
 
-inline TenoParams teno_params(int limiter, double C_T) {
+// The q of the all-smooth test (teno_all_smooth) for cutoff C_T:
+// (1 + q)^6 (K - 2) C_T < 1 with a margin far above the roundings of the
+// cutoff; negative (the test never holds) where no such q > 0 exists.  The
+// adaptive cutoff takes at most 1e-7.
+inline double teno_quick(int K, bool adaptive, double C_T) {
+  const double x = (K - 2) * (adaptive ? 1e-7 : C_T);
+  if (!(x > 0.0)) return x == 0.0 ? INFINITY : -1.0;
+  const double q = 0.99 * (pow(x, -1.0 / 6.0) - 1.0);
+  return q > 1e-6 ? q : -1.0;
+}
+
+inline TenoParams teno_params(int K, bool adaptive, int limiter, double C_T) {
   int kind;
   double beta;
   limiter_kind(limiter, &kind, &beta);
   TenoParams tp;
   tp.C_T = C_T;
   tp.mp_beta3 = beta / 3.0;
+  tp.quick = teno_quick(K, adaptive, C_T);
   return tp;
 }
 

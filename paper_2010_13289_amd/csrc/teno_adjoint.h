@@ -230,7 +230,9 @@ __device__ __forceinline__ void teno_m_vjp(const double (&v)[K], const TenoParam
 #pragma unroll
   for (int j = 0; j < K - 1; ++j) D[j] = v[j + 1] - v[j];
   bool smooth[K - 2];
-  teno_cutoff<K, ADAPT>(D, tp, smooth);
+  double beta[K - 2], tau;
+  teno_indicators<K>(D, beta, tau);
+  teno_cutoff<K, ADAPT>(D, beta, tau, tp, smooth);
   uint32_t mask = 0;
 #pragma unroll
   for (int k = 0; k < K - 2; ++k) mask |= (smooth[k] ? 1u : 0u) << k;

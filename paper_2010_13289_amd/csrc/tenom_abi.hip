@@ -94,15 +94,13 @@ void field_map(const tenom_grid* g, int axis, int (&fld)[5]) {
   fld[nd + 1] = nd + 1;
 }
 
-FaceParams face_params(const tenom_grid* g, int axis, int limiter, double C_T, double gamma) {
+FaceParams face_params(const tenom_grid* g, int scheme, int axis, int limiter, double C_T, double gamma) {
   FaceParams fp;
-  int kind;
-  double beta;
-  limiter_kind(limiter, &kind, &beta);
+  bool adaptive;
+  const int K = scheme_K(scheme, &adaptive);
   fp.gamma = gamma;
   fp.adv = (g->system == TENOM_SYS_SCALAR) ? g->adv[axis] : 0.0;
-  fp.tp.C_T = C_T;
-  fp.tp.mp_beta3 = beta / 3.0;
+  fp.tp = teno_params(K, adaptive, limiter, C_T);
   return fp;
 }
 
@@ -181,7 +179,7 @@ int vjp_axes(const tenom_grid* g, int scheme, int limiter, double C_T, double ga
     L.ax.nfaces = vjp_faces(g, ax);
     L.ax.inv_dx = 1.0 / g->dx[ax];
     field_map(g, ax, L.fld);
-    L.fp = face_params(g, ax, limiter, C_T, gamma);
+    L.fp = face_params(g, scheme, ax, limiter, C_T, gamma);
     L.stream = s;
     hipError_t e;
     {
@@ -279,7 +277,7 @@ int sweep(const tenom_grid* g, int scheme, int limiter, double C_T, double gamma
   const bool tile = choice == TENOM_SWEEP_TILE ||
                     (choice == TENOM_SWEEP_AUTO && tiles >= 512 && (axis != 0 || K == 6));
   field_map(g, axis, L.fld);
-  L.fp = face_params(g, axis, limiter, C_T, gamma);
+  L.fp = face_params(g, scheme, axis, limiter, C_T, gamma);
   L.stream = stream;
   hipError_t e;
   {
@@ -532,7 +530,7 @@ int tenom_reconstruct_faces(const tenom_grid* grid, int scheme, int limiter, dou
   L.nz = d.nz;
   L.bc = grid->bc[axis];
   field_map(grid, axis, L.fld);
-  L.fp = face_params(grid, axis, limiter, C_T, gamma);
+  L.fp = face_params(grid, scheme, axis, limiter, C_T, gamma);
   L.stream = (hipStream_t)stream;
   hipError_t e;
   {

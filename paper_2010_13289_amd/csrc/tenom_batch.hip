@@ -150,7 +150,7 @@ int check_call(const tenom_batch_plan* P, int scheme, int limiter, double C_T, d
   if (P->count > 0 && !U) return fail(TENOM_EINVAL, "U must not be NULL");
   m->fp.gamma = gamma;
   m->fp.adv = 0.0;
-  m->fp.tp = teno_params(limiter, C_T);
+  m->fp.tp = teno_params(m->K, m->adapt, limiter, C_T);
   return check_device(P);
 }
 
