@@ -403,10 +403,10 @@ int tenom_version(void);
  * segments of 256 cells, and along y and z each lane marches one x column
  * along a segment of the line with its stencil in an LDS ring.
  * TENOM_SWEEP_TILE: a workgroup stages tiles of 8 adjacent lines (x columns
- * for y and z, y rows for x) by a chunk of the line in LDS and walks the
- * lines whole.  TENOM_SWEEP_AUTO (the default): per axis, the tile kernel
- * when the lines alone give at least 512 workgroups (along x only for the
- * six-point schemes), else the line kernel.
+ * for y and z, y rows for x) by a chunk of the line in LDS and walks a segment
+ * of the lines, or the lines whole.  TENOM_SWEEP_AUTO (the default): the tile
+ * kernel in 2D and 3D, except along x where the rows fill at most 512
+ * workgroups of the line kernel; the line kernel in 1D.
  * Returns TENOM_EINVAL for any other value.  The setting is process-wide;
  * calls made while another thread changes it may use either kernel.
  */

@@ -10,11 +10,12 @@
 //                  each thread forms one cell's divergence and applies the
 //                  epilogue.  A periodic row of <= 256 cells is one segment,
 //                  so every face and every cell is computed exactly once.
-//  k_sweep_tile    sweep along y or z (strided) for grids with many lines:
-//                  a workgroup takes TX adjacent x columns of one line and
-//                  walks it in chunks, each chunk a row sweep of a strided
-//                  tile staged in LDS.
-//  k_sweep_march   sweep along y or z (strided).  Each lane owns one x
+//  k_sweep_tile    sweep along any axis of a 2D or 3D grid: a workgroup takes
+//                  TX adjacent lines (x columns for y and z, y rows for x)
+//                  over a segment of the axis and walks it in chunks, each
+//                  chunk a row sweep of a strided tile staged in LDS.
+//  k_sweep_march   sweep along y or z (strided), the line kernel that
+//                  tenom_set_sweep_kernel can ask for.  Each lane owns one x
 //                  column (coalesced 512-byte rows per wave; the block's
 //                  wavefronts take consecutive (line, segment) units) and marches
 //                  along the axis over a segment of cells, keeping the face's
@@ -297,28 +298,57 @@ void k_sweep_row(SweepParams<NF> p) {
 }
 
 // ---------------------------------------------------------------------------
-// Tile sweep (any axis).  A 256-thread workgroup owns TX adjacent lines
-// along the axis (x columns for y and z, y rows for x) and walks them whole
-// in chunks of FJ = 256 / TX faces per line.  Each chunk is a row sweep on a
+// Tile sweep (any axis).  A 256-thread workgroup owns a segment (or the
+// whole, tile_segment) of TX adjacent lines along the axis (x columns for y
+// and z, y rows for x) and walks it in chunks of FJ = 256 / TX faces per line.  Each chunk is a row sweep on a
 // tile: its cells are staged in LDS (row r of the chunk at staging indices
 // r TX .. r TX + TX - 1) with their flux, signal speed and Roe inputs, each
 // thread computes one face, the fluxes go through LDS and each thread closes
 // the cell left of its face.  The last face of a chunk is handed to the next
-// chunk through LDS and face 0 of a periodic line is kept for its last cell,
-// so a line of M cells costs M faces (M + 1 when transmissive); only the
-// K - 1 halo rows of each chunk are staged twice.  A wavefront's 64 faces
+// chunk through LDS and face 0 of a whole periodic line is kept for its last
+// cell, so M cells cost M faces (M + 1 for a segment or a transmissive line);
+// only the K - 1 halo rows of each chunk are staged twice.  A wavefront's 64 faces
 // form an 8 x 8 patch (8 lines by 8 faces), which a discontinuity crosses
 // far less often than a strip of 64 faces along one line: most wavefronts
 // then skip the limiter (StagedCells with REREAD).
 // ---------------------------------------------------------------------------
 constexpr int kTileColumns = 8;  // columns (lines side by side) per tile-sweep workgroup
 
-// Workgroups of a tile sweep along `axis`: the lines of the other axis times
-// the column groups (x columns for y and z, y rows for x).
+// Whole-line workgroups of a tile sweep along `axis`: the lines of the other
+// axis times the column groups (x columns for y and z, y rows for x).
 inline long tile_count(int axis, int nx, int ny, int nz) {
   const long lines = (axis == 2) ? ny : nz;
   const int across = (axis == 0) ? ny : nx;
   return lines * ((across + kTileColumns - 1) / kTileColumns);
+}
+
+// Cells per segment of a tile sweep.  Segments of 32 c - 1 cells take c
+// chunks (one redundant face each); a whole line hands its faces on instead.
+// More segments fill the chip and shorten the last round, fewer save the
+// redundant faces and halo rows.  The c with the smallest estimate of
+//   workgroups (chunks + 0.15) / slots + 0.7 (chunks of one workgroup + 0.15),
+// slots = workgroups the chip holds, is taken; the estimate's order agreed
+// with the measured sweeps (Euler, six points unless stated; one chunk, two,
+// four, in us): 1024^2 y 67, 71, 79; 2048^2 y 236, 229, 235; 187x150x93 y at
+// eight points 313, 302, 316 (the last whole lines).
+inline int tile_segment(int axis, int n, int nx, int ny, int nz, int bc, int waves_per_simd) {
+  const double lines = (double)tile_count(axis, nx, ny, nz);
+  const double slots = 256.0 * waves_per_simd;  // 256 CUs, one wavefront of a workgroup per SIMD
+  constexpr double start = 0.15;
+  int best = n;
+  double best_t = 0.0;
+  for (int c = 1;; ++c) {
+    const int seg = 32 * c - 1;
+    const bool whole = seg >= n || (bc == 0 && seg + 1 == n);
+    const int nseg = whole ? 1 : (n + seg - 1) / seg;
+    const double chunks = (n + (whole && bc == 0 ? 0 : nseg)) / (32.0 * nseg);
+    const double t = lines * nseg * (chunks + start) / slots + 0.7 * (c + start);
+    if (c == 1 || t < best_t) {
+      best_t = t;
+      best = whole ? n : seg;
+    }
+    if (whole) return best;
+  }
 }
 
 template <int NF, int K>
@@ -347,10 +377,11 @@ void k_sweep_tile(SweepParams<NF> p, int axis) {
   const int tile = xcd * q8 + min(xcd, r8) + (b >> 3);
   // column groups: x columns for y and z, y rows for x
   const int ncg = ((axis == 0 ? p.ny : p.nx) + TX - 1) / TX;
-  const int o = tile / ncg;  // z of an x or y line, y of a z line
+  const int o = tile / ncg / p.nseg;  // z of an x or y line, y of a z line
+  const int c0 = (tile / ncg % p.nseg) * p.seg;  // first cell of the segment
   const long N = (long)p.nx * p.ny * p.nz;
-  const bool wrap = p.bc == 0;
-  const int nface = wrap ? p.n : p.n + 1;  // face j lies between cells j - 1 and j
+  const bool wrap = p.bc == 0 && p.nseg == 1;  // a whole periodic line
+  const int nface = wrap ? p.n : min(p.seg, p.n - c0) + 1;  // face j lies between cells c0 + j - 1 and c0 + j
   const int nchunk = (nface + FJ - 1) / FJ;
   // A periodic x line is walked from its cell 1 (cell m of the walk is cell
   // m + 1 of the line, the last one cell 0): a chunk then closes 32
@@ -394,7 +425,7 @@ void k_sweep_tile(SweepParams<NF> p, int axis) {
     {
       const Where w = where();
       for (int r = w.f; r < nfk + K - 1; r += FJ)
-        stage_cell<NF>(stage, NC, r * TX + w.col, p, N, cell_at(w.L, j0 - K / 2 + r + rot));
+        stage_cell<NF>(stage, NC, r * TX + w.col, p, N, cell_at(w.L, c0 + j0 - K / 2 + r + rot));
     }
     __syncthreads();
     __builtin_amdgcn_s_setprio(0);
@@ -421,8 +452,8 @@ void k_sweep_tile(SweepParams<NF> p, int axis) {
     __syncthreads();
     __builtin_amdgcn_s_setprio(3);
     {
-      // this thread closes cell j - 1 and, on a periodic line, the last cell
-      // (right of the last face) with face 0 as its right face.  The
+      // this thread closes cell c0 + j - 1 and, on a whole periodic line, the
+      // last cell (right of the last face) with face 0 as its right face.  The
       // epilogue's parameters are read anew through an opaque pointer to the
       // argument: held from the kernel's start they would be spilled across
       // the face and read back lane by lane.
@@ -433,7 +464,7 @@ void k_sweep_tile(SweepParams<NF> p, int axis) {
       const int f = w.f, col = w.col, j = j0 + f;
       const bool act = f < nfk && w.in;
       if (act && j >= 1) {
-        const long cell = w.L.base + (long)(j - 1 + rot) * w.L.stride;
+        const long cell = w.L.base + (long)(c0 + j - 1 + rot) * w.L.stride;
         EpiIn<NF> ein;
         epi_load<NF>(pe, N, cell, ein);
         double us[NF], div[NF];
@@ -713,9 +744,9 @@ hipError_t launch_tile(const SweepLaunch& a) {
   for (int q = 0; q < NF; ++q) p.fld[q] = a.fld[q];
   if (a.axis < 0 || a.axis > 2) return hipErrorInvalidValue;
   p.n = (a.axis == 0) ? a.nx : (a.axis == 1) ? a.ny : a.nz;
-  p.seg = p.n;
-  p.nseg = 1;
-  const long tiles = tile_count(a.axis, a.nx, a.ny, a.nz);
+  p.seg = tile_segment(a.axis, p.n, a.nx, a.ny, a.nz, a.bc, RowOccupancy<NF, K>::WAVES);
+  p.nseg = (p.n + p.seg - 1) / p.seg;
+  const long tiles = tile_count(a.axis, a.nx, a.ny, a.nz) * p.nseg;
   hipLaunchKernelGGL((k_sweep_tile<NF, K, LIM, ADAPT>), dim3((unsigned)tiles), dim3(256), 0, a.stream, p, a.axis);
   return hipGetLastError();
 }

@@ -266,16 +266,18 @@ int sweep(const tenom_grid* g, int scheme, int limiter, double C_T, double gamma
   L.inv_dx = 1.0 / g->dx[axis];
   const int n_axis = axis == 0 ? d.nx : (axis == 1 ? d.ny : d.nz);
   L.seg = axis == 0 ? 0 : march_segment(n_axis, d.nx, axis == 1 ? d.nz : d.ny);
-  // The tile sweep walks whole lines, so it is taken when the lines alone
-  // give at least 512 workgroups (two per CU); else the line kernels: the row
-  // sweep for x (which also splits long rows), the march for y and z (which
-  // splits lines into segments).  Along x the row sweep's contiguous strips
-  // need no halo rows staged twice: at eight points it measured faster than
-  // the tile, at six points slower (256^3 Euler, one box).
-  const long tiles = tile_count(axis, d.nx, d.ny, d.nz);
+  // The tile sweep serves every axis of 2D and 3D grids (its 8 x 8 patches of
+  // faces skip the limiter far more often than strips along one line, and its
+  // segments fill the chip on small grids, where the march runs few serial
+  // wavefronts: 256^2 y 48 -> 15 us, 72x64x56 y 168 -> 35, 1024^2 y 95 -> 67,
+  // 128^3 x at eight points 372 (row) -> 273).  The row sweep serves 1D, and x
+  // rows that fill its workgroups where those are at most two per CU: with the
+  // chip part empty the shorter pass through one workgroup counts (256^2 x
+  // 11.4 us against 15.4).
+  const long row_blocks = (long)((d.nx + 254) / 255) * d.ny * d.nz;
+  const bool few_rows = axis == 0 && (g->ndim == 1 || (row_blocks <= 512 && d.nx >= 128));
   const int choice = g_sweep_kernel.load(std::memory_order_relaxed);
-  const bool tile = choice == TENOM_SWEEP_TILE ||
-                    (choice == TENOM_SWEEP_AUTO && tiles >= 512 && (axis != 0 || K == 6));
+  const bool tile = choice == TENOM_SWEEP_TILE || (choice == TENOM_SWEEP_AUTO && !few_rows);
   field_map(g, axis, L.fld);
   L.fp = face_params(g, scheme, axis, limiter, C_T, gamma);
   L.stream = stream;

@@ -141,3 +141,23 @@ def test_automatic_choice_at_64_cubed_against_the_oracle(T, orc):
         excl |= faces_to_cells(band_faces(bd), 2 - axis, 64, grid["bc"][axis] == 0, 1)
     assert excl.mean() < 0.01
     assert_close_fields(dg, do, exclude=excl, what="64^3 dU/dt, automatic sweep kernels")
+
+
+# Line lengths at the edges of the one-chunk segments that small grids take
+# (31 cells; a periodic line of at most 32 wraps whole), in 2D; then grids with
+# enough lines for segments of several chunks and for whole lines, each along
+# x (with the periodic walk's shifted start) and a strided axis.
+SEGMENT_SHAPES = [((m, 9), [b, 1 - b], K) for m in (31, 32, 33, 62, 63, 64, 94) for b in (0, 1) for K in (6, 8)]
+SEGMENT_SHAPES += [((9, m), [b, 0], 6) for m in (32, 33, 63) for b in (0, 1)]
+SEGMENT_SHAPES += [((70, 160, 200), [0, 0, 0], 6), ((200, 160, 70), [0, 1, 1], 6), ((150, 93, 187), [1, 0, 0], 8),
+                   ((136, 128, 100), [0, 1, 1], 8)]
+
+
+@pytest.mark.parametrize("shape,bc,K", SEGMENT_SHAPES, ids=[f"{'x'.join(map(str, s))}-{''.join(map(str, b))}-{k}"
+                                                            for s, b, k in SEGMENT_SHAPES])
+def test_segments_agree_with_the_march(T, shape, bc, K):
+    n = list(reversed(shape))
+    grid = dict(ndim=len(n), n=n, dx=[0.05, 0.07, 0.06][:len(n)], bc=bc, system=1)
+    U = W.random_euler_state(shape, seed=sum(shape) + K, kind="mixed")
+    print(f"[segments] n={n} bc={bc} K={K}", flush=True)
+    check_identical(T, grid, U, K, 1, 1e-5 if K == 6 else 1e-7, "segments")
