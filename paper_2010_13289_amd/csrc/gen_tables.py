@@ -10,19 +10,16 @@ reconstruction is exactly translation-equivariant.
 * the smoothness measures beta_{k,r} of the candidates and beta_K of the
   full stencil (Sec. 2.2): sum_{j=1}^{r-1} int_{-1/2}^{1/2} (p^(j))^2 dxi of
   the degree r-1 polynomial whose cell averages are the stencil values,
-  emitted as a positive sum of squares sum_q w_q y_q^2: six points from an
-  exact LDL^T factorisation in the differences (y = L^T D); eight points
-  from the exact LDL^T over the polynomial's Taylor coefficients, each row
-  written in the differences with coprime integer coefficients and the
-  weights times one common scale (beta_scale), so that almost every
-  constant is an instruction literal (see emit),
+  emitted as a positive sum of squares sum_q w_q y_q^2 from an exact LDL^T
+  factorisation in the differences, eliminated from the farthest difference
+  to the central one, with all measures times one scale (beta_scale) that
+  makes the leading squares of the three-cell measures weightless (see emit),
 * the optimal (maximum-order) linear weights d_k (Sec. 3.3).
 
 Run: python gen_tables.py > teno_tables.h  (the build does this).
 """
 from __future__ import annotations
 
-import struct
 import sys
 from fractions import Fraction as Fr
 from math import factorial, gcd
@@ -134,57 +131,21 @@ def optimal_weights(K):
     return d
 
 
-def taylor_rows(lo, hi):
-    """beta on the stencil [lo, hi] as sum_q w_q (row_q . D)^2 with integer
-    rows: the exact LDL^T of the measure's Gram matrix over the Taylor
-    coefficients a_1 .. a_{r-1} of the polynomial about x_i (ascending),
-    each row of L^T a written in the differences D and scaled to coprime
-    integers (the scale moves into w_q).  Returns [(ints, w)]."""
-    r = hi - lo + 1
-    n = r - 1
-    P = poly_map(lo, hi)
-    T = values_from_diffs(r)
-    # Taylor coefficients a_l (l = 1..r-1) in the differences
-    M = [[sum(P[l][a] * T[a][j] for a in range(r)) for j in range(n)] for l in range(1, r)]
-
-    def mom(e):
-        return Fr(0) if e % 2 else 2 * Fr(1, 2) ** (e + 1) / (e + 1)
-
-    H = [[Fr(0)] * n for _ in range(n)]
-    for j in range(1, r):
-        for k1 in range(j, r):
-            for k2 in range(j, r):
-                H[k1 - 1][k2 - 1] += (Fr(factorial(k1), factorial(k1 - j)) * Fr(factorial(k2), factorial(k2 - j))
-                                      * mom(k1 + k2 - 2 * j))
-    L, w = ldl(H)
-    rows = []
-    for q in range(n):
-        row = [sum(L[i][q] * M[i][j] for i in range(n)) for j in range(n)]
-        den = 1
-        for c in row:
-            den = den * c.denominator // gcd(den, c.denominator)
-        ints = [c * den for c in row]
-        g = 0
-        for c in ints:
-            g = gcd(g, abs(int(c)))
-        ints = [c / g for c in ints]
-        scale = Fr(den, g)
-        rows.append((ints, w[q] / (scale * scale)))
-    # the form is the measure: sum_q w_q (row_q . D)^2 == D^T Q D
+def ordered_ldl(lo, hi, centre):
+    """The measure on the stencil [lo, hi] as sum_q w_q y_q^2 over the
+    differences numbered by their right cell's offset less one (difference m
+    lies between cells m and m + 1), eliminated from the farthest to `centre`,
+    which is left alone in the last square.  Returns [(row, w)], row a dict
+    {difference: coefficient} with coefficient 1 for the eliminated one."""
+    n = hi - lo
+    order = sorted(range(n), key=lambda j: (-abs(lo + j - centre), j))
     Q = diff_quadratic(lo, hi)
+    Lw, wts = ldl([[Q[i][j] for j in order] for i in order])
+    rows = [({lo + order[j]: Lw[j][q] for j in range(q, n)}, wts[q]) for q in range(n)]
     for i in range(n):
         for j in range(n):
-            assert sum(wq * ints[i] * ints[j] for ints, wq in rows) == Q[i][j]
+            assert sum(wq * row.get(lo + i, 0) * row.get(lo + j, 0) for row, wq in rows) == Q[i][j]
     return rows
-
-
-def literal_ok(x: Fr) -> bool:
-    """True when x is a double whose low 32 bits are zero: such a constant
-    is a 32-bit literal of the instruction, with no register to load."""
-    if x != Fr(float(x)):
-        return False
-    bits = struct.unpack("<Q", struct.pack("<d", float(x)))[0]
-    return (bits & 0xFFFFFFFF) == 0
 
 
 def lit(x: Fr) -> str:
@@ -235,14 +196,9 @@ def candidate_coeffs(K: int, k: int) -> list:
 
 
 def emit(K: int, literal: bool) -> str:
-    """Device code of one scheme.  literal: every constant that multiplies
-    data is, where the exact rationals allow, a double whose low 32 bits are
-    zero (an instruction literal): candidates as 1/den times an integer
-    form, the indicators in integer Taylor-coefficient rows with weights
-    scaled by one common factor (beta_scale, a power of two times the lcm
-    of the candidate stencils' weight denominators).  Otherwise the rational
-    coefficients are used directly (a triangular LDL^T in the differences)
-    and beta_scale = 1."""
+    """Device code of one scheme.  literal: the candidates as 1/den times an
+    integer form, so that their constants are instruction literals (the
+    eight-point kernels hold fewer constants in scalar registers)."""
     nk = K - 2
     lo_full = -(K // 2) + 1
     lines = []
@@ -262,21 +218,9 @@ def emit(K: int, literal: bool) -> str:
     names = [f"D[{j}]" for j in range(K - 1)]
     cand = [candidate_coeffs(K, k) for k in range(nk)]
     stencils = [(k, CANDIDATES[k]) for k in range(nk)] + [("K", (lo_full, K // 2))]
-    scale = Fr(1)
-    if literal:
-        trows = {tag: taylor_rows(a, b) for tag, (a, b) in stencils}
-        den = 1
-        for tag, _ in stencils:
-            if tag == "K":
-                continue
-            for _, wq in trows[tag]:
-                den = den * wq.denominator // gcd(den, wq.denominator)
-        scale = Fr(den)
-        while scale > 2:
-            scale /= 2
-        for tag, _ in stencils:
-            if tag != "K":
-                assert all(literal_ok(wq * scale) for _, wq in trows[tag]), tag
+    # the three-cell measures then have unit leading squares, and the two
+    # that share a centre difference share its remaining square
+    scale = Fr(3, 4)
     w("  // every beta below is beta_scale times the measure of Eq. measureTENO;")
     w("  // the cutoff scales eps by the same factor")
     w(f"  static constexpr double beta_scale = {lit(scale)};")
@@ -294,6 +238,19 @@ def emit(K: int, literal: bool) -> str:
             w(f"    c[{k}] = {lit(Fr(1, den))} * ({linear_form(ints, names)});")
         else:
             w(f"    c[{k}] = {linear_form(cand[k], names)};")
+    w("  }")
+    # every candidate smooth: sum_k d_k c_k is the K-point linear scheme on
+    # 2n + 1 = K - 1 differences, antisymmetric about the middle one up to its
+    # 1/2: D_n / 2 + sum_m e_m (D_{n-m} - D_{n+m})
+    mid = K // 2 - 1
+    tot = [sum(d[k] * cand[k][j] for k in range(nk)) for j in range(K - 1)]
+    assert tot[mid] == Fr(1, 2) and all(tot[mid - m] == -tot[mid + m] for m in range(1, mid + 1))
+    w("  // sum_k d_k c_k: the linear scheme all smooth candidates assemble to, minus v_i")
+    w("  static __device__ __forceinline__ double linear(const double* D) {")
+    expr = f"0.5 * D[{mid}]"
+    for m in range(1, mid + 1):
+        expr = f"fma({lit(tot[mid - m])}, D[{mid - m}] - D[{mid + m}], {expr})"
+    w(f"    return {expr};")
     w("  }")
     # transpose of the candidate map, for the adjoint: Dbar += C^T cbar
     w("  // adjoint of candidates: Dbar[j] += sum_k (d c_k / d D_j) cbar[k]")
@@ -314,25 +271,32 @@ def emit(K: int, literal: bool) -> str:
     # betas
     w("  // smoothness measures beta_k (candidates) and beta_K (full stencil)")
     w("  static __device__ __forceinline__ void betas(const double* D, double* beta, double& betaK) {")
+    def D(m):  # difference between cells m and m + 1
+        return f"D[{m + K // 2 - 1}]"
+
+    rest = None
+    for m in (0, -1):
+        for k in (k for k in range(3) if (0 if k < 2 else -1) == m):
+            rows = ordered_ldl(*CANDIDATES[k], m)
+            assert rows[0][1] * scale == 1
+            assert rest in (None, rows[1][1] * scale)
+            rest = rows[1][1] * scale
+    for m, name in ((0, "s0"), (-1, "s1")):
+        w(f"    const double {name} = ({lit(rest)} * {D(m)}) * {D(m)};")
     for tag, (a, b) in stencils:
-        first = a + K // 2 - 1  # index of the first difference of this stencil
-        n = b - a
-        dn = [f"D[{first + j}]" for j in range(n)]
-        if literal:
-            rows = [(ints, wq * scale) for ints, wq in trows[tag]]
-            ys = [linear_form(ints, dn) for ints, _ in rows]
-            wts = [wq for _, wq in rows]
-        else:
-            Q = diff_quadratic(a, b)
-            L, wts = ldl(Q)
-            ys = [linear_form([L[j][q] if j >= q else Fr(0) for j in range(n)], dn) for q in range(n)]
-        w("    {")
-        for q in range(n):
-            w(f"      const double y{q} = {ys[q]};")
-        expr = f"{lit(wts[0])} * (y0 * y0)"
-        for q in range(1, n):
-            expr = f"fma({lit(wts[q])} * y{q}, y{q}, {expr})"
+        # centre: the difference whose square is shared
+        m = 0 if b > 0 else -1
+        rows = ordered_ldl(a, b, m)
+        shared = "s0" if m == 0 else "s1"
         target = "betaK" if tag == "K" else f"beta[{tag}]"
+        w("    {")
+        for q, (row, _) in enumerate(rows[:-1]):
+            w(f"      const double y{q} = {linear_form(row.values(), [D(k) for k in row])};")
+        wl = rows[-1][1] * scale / rest
+        expr = shared if wl == 1 else f"{lit(wl)} * {shared}"
+        for q, (_, wq) in reversed(list(enumerate(rows[:-1]))):
+            wq = wq * scale
+            expr = f"fma(y{q}, y{q}, {expr})" if wq == 1 else f"fma({lit(wq)} * y{q}, y{q}, {expr})"
         w(f"      {target} = {expr};")
         w("    }")
     w("  }")
@@ -345,11 +309,6 @@ def main(out=sys.stdout):
     out.write("// reconstruction in difference form.  Do not edit.\n")
     out.write("#pragma once\n\n")
     out.write("template <int K> struct TenoTables;\n\n")
-    # six points: the exact rationals as they come (the six-point kernels
-    # run at three or more wavefronts per SIMD, which hide the scalar moves
-    # of non-literal constants); eight points: literal-friendly forms (their
-    # kernels run at one wavefront per SIMD, where every constant moved into
-    # a scalar register costs an issue slot)
     out.write(emit(6, literal=False) + "\n\n")
     out.write(emit(8, literal=True) + "\n")
 

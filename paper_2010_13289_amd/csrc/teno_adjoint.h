@@ -232,7 +232,7 @@ __device__ __forceinline__ void teno_m_vjp(const double (&v)[K], const TenoParam
   bool smooth[K - 2];
   double beta[K - 2], tau;
   teno_indicators<K>(D, beta, tau);
-  teno_cutoff<K, ADAPT>(D, beta, tau, tp, smooth);
+  teno_cutoff<K, ADAPT, 2>(D, beta, tau, tp, smooth);
   uint32_t mask = 0;
 #pragma unroll
   for (int k = 0; k < K - 2; ++k) mask |= (smooth[k] ? 1u : 0u) << k;
@@ -807,7 +807,8 @@ __device__ __forceinline__ double field_fwd(const double* sX, const double* sF, 
   // rest whose acoustic fields carry rounding noise, the skip's branches
   // cost the kernel 5 %; the reverse keeps its skip, which costs nothing
   // measurable there)
-  return 0.5 * (teno_m<K, LIM, true, ADAPT>(vp, tp, cp) + teno_m<K, LIM, true, ADAPT>(vm, tp, cm));
+  return 0.5 * (teno_m<K, LIM, true, ADAPT, false, 2, false>(vp, tp, cp) +
+                teno_m<K, LIM, true, ADAPT, false, 2, false>(vm, tp, cm));
 }
 
 // Ordering of LDS accesses between lanes of one wavefront: the hardware

@@ -16,11 +16,11 @@
 namespace tenom {
 
 // Eq. measureTENO: gamma_k = (C + tau_K / (beta_k + eps))^q, C = 1, q = 6.
-// The reconstruction runs on twice the split fluxes (see lf_split2), which
-// scales beta and tau by 4; eps is scaled by the same exact factor, so every
-// rounding step is the same as on the halved values.
+// The reconstruction runs on SC = 2 (see lf_split2) or 4 (acoustic fields,
+// see euler_face) times the split fluxes, which scales beta and tau by SC^2;
+// eps is scaled by the same exact factor, so every rounding step is the same
+// as on the halved values.
 constexpr double kEps = 1e-40;
-constexpr double kEps2x = 4.0 * kEps;
 
 // Limiter kinds (template values).  The C ABI's limiter IDs map onto them:
 // MP with d^M4 (IDs 1, 5) and with d^MM (IDs 6, 7, 8) differ only in the
@@ -105,9 +105,9 @@ __device__ __forceinline__ void teno_indicators(const double (&D)[K - 1], double
   tau = fabs(fma(fma(4.0, beta[0], beta[1] + beta[2]), -1.0 / 6.0, betaK));
 }
 
-template <int K>
+template <int K, int SC>
 __device__ __forceinline__ constexpr double teno_eps() {
-  return kEps2x * TenoTables<K>::beta_scale;
+  return SC * SC * kEps * TenoTables<K>::beta_scale;
 }
 
 // Sufficient test that every candidate is smooth, without the reciprocals and
@@ -120,32 +120,33 @@ __device__ __forceinline__ constexpr double teno_eps() {
 // On smooth data tau is sixth order against second-order beta_k: on the
 // 256^3 benchmark state the test holds in 96 to 99.9 % of the
 // reconstructions, where all candidates are smooth in 97 to 99.9 %.
-template <int K>
+template <int K, int SC>
 __device__ __forceinline__ bool teno_all_smooth(const double (&beta)[K - 2], double tau, const TenoParams& tp) {
   double m = beta[0];
 #pragma unroll
   for (int k = 1; k < K - 2; ++k) m = fmin(m, beta[k]);
-  return tau <= tp.quick * (m + teno_eps<K>());
+  return tau <= tp.quick * (m + teno_eps<K, SC>());
 }
 
 // Smoothness decisions delta_k (true = smooth) from the indicators: gamma_k
 // and the cutoff (Eqs. measureTENO, normalize, cut-off); with ADAPT the
 // cutoff of Sec. 2.4 (Eqs. shock_indicator, cut-off_adjust).
-template <int K, bool ADAPT>
+template <int K, bool ADAPT, int SC>
 __device__ __forceinline__ void teno_cutoff(const double (&D)[K - 1], const double (&beta)[K - 2], double tau,
                                             const TenoParams& tp, bool (&smooth)[K - 2]) {
   constexpr int NK = K - 2;
   constexpr int C0 = K / 2 - 1;  // index of v_i
   double C_T = tp.C_T;
   if constexpr (ADAPT) {
-    // eta at cells i-1 .. i+2 (eps scaled by 4 for the doubled values), the
-    // minimum, m = 1 - min(1, eta / C_r)
+    // eta at cells i-1 .. i+2 (eps scaled with the values), the minimum,
+    // m = 1 - min(1, eta / C_r)
+    constexpr double reps = SC * SC * kRenEps;
     double eta = 0.0;
 #pragma unroll
     for (int j = C0 - 1; j <= C0 + 2; ++j) {
       const double a = D[j], b = D[j - 1];
-      const double num = fabs(2.0 * a * b) + 4.0 * kRenEps;
-      const double den = fma(a, a, fma(b, b, 4.0 * kRenEps));
+      const double num = fabs(2.0 * a * b) + reps;
+      const double den = fma(a, a, fma(b, b, reps));
       const double e = num * rcp1(den);
       eta = (j == C0 - 1) ? e : fmin(eta, e);
     }
@@ -165,7 +166,7 @@ __device__ __forceinline__ void teno_cutoff(const double (&D)[K - 1], const doub
   // gamma_k and the cutoff: chi_k = gamma_k / sum < C_T  <=>  gamma_k < C_T sum
   double b[NK], binv[NK];
 #pragma unroll
-  for (int k = 0; k < NK; ++k) b[k] = beta[k] + teno_eps<K>();
+  for (int k = 0; k < NK; ++k) b[k] = beta[k] + teno_eps<K, SC>();
   rcp_pairs<NK>(b, binv);
   double g[NK];
   double sum = 0.0;
@@ -293,15 +294,18 @@ __device__ __forceinline__ double va_den(double dm, double dp) { return fmax(fma
 
 // One TENO-M reconstruction (Secs. 2.2-3.3).  With SKIP, a wavefront in
 // which teno_all_smooth holds in every lane skips the cutoff and the limiter,
-// which only reaches nonsmooth candidates: the assembly then adds the same
-// terms in the same order, so the result has the same bits.  When FLAGS, `bits` receives
+// which only reaches nonsmooth candidates, and assembles the linear scheme;
+// without the skip those lanes select the same value, so the result has the
+// same bits.  The values are SC times the split fluxes.  Without LINEAR (the
+// adjoint, which needs the decisions and the value, but not its last bits)
+// the linear scheme is not selected.  When FLAGS, `bits` receives
 // delta_k (1 = smooth) in bit k and, above bit 7, the limiter's decisions
 // (what the adjoint with frozen branches needs): MP limiters, per candidate
 // k the median's choice in bits 8 + 2k (0 the candidate, 1 the lower bound,
 // 2 the upper) and mp_code in bits 20..31; TVD minmod, the minmod's pick in
 // bits 8..9 (0 none, 1 d-, 2 d+); TVD5, bits 8..9 (0 none, 1 2d-, 2 2d+,
 // 3 the fifth-order slope).
-template <int K, int LIM, bool FLAGS, bool ADAPT, bool SKIP = false>
+template <int K, int LIM, bool FLAGS, bool ADAPT, bool SKIP = false, int SC = 2, bool LINEAR = true>
 __device__ __forceinline__ double teno_m(const double (&v)[K], const TenoParams& tp, uint32_t& bits) {
   using T = TenoTables<K>;
   constexpr int NK = K - 2;
@@ -315,20 +319,23 @@ __device__ __forceinline__ double teno_m(const double (&v)[K], const TenoParams&
   double c[NK];
   double beta[NK], tau;
   teno_indicators<K>(D, beta, tau);
-  if constexpr (SKIP && LIM != LIM_TENO) {
-    static_assert(!FLAGS, "the skip leaves no decision codes");
-    const bool rough = !teno_all_smooth<K>(beta, tau, tp);
+  if constexpr (SKIP) {
+    const bool rough = !teno_all_smooth<K, SC>(beta, tau, tp);
     if (__builtin_amdgcn_ballot_w64(rough) == 0) {  // uniform across the wavefront
-      T::candidates(D, c);
-      double acc = 0.0;
-#pragma unroll
-      for (int k = 0; k < NK; ++k) acc = fma(T::d(k), c[k], acc);
-      return v[C0] + acc;
+      if constexpr (FLAGS) bits |= (1u << NK) - 1u;
+      return v[C0] + T::linear(D);
     }
   }
   T::candidates(D, c);
   bool smooth[NK];
-  teno_cutoff<K, ADAPT>(D, beta, tau, tp, smooth);
+  teno_cutoff<K, ADAPT, SC>(D, beta, tau, tp, smooth);
+  // a lane whose candidates are all smooth takes the linear scheme's value in
+  // every kernel, whatever its wavefront does: the result does not depend on
+  // how the faces are grouped
+  bool linear = true;
+#pragma unroll
+  for (int k = 0; k < NK; ++k) linear &= smooth[k];
+  const double flin = v[C0] + T::linear(D);
 
   // limiter on the nonsmooth candidates (Eq. mp_flux), relative to v_i
   const double dm = D[C0 - 1];  // f_i - f_{i-1}
@@ -396,7 +403,7 @@ __device__ __forceinline__ double teno_m(const double (&v)[K], const TenoParams&
       den = smooth[k] ? den + T::d(k) : den;
       if constexpr (FLAGS) bits |= (smooth[k] ? 1u : 0u) << k;
     }
-    return fma(num, rcp(den), v[C0]);
+    return LINEAR && linear ? flin : fma(num, rcp(den), v[C0]);
   } else {
     // assembly with the optimal weights, no renormalisation (Eq. reconstuction)
     double acc = 0.0;
@@ -411,7 +418,7 @@ __device__ __forceinline__ double teno_m(const double (&v)[K], const TenoParams&
       acc = fma(T::d(k), smooth[k] ? c[k] : lim, acc);
       if constexpr (FLAGS) bits |= (smooth[k] ? 1u : 0u) << k;
     }
-    return v[C0] + acc;
+    return LINEAR && linear ? flin : v[C0] + acc;
   }
 }
 
@@ -566,7 +573,9 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
   for (int d = 0; d < ND; ++d) q2t = fma(ut[d], ut[d], q2t);
   const double b2 = 0.5 * q2t * b1;
 
-  // left eigenvectors applied to a conservative vector X
+  // left eigenvectors applied to a conservative vector X, the acoustic rows
+  // doubled: their fields are reconstructed at SC = 4, and the halving joins
+  // the one of the reconstructed sum (exact factors, the same bits)
   // (no contraction: the same roundings for every stencil cell)
   auto project = [&](const double (&X)[NF], double (&w)[NF]) {
 #pragma clang fp contract(off)
@@ -575,15 +584,15 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
     for (int d = 0; d < ND; ++d) um = fma(ut[d], X[1 + d], um);
     const double A = fma(b2, X[0], b1 * (X[NF - 1] - um));
     const double Bn = fma(ut[0], X[0], -X[1]);  // B = Bn / c
-    w[0] = 0.5 * fma(Bn, cinv, A);
+    w[0] = fma(Bn, cinv, A);
     w[1] = X[0] - A;
 #pragma unroll
     for (int t = 1; t < ND; ++t) w[1 + t] = fma(-ut[t], X[0], X[1 + t]);
-    w[NF - 1] = 0.5 * fma(-Bn, cinv, A);
+    w[NF - 1] = fma(-Bn, cinv, A);
   };
 
   double fc[NF];
-  if constexpr (!FLAGS && P::kReread && LIM != LIM_TENO) {
+  if constexpr (P::kReread) {
     // Group by group of fields from the staged cells: each group's stencil
     // values are projected from a fresh read of the cells (only the group's
     // rows of the eigenvectors survive), so that no array of every field's
@@ -610,8 +619,12 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
       for (int q = 0; q < NF; ++q) {
         if ((mask >> q) & 1u) {
           bits[0][q] = bits[1][q] = 0u;
-          fc[q] = 0.5 * (teno_m<K, LIM, false, ADAPT, true>(vp[q], tp, bits[0][q]) +
-                         teno_m<K, LIM, false, ADAPT, true>(vm[q], tp, bits[1][q]));
+          if (q == 0 || q == NF - 1)
+            fc[q] = 0.25 * (teno_m<K, LIM, FLAGS, ADAPT, true, 4>(vp[q], tp, bits[0][q]) +
+                            teno_m<K, LIM, FLAGS, ADAPT, true, 4>(vm[q], tp, bits[1][q]));
+          else
+            fc[q] = 0.5 * (teno_m<K, LIM, FLAGS, ADAPT, true>(vp[q], tp, bits[0][q]) +
+                           teno_m<K, LIM, FLAGS, ADAPT, true>(vm[q], tp, bits[1][q]));
         }
       }
     };
@@ -648,7 +661,11 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
 #pragma unroll
       for (int m = 0; m < K; ++m) lf_split2(G[m][q], alpha, W[m][q], vp[m], vm[K - 1 - m]);
       bits[0][q] = bits[1][q] = 0u;
-      fc[q] = 0.5 * (teno_m<K, LIM, FLAGS, ADAPT>(vp, tp, bits[0][q]) + teno_m<K, LIM, FLAGS, ADAPT>(vm, tp, bits[1][q]));
+      if (q == 0 || q == NF - 1)
+        fc[q] = 0.25 * (teno_m<K, LIM, FLAGS, ADAPT, false, 4>(vp, tp, bits[0][q]) +
+                        teno_m<K, LIM, FLAGS, ADAPT, false, 4>(vm, tp, bits[1][q]));
+      else
+        fc[q] = 0.5 * (teno_m<K, LIM, FLAGS, ADAPT>(vp, tp, bits[0][q]) + teno_m<K, LIM, FLAGS, ADAPT>(vm, tp, bits[1][q]));
     }
   }
 
@@ -703,36 +720,5 @@ __device__ __forceinline__ void face_flux(P& prov, const FaceParams& fp, double 
     euler_face<NF, K, LIM, FLAGS, ADAPT>(prov, fp.gamma, fp.tp, F, bits);
   }
 }
-
-// ---------------------------------------------------------------------------
-// Cell providers
-// ---------------------------------------------------------------------------
-
-// straight from global memory (face j of a line)
-template <int NF, int K>
-struct GlobalCells {
-  static constexpr bool kReread = false;  // re-reads would go to memory
-  const double* __restrict__ U;
-  long N;
-  const int* fld;
-  Line L;
-  int j;
-  double gamma;
-  __device__ __forceinline__ void load(int pos, double (&X)[NF]) const {
-    const long cell = cell_at(L, pos);
-#pragma unroll
-    for (int q = 0; q < NF; ++q) X[q] = U[fld[q] * N + cell];
-  }
-  __device__ __forceinline__ void cell(int m, double (&X)[NF], double (&F)[NF], double& lam) const {
-    load(j - K / 2 + m, X);
-    cell_physics<NF>(X, gamma, F, lam);
-  }
-  __device__ __forceinline__ void roe(int s, RoeIn<NF>& r) const {
-    double X[NF];
-    load(j - 1 + s, X);
-    roe_input<NF>(X, gamma, r);
-  }
-  __device__ __forceinline__ double value(int m) const { return U[cell_at(L, j - K / 2 + m)]; }
-};
 
 }  // namespace tenom

@@ -1,8 +1,8 @@
 // Kernels of the TENO-M path and their launchers.
 //
-//  k_faces         one thread per face of one axis; writes the face fluxes
-//                  (and optionally the smoothness flags).  The unit the
-//                  reconstruct_faces call exposes.
+//  k_faces         face fluxes (and optionally the smoothness flags) of one
+//                  axis from staged tiles.  The unit the reconstruct_faces
+//                  call exposes.
 //  k_sweep_row     sweep along x (unit stride).  A 256-thread workgroup owns
 //                  one row segment: the segment's cells are staged in LDS
 //                  with their flux, signal speed and Roe inputs, each thread
@@ -100,53 +100,6 @@ __device__ __forceinline__ void epi_store(const SweepParams<NF>& p, long N, long
 }
 
 // ---------------------------------------------------------------------------
-template <int NF, int K, int LIM, bool ADAPT>
-__global__ __launch_bounds__(256) void k_faces(const double* __restrict__ U, double* __restrict__ Fhat,
-                                               uint8_t* __restrict__ flags, int axis, int nx, int ny, int nz,
-                                               int bc, int fld0, int fld1, int fld2, int fld3, int fld4,
-                                               FaceParams fp) {
-  const int fnx = nx + (axis == 0), fny = ny + (axis == 1), fnz = nz + (axis == 2);
-  const long nfaces = (long)fnx * fny * fnz;
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nfaces) return;
-  const int fx = (int)(t % fnx);
-  const int fy = (int)((t / fnx) % fny);
-  const int fz = (int)(t / ((long)fnx * fny));
-  const long N = (long)nx * ny * nz;
-  Line L;
-  int j;
-  if (axis == 0) {
-    L = Line{(long)nx * (fy + (long)ny * fz), 1, nx, bc};
-    j = fx;
-  } else if (axis == 1) {
-    L = Line{fx + (long)nx * ny * fz, nx, ny, bc};
-    j = fy;
-  } else {
-    L = Line{fx + (long)nx * fy, (long)nx * ny, nz, bc};
-    j = fz;
-  }
-  const int fall[5] = {fld0, fld1, fld2, fld3, fld4};
-  int fld[NF];
-#pragma unroll
-  for (int q = 0; q < NF; ++q) fld[q] = fall[q];
-  GlobalCells<NF, K> prov{U, N, fld, L, j, fp.gamma};
-  double F[NF];
-  uint32_t bits[2][NF];
-  if (flags) {
-    face_flux<NF, K, LIM, ADAPT, true>(prov, fp, F, bits);
-#pragma unroll
-    for (int q = 0; q < NF; ++q) {
-      flags[(long)q * nfaces + t] = (uint8_t)bits[0][q];
-      flags[(long)(NF + q) * nfaces + t] = (uint8_t)bits[1][q];
-    }
-  } else {
-    face_flux<NF, K, LIM, ADAPT, false>(prov, fp, F, bits);
-  }
-#pragma unroll
-  for (int q = 0; q < NF; ++q) Fhat[(long)fld[q] * nfaces + t] = F[q];
-}
-
-// ---------------------------------------------------------------------------
 // Row sweep.  Cells of the segment (plus K-1 halo cells) are staged once in
 // LDS together with their physical flux, signal speed and Roe inputs, so a
 // face reads its K cells instead of recomputing them.
@@ -209,17 +162,18 @@ struct StagedCells {
 // Stage cell `cell` of the grid at staging index c: its state and, for the
 // Euler equations, its flux, signal speed and Roe inputs.
 template <int NF>
-__device__ __forceinline__ void stage_cell(double* stage, int nc, int c, const SweepParams<NF>& p, long N, long cell) {
+__device__ __forceinline__ void stage_cell(double* stage, int nc, int c, const double* __restrict__ U,
+                                           const int (&fld)[NF], double gamma, long N, long cell) {
   double X[NF];
 #pragma unroll
-  for (int q = 0; q < NF; ++q) X[q] = p.U[p.fld[q] * N + cell];
+  for (int q = 0; q < NF; ++q) X[q] = U[fld[q] * N + cell];
 #pragma unroll
   for (int q = 0; q < NF; ++q) stage[q * nc + c] = X[q];
   if constexpr (NF > 1) {
     double F[NF], lam;
     RoeIn<NF> r;
-    cell_physics<NF>(X, p.fp.gamma, F, lam);
-    roe_input<NF>(X, p.fp.gamma, r);
+    cell_physics<NF>(X, gamma, F, lam);
+    roe_input<NF>(X, gamma, r);
 #pragma unroll
     for (int q = 0; q < NF; ++q) stage[(NF + q) * nc + c] = F[q];
     stage[(2 * NF) * nc + c] = lam;
@@ -260,13 +214,13 @@ void k_sweep_row(SweepParams<NF> p) {
   __builtin_amdgcn_s_setprio(3);
 
   // stage cells c_begin - K/2 .. c_begin + nface + K/2 - 2
-  for (int c = t; c < nstage; c += 256) stage_cell<NF>(stage, NC, c, p, N, cell_at(L, c_begin - K / 2 + c));
+  for (int c = t; c < nstage; c += 256) stage_cell<NF>(stage, NC, c, p.U, p.fld, p.fp.gamma, N, cell_at(L, c_begin - K / 2 + c));
   __syncthreads();
 
   double F[NF];
   __builtin_amdgcn_s_setprio(0);
   if (t < nface) {
-    StagedCells<NF, K> prov{stage, NC, t};
+    StagedCells<NF, K, 1, true> prov{stage, NC, t};
     uint32_t bits[2][NF];
     face_flux<NF, K, LIM, ADAPT, false>(prov, p.fp, F, bits);
   }
@@ -425,7 +379,7 @@ void k_sweep_tile(SweepParams<NF> p, int axis) {
     {
       const Where w = where();
       for (int r = w.f; r < nfk + K - 1; r += FJ)
-        stage_cell<NF>(stage, NC, r * TX + w.col, p, N, cell_at(w.L, c0 + j0 - K / 2 + r + rot));
+        stage_cell<NF>(stage, NC, r * TX + w.col, p.U, p.fld, p.fp.gamma, N, cell_at(w.L, c0 + j0 - K / 2 + r + rot));
     }
     __syncthreads();
     __builtin_amdgcn_s_setprio(0);
@@ -491,6 +445,89 @@ void k_sweep_tile(SweepParams<NF> p, int axis) {
     }
     __syncthreads();  // the next chunk's staging overwrites the cells read here
   }
+}
+
+// ---------------------------------------------------------------------------
+// Face fluxes of one axis (and, with FLAGS, the smoothness bytes).  A
+// 256-thread workgroup takes 256 / TX faces of TX adjacent lines, staged as one
+// chunk of the tile sweep: the cell physics once per cell instead of K times,
+// and wavefronts whose faces are all smooth skip cutoff and limiter.  Bound by
+// VALU issue like the sweeps.  TX = 1 serves single lines (1D).  64^3 Euler
+// with flags at eight points: 50 us from global memory, one thread per face,
+// 25 staged.
+// ---------------------------------------------------------------------------
+template <int NF>
+struct FacesParams {
+  const double* U;
+  double* Fhat;
+  uint8_t* flags;
+  int axis, nx, ny, nz, bc;
+  int fld[NF];
+  FaceParams fp;
+};
+
+template <int NF, int K, int LIM, bool ADAPT, int TX, bool FLAGS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RowOccupancy<NF, K>::WAVES)))
+void k_faces(FacesParams<NF> p) {
+  constexpr int FJ = 256 / TX;
+  constexpr int ROWS = FJ + K - 1, NC = ROWS * TX;
+  __shared__ double stage[RowStage<NF>::NE * NC];
+  const int n = p.axis == 0 ? p.nx : (p.axis == 1 ? p.ny : p.nz);
+  const int across = p.axis == 0 ? p.ny : p.nx;  // the lines side by side
+  const int nfl = p.bc == 0 ? n : n + 1;  // a periodic line's face n is its face 0
+  const int ncg = (across + TX - 1) / TX, nch = (nfl + FJ - 1) / FJ;
+  const int b = (int)blockIdx.x;
+  const int o = b / ncg / nch;  // z of an x or y line, y of a z line
+  const int j0 = (b / ncg % nch) * FJ;
+  const int nfk = min(FJ, nfl - j0);
+  const long N = (long)p.nx * p.ny * p.nz;
+  const int t = threadIdx.x, col = t % TX, f = t / TX;
+  const int c = (b % ncg) * TX + col;
+  const int cs = min(c, across - 1);  // lines beyond the grid stage a real line and store nothing
+  Line L;
+  long face, fstride;  // index of the line's face 0, step along the axis
+  if (p.axis == 0) {
+    const long r = cs + (long)p.ny * o;
+    L = Line{r * p.nx, 1, n, p.bc};
+    face = r * (p.nx + 1);
+    fstride = 1;
+  } else if (p.axis == 1) {
+    L = Line{cs + (long)p.nx * p.ny * o, p.nx, n, p.bc};
+    face = cs + (long)p.nx * (p.ny + 1) * o;
+    fstride = p.nx;
+  } else {
+    L = Line{cs + (long)p.nx * o, (long)p.nx * p.ny, n, p.bc};
+    face = cs + (long)p.nx * o;
+    fstride = (long)p.nx * p.ny;
+  }
+  __builtin_amdgcn_s_setprio(3);  // high while loads and stores issue, as in the sweeps
+  for (int r = f; r < nfk + K - 1; r += FJ)
+    stage_cell<NF>(stage, NC, r * TX + col, p.U, p.fld, p.fp.gamma, N, cell_at(L, j0 - K / 2 + r));
+  __syncthreads();
+  __builtin_amdgcn_s_setprio(0);
+  if (f >= nfk) return;
+  double F[NF];
+  uint32_t bits[2][NF];
+  {
+    StagedCells<NF, K, TX, true> prov{stage, NC, f * TX + col};
+    face_flux<NF, K, LIM, ADAPT, FLAGS>(prov, p.fp, F, bits);
+  }
+  if (c >= across) return;
+  __builtin_amdgcn_s_setprio(3);
+  const long nfaces = N / n * (n + 1);
+  auto store = [&](int j) {
+    const long at = face + (long)j * fstride;
+#pragma unroll
+    for (int q = 0; q < NF; ++q) {
+      p.Fhat[(long)p.fld[q] * nfaces + at] = F[q];
+      if constexpr (FLAGS) {
+        p.flags[(long)q * nfaces + at] = (uint8_t)bits[0][q];
+        p.flags[(long)(NF + q) * nfaces + at] = (uint8_t)bits[1][q];
+      }
+    }
+  };
+  store(j0 + f);
+  if (j0 + f == 0 && nfl == n) store(n);
 }
 
 // ---------------------------------------------------------------------------
@@ -674,13 +711,38 @@ struct SweepLaunch {
   hipStream_t stream;
 };
 
+template <int NF, int K, int LIM, bool ADAPT, int TX>
+hipError_t launch_faces_tx(const FacesLaunch& a) {
+  FacesParams<NF> p;
+  p.U = a.U;
+  p.Fhat = a.Fhat;
+  p.flags = a.flags;
+  p.axis = a.axis;
+  p.nx = a.nx;
+  p.ny = a.ny;
+  p.nz = a.nz;
+  p.bc = a.bc;
+  p.fp = a.fp;
+  for (int q = 0; q < NF; ++q) p.fld[q] = a.fld[q];
+  constexpr int FJ = 256 / TX;
+  const int n = a.axis == 0 ? a.nx : (a.axis == 1 ? a.ny : a.nz);
+  const long across = a.axis == 0 ? a.ny : a.nx, others = a.axis == 2 ? a.ny : a.nz;
+  const int nfl = a.bc == 0 ? n : n + 1;
+  const long blocks = others * ((across + TX - 1) / TX) * ((nfl + FJ - 1) / FJ);
+  if (a.flags)
+    hipLaunchKernelGGL((k_faces<NF, K, LIM, ADAPT, TX, true>), dim3((unsigned)blocks), dim3(256), 0, a.stream, p);
+  else
+    hipLaunchKernelGGL((k_faces<NF, K, LIM, ADAPT, TX, false>), dim3((unsigned)blocks), dim3(256), 0, a.stream, p);
+  return hipGetLastError();
+}
+
 template <int NF, int K, int LIM, bool ADAPT>
 hipError_t launch_faces(const FacesLaunch& a) {
-  const long nfaces = (long)(a.nx + (a.axis == 0)) * (a.ny + (a.axis == 1)) * (a.nz + (a.axis == 2));
-  const unsigned blocks = (unsigned)((nfaces + 255) / 256);
-  hipLaunchKernelGGL((k_faces<NF, K, LIM, ADAPT>), dim3(blocks), dim3(256), 0, a.stream, a.U, a.Fhat, a.flags, a.axis,
-                     a.nx, a.ny, a.nz, a.bc, a.fld[0], a.fld[1], a.fld[2], a.fld[3], a.fld[4], a.fp);
-  return hipGetLastError();
+  // single lines fill a workgroup with 256 faces of one line
+  if constexpr (NF == 3) return launch_faces_tx<NF, K, LIM, ADAPT, 1>(a);
+  if constexpr (NF == 1)
+    if (a.ny == 1 && a.nz == 1) return launch_faces_tx<NF, K, LIM, ADAPT, 1>(a);
+  if constexpr (NF != 3) return launch_faces_tx<NF, K, LIM, ADAPT, kTileColumns>(a);
 }
 
 template <int NF, int K, int LIM, bool ADAPT>

@@ -14,13 +14,17 @@ template <> struct TenoTables<6> {
   }
   // every beta below is beta_scale times the measure of Eq. measureTENO;
   // the cutoff scales eps by the same factor
-  static constexpr double beta_scale = 1.0;
+  static constexpr double beta_scale = (3.0 / 4.0);
   // candidate fluxes minus v_i, from the candidate stencils of Table 1
   static __device__ __forceinline__ void candidates(const double* D, double* c) {
     c[0] = fma((1.0 / 3.0), D[2], (1.0 / 6.0) * D[1]);
     c[1] = fma((-1.0 / 6.0), D[3], (2.0 / 3.0) * D[2]);
     c[2] = fma((5.0 / 6.0), D[1], (-1.0 / 3.0) * D[0]);
     c[3] = fma((1.0 / 12.0), D[4], fma((-1.0 / 3.0), D[3], (3.0 / 4.0) * D[2]));
+  }
+  // sum_k d_k c_k: the linear scheme all smooth candidates assemble to, minus v_i
+  static __device__ __forceinline__ double linear(const double* D) {
+    return fma((-1.0 / 60.0), D[0] - D[4], fma((7.0 / 60.0), D[1] - D[3], 0.5 * D[2]));
   }
   // adjoint of candidates: Dbar[j] += sum_k (d c_k / d D_j) cbar[k]
   static __device__ __forceinline__ void candidates_vjp(const double* cbar, double* Dbar) {
@@ -32,34 +36,31 @@ template <> struct TenoTables<6> {
   }
   // smoothness measures beta_k (candidates) and beta_K (full stencil)
   static __device__ __forceinline__ void betas(const double* D, double* beta, double& betaK) {
+    const double s0 = ((39.0 / 64.0) * D[2]) * D[2];
+    const double s1 = ((39.0 / 64.0) * D[1]) * D[1];
     {
       const double y0 = fma((-5.0 / 8.0), D[2], D[1]);
-      const double y1 = D[2];
-      beta[0] = fma((13.0 / 16.0) * y1, y1, (4.0 / 3.0) * (y0 * y0));
+      beta[0] = fma(y0, y0, s0);
     }
     {
-      const double y0 = fma((-11.0 / 20.0), D[3], D[2]);
-      const double y1 = D[3];
-      beta[1] = fma((13.0 / 40.0) * y1, y1, (10.0 / 3.0) * (y0 * y0));
+      const double y0 = fma((-11.0 / 8.0), D[2], D[3]);
+      beta[1] = fma(y0, y0, s0);
     }
     {
       const double y0 = fma((-11.0 / 8.0), D[1], D[0]);
-      const double y1 = D[1];
-      beta[2] = fma((13.0 / 16.0) * y1, y1, (4.0 / 3.0) * (y0 * y0));
+      beta[2] = fma(y0, y0, s1);
     }
     {
-      const double y0 = fma((927.0 / 2107.0), D[4], fma((-2594.0 / 2107.0), D[3], D[2]));
-      const double y1 = fma((-13313.0 / 27098.0), D[4], D[3]);
-      const double y2 = D[4];
-      beta[3] = fma((10153.0 / 162588.0) * y2, y2, fma((13549.0 / 6321.0) * y1, y1, (2107.0 / 240.0) * (y0 * y0)));
+      const double y0 = fma((927.0 / 547.0), D[2], fma((-1394.0 / 547.0), D[3], D[4]));
+      const double y1 = fma((-3167.0 / 2126.0), D[2], D[3]);
+      beta[3] = fma((547.0 / 320.0) * y0, y0, fma((1063.0 / 2188.0) * y1, y1, (3124.0 / 3189.0) * s0));
     }
     {
-      const double y0 = fma((122810.0 / 271779.0), D[4], fma((-606571.0 / 271779.0), D[3], fma((1124555.0 / 271779.0), D[2], fma((-306207.0 / 90593.0), D[1], D[0]))));
-      const double y1 = fma((-11287126279.0 / 39800226981.0), D[4], fma((49345301363.0 / 39800226981.0), D[3], fma((-74779183825.0 / 39800226981.0), D[2], D[1])));
-      const double y2 = fma((569087044063309.0 / 2535830006332177.0), D[4], fma((-2191308206103902.0 / 2535830006332177.0), D[3], D[2]));
-      const double y3 = fma(-0.3841978250666033, D[4], D[3]);
-      const double y4 = D[4];
-      betaK = fma(0.03897812227306876 * y4, y4, fma(1.0316113515772065 * y3, y3, fma((2535830006332177.0 / 601779431952720.0) * y2, y2, fma((13266742327.0 / 3652709760.0) * y1, y1, (90593.0 / 40320.0) * (y0 * y0)))));
+      const double y0 = fma((1124555.0 / 271779.0), D[2], fma((-606571.0 / 271779.0), D[3], fma((-306207.0 / 90593.0), D[1], fma((122810.0 / 271779.0), D[4], D[0]))));
+      const double y1 = fma((94709347673.0 / 22867021007.0), D[2], fma((-81876422035.0 / 22867021007.0), D[3], fma((-33861378837.0 / 22867021007.0), D[1], D[4])));
+      const double y2 = fma((-294807913978694.0 / 242805260682217.0), D[2], fma((93932261176693.0 / 242805260682217.0), D[3], D[1]));
+      const double y3 = fma((-5806166826175189.0 / 3848503014457426.0), D[2], D[3]);
+      betaK = fma((90593.0 / 53760.0) * y0, y0, fma((22867021007.0 / 43832517120.0) * y1, y1, fma((242805260682217.0 / 153666381167040.0) * y2, y2, fma((1924251507228713.0 / 4856105213644340.0) * y3, y3, 0.9782800937737386 * s0))));
     }
   }
 };
@@ -74,7 +75,7 @@ template <> struct TenoTables<8> {
   }
   // every beta below is beta_scale times the measure of Eq. measureTENO;
   // the cutoff scales eps by the same factor
-  static constexpr double beta_scale = (20475.0 / 16384.0);
+  static constexpr double beta_scale = (3.0 / 4.0);
   // candidate fluxes minus v_i, from the candidate stencils of Table 1
   static __device__ __forceinline__ void candidates(const double* D, double* c) {
     c[0] = (1.0 / 6.0) * (fma(2.0, D[3], D[2]));
@@ -83,6 +84,10 @@ template <> struct TenoTables<8> {
     c[3] = (1.0 / 12.0) * (fma(-4.0, D[4], 9.0 * D[3]) + D[5]);
     c[4] = (1.0 / 12.0) * (fma(13.0, D[2], fma(-10.0, D[1], 3.0 * D[0])));
     c[5] = (1.0 / 60.0) * (fma(-3.0, D[6], fma(14.0, D[5], fma(-29.0, D[4], 48.0 * D[3]))));
+  }
+  // sum_k d_k c_k: the linear scheme all smooth candidates assemble to, minus v_i
+  static __device__ __forceinline__ double linear(const double* D) {
+    return fma((1.0 / 280.0), D[0] - D[6], fma((-13.0 / 420.0), D[1] - D[5], fma((113.0 / 840.0), D[2] - D[4], 0.5 * D[3])));
   }
   // adjoint of candidates: Dbar[j] += sum_k (d c_k / d D_j) cbar[k]
   static __device__ __forceinline__ void candidates_vjp(const double* cbar, double* Dbar) {
@@ -102,49 +107,44 @@ template <> struct TenoTables<8> {
   }
   // smoothness measures beta_k (candidates) and beta_K (full stencil)
   static __device__ __forceinline__ void betas(const double* D, double* beta, double& betaK) {
+    const double s0 = ((39.0 / 64.0) * D[3]) * D[3];
+    const double s1 = ((39.0 / 64.0) * D[2]) * D[2];
     {
-      const double y0 = D[2] + D[3];
-      const double y1 = -D[2] + D[3];
-      beta[0] = fma((88725.0 / 65536.0) * y1, y1, (20475.0 / 65536.0) * (y0 * y0));
+      const double y0 = fma((-5.0 / 8.0), D[3], D[2]);
+      beta[0] = fma(y0, y0, s0);
     }
     {
-      const double y0 = 3.0 * D[3] - D[4];
-      const double y1 = -D[3] + D[4];
-      beta[1] = fma((88725.0 / 65536.0) * y1, y1, (20475.0 / 65536.0) * (y0 * y0));
+      const double y0 = fma((-11.0 / 8.0), D[3], D[4]);
+      beta[1] = fma(y0, y0, s0);
     }
     {
-      const double y0 = fma(3.0, D[2], -D[1]);
-      const double y1 = -D[1] + D[2];
-      beta[2] = fma((88725.0 / 65536.0) * y1, y1, (20475.0 / 65536.0) * (y0 * y0));
+      const double y0 = fma((-11.0 / 8.0), D[2], D[1]);
+      beta[2] = fma(y0, y0, s1);
     }
     {
-      const double y0 = fma(2.0, D[5], fma(-7.0, D[4], 11.0 * D[3]));
-      const double y1 = fma(3.0, D[4], -2.0 * D[3]) - D[5];
-      const double y2 = fma(-2.0, D[4], D[3]) + D[5];
-      beta[3] = fma((355355.0 / 262144.0) * y2, y2, fma((88725.0 / 65536.0) * y1, y1, (2275.0 / 65536.0) * (y0 * y0)));
+      const double y0 = fma((927.0 / 547.0), D[3], fma((-1394.0 / 547.0), D[4], D[5]));
+      const double y1 = fma((-3167.0 / 2126.0), D[3], D[4]);
+      beta[3] = fma((547.0 / 320.0) * y0, y0, fma((1063.0 / 2188.0) * y1, y1, (3124.0 / 3189.0) * s0));
     }
     {
-      const double y0 = fma(11.0, D[2], fma(-7.0, D[1], 2.0 * D[0]));
-      const double y1 = fma(2.0, D[2], fma(-3.0, D[1], D[0]));
-      const double y2 = fma(-2.0, D[1], D[0]) + D[2];
-      beta[4] = fma((355355.0 / 262144.0) * y2, y2, fma((88725.0 / 65536.0) * y1, y1, (2275.0 / 65536.0) * (y0 * y0)));
+      const double y0 = fma((927.0 / 547.0), D[2], fma((-1394.0 / 547.0), D[1], D[0]));
+      const double y1 = fma((-3167.0 / 2126.0), D[2], D[1]);
+      beta[4] = fma((547.0 / 320.0) * y0, y0, fma((1063.0 / 2188.0) * y1, y1, (3124.0 / 3189.0) * s1));
     }
     {
-      const double y0 = fma(-3.0, D[6], fma(13.0, D[5], fma(-23.0, D[4], 25.0 * D[3])));
-      const double y1 = fma(119.0, D[6], fma(-487.0, D[5], fma(747.0, D[4], -379.0 * D[3])));
-      const double y2 = fma(-3.0, D[6], fma(11.0, D[5], fma(-13.0, D[4], 5.0 * D[3])));
-      const double y3 = fma(-3.0, D[5], fma(3.0, D[4], -D[3])) + D[6];
-      beta[5] = fma((1421461.0 / 1048576.0) * y3, y3, fma((355355.0 / 1048576.0) * y2, y2, fma((21.0 / 262144.0) * y1, y1, (2275.0 / 262144.0) * (y0 * y0))));
+      const double y0 = fma((-86329.0 / 45316.0), D[3], fma((100839.0 / 22658.0), D[4], fma((-163185.0 / 45316.0), D[5], D[6])));
+      const double y1 = fma((1813059.0 / 838195.0), D[3], fma((-41089198.0 / 14249315.0), D[4], D[5]));
+      const double y2 = fma((-350813921.0 / 232768856.0), D[3], D[4]);
+      beta[5] = fma((11329.0 / 3360.0) * y0, y0, fma((2849863.0 / 5800448.0) * y1, y1, fma((29096107.0 / 71246575.0) * y2, y2, (1110161041.0 / 1134748173.0) * s0)));
     }
     {
-      const double y0 = fma(-3.0, D[6], fma(25.0, D[5], fma(-101.0, D[4], fma(319.0, D[3], fma(214.0, D[2], fma(-38.0, D[1], 4.0 * D[0]))))));
-      const double y1 = fma(31.0, D[5], fma(-386.0, D[4], fma(3733.0, D[3], fma(-3733.0, D[2], fma(386.0, D[1], -31.0 * D[0])))));
-      const double y2 = fma(231457.0, D[6], fma(-1883352.0, D[5], fma(6923805.0, D[4], fma(-7586480.0, D[3], fma(514515.0, D[2], fma(2063208.0, D[1], -263153.0 * D[0]))))));
-      const double y3 = fma(-8595883.0, D[5], fma(94152011.0, D[4], fma(-239476618.0, D[3], fma(239476618.0, D[2], fma(-94152011.0, D[1], 8595883.0 * D[0])))));
-      const double y4 = fma(-14403157668.0, D[6], fma(107939005549.0, D[5], fma(-280607543643.0, D[4], fma(331103272442.0, D[3], fma(-173007245938.0, D[2], fma(21858767385.0, D[1], 7116901873.0 * D[0]))))));
-      const double y5 = fma(-5.0, D[4], fma(10.0, D[3], fma(-10.0, D[2], fma(5.0, D[1], -D[0])))) + D[5];
-      const double y6 = fma(-6.0, D[5], fma(15.0, D[4], fma(-20.0, D[3], fma(15.0, D[2], fma(-6.0, D[1], D[0]))))) + D[6];
-      betaK = fma(1.3556117992444507 * y6, y6, fma(1.3556117987064134 * y5, y5, fma(7.317932587277675e-22 * y4, y4, fma((1.0 / 1931700816838656.0) * y3, y3, fma((13.0 / 148588084592640.0) * y2, y2, fma((1.0 / 5505024.0) * y1, y1, (13.0 / 1835008.0) * (y0 * y0)))))));
+      const double y0 = fma((-1985504465170.0 / 139164877641.0), D[3], fma((1291035808745.0 / 139164877641.0), D[4], fma((33287419730.0 / 2728723091.0), D[2], fma((-148180843597.0 / 46388292547.0), D[5], fma((-760759377191.0 / 139164877641.0), D[1], fma((63540330136.0 / 139164877641.0), D[6], D[0]))))));
+      const double y1 = fma(-13.515941989697778, D[3], fma(12.478417152406076, D[4], fma(7.105483305004352, D[2], fma(-5.631116607688648, D[5], fma(-1.4522842377772984, D[1], D[6])))));
+      const double y2 = fma(3.8771268766168543, D[3], fma(-1.9991216022994762, D[4], fma(-3.2886087899408385, D[2], fma(0.3842944201275226, D[5], D[1]))));
+      const double y3 = fma(4.238216248470905, D[3], fma(-3.6269357500773, D[4], fma(-1.5238975608025418, D[2], D[5])));
+      const double y4 = fma(-1.2120737331410925, D[3], fma(0.3854478132403791, D[4], D[2]));
+      const double y5 = fma(-1.508775853969574, D[3], D[4]);
+      betaK = fma((46388292547.0 / 27675648000.0) * y0, y0, fma(0.5581038616642391 * y1, y1, fma(1.5708030070653975 * y2, y2, fma(0.3983582187938113 * y3, y3, fma(1.576857200520724 * y4, y4, fma(0.39470622634302344 * y5, y5, 0.9782785997787286 * s0))))));
     }
   }
 };
