@@ -321,7 +321,7 @@ __device__ __forceinline__ double teno_m(const double (&v)[K], const TenoParams&
   teno_indicators<K>(D, beta, tau);
   if constexpr (SKIP) {
     const bool rough = !teno_all_smooth<K, SC>(beta, tau, tp);
-    if (__builtin_amdgcn_ballot_w64(rough) == 0) {  // uniform across the wavefront
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(rough) == 0, 1)) {  // uniform across the wavefront
       if constexpr (FLAGS) bits |= (1u << NK) - 1u;
       return v[C0] + T::linear(D);
     }
@@ -337,6 +337,7 @@ __device__ __forceinline__ double teno_m(const double (&v)[K], const TenoParams&
   for (int k = 0; k < NK; ++k) linear &= smooth[k];
   const double flin = v[C0] + T::linear(D);
 
+  constexpr bool CODES = FLAGS && !SKIP;  // the limiter's decisions too
   // limiter on the nonsmooth candidates (Eq. mp_flux), relative to v_i
   const double dm = D[C0 - 1];  // f_i - f_{i-1}
   const double dp = D[C0];      // f_{i+1} - f_i
@@ -346,7 +347,7 @@ __device__ __forceinline__ double teno_m(const double (&v)[K], const TenoParams&
     mp_bounds<K, LIM>(D, tp, ms);
     lo = ms.lo;
     hi = ms.hi;
-    if constexpr (FLAGS) {
+    if constexpr (CODES) {
       bits |= mp_code<K, LIM>(D, ms) << 20;
 #pragma unroll
       for (int k = 0; k < NK; ++k) {
@@ -358,7 +359,7 @@ __device__ __forceinline__ double teno_m(const double (&v)[K], const TenoParams&
     }
   } else if constexpr (LIM == LIM_TVD_MINMOD) {
     ftvd = 0.5 * minmod2(dm, dp);
-    if constexpr (FLAGS) {
+    if constexpr (CODES) {
       const double a[2] = {dm, dp};
       bits |= minmod_pick(a, 2) << 8;
     }
@@ -368,7 +369,7 @@ __device__ __forceinline__ double teno_m(const double (&v)[K], const TenoParams&
     const double dn = fmin(0.0, fmax(fmax(2.0 * dm, 2.0 * dp), B));
     const double dn0 = (dm < 0.0) ? dn : 0.0;
     ftvd = 0.5 * ((dm > 0.0) ? up : dn0);
-    if constexpr (FLAGS) {
+    if constexpr (CODES) {
       // the same choices as the fmin/fmax chains, first argument on a tie
       const bool pos = dm > 0.0, neg = dm < 0.0;
       // both sides evaluated, then selected (nested or short-circuit
@@ -628,14 +629,17 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
         }
       }
     };
-    // The acoustic and entropy fields share their projection's terms.  In 2D
-    // and 3D they form one group and each shear field is alone; in 1D the
-    // acoustic pair is one group and the entropy field another (one group of
-    // all three needs 190 VGPRs in the batched kernel against 162, and was
-    // 10 % slower there).
-    if constexpr (NF == 3) {
-      group(1u | 4u);
-      group(2u);
+    // The acoustic and entropy fields share their projection's terms.  At six
+    // points in 2D and 3D they form one group and each shear field is alone
+    // (130 VGPRs instead of 150 with the entropy field alone too, but no gain:
+    // 2D at four wavefronts per SIMD 1 % slower).  At eight points, and in 1D,
+    // the acoustic pair is one group and every other field alone: the sweeps
+    // then fit three wavefronts per SIMD instead of two (256^3 Euler x 1573 ->
+    // 1394 us, y 1322 -> 1175, z 1412 -> 1243).
+    if constexpr (NF == 3 || K == 8) {
+      group(1u | (1u << (NF - 1)));
+#pragma unroll
+      for (int q = 1; q < NF - 1; ++q) group(1u << q);
     } else {
       group(3u | (1u << (NF - 1)));
 #pragma unroll

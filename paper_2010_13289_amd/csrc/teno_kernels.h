@@ -184,16 +184,13 @@ __device__ __forceinline__ void stage_cell(double* stage, int nc, int c, const d
   }
 }
 
-// Waves per SIMD the row and tile sweeps are compiled for: three where the
-// face fits in 168 VGPRs without spilling (six points), two at eight points
-// (at most 256 VGPRs; every eight-point variant fits without spilling).
-template <int NF, int K>
-struct RowOccupancy {
-  static constexpr int WAVES = (K == 6) ? 3 : 2;
-};
+// Waves per SIMD the face, row and tile kernels are compiled for: at most 168
+// VGPRs, which the face fits (the adaptive eight-point MP face spills 12
+// bytes), and three tiles fit in a CU's LDS.
+constexpr int kFaceWaves = 3;
 
 template <int NF, int K, int LIM, bool ADAPT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RowOccupancy<NF, K>::WAVES)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFaceWaves)))
 void k_sweep_row(SweepParams<NF> p) {
   constexpr int NC = 256 + K - 1;  // staged cells per segment
   constexpr int NE = RowStage<NF>::NE;
@@ -285,9 +282,9 @@ inline long tile_count(int axis, int nx, int ny, int nz) {
 // with the measured sweeps (Euler, six points unless stated; one chunk, two,
 // four, in us): 1024^2 y 67, 71, 79; 2048^2 y 236, 229, 235; 187x150x93 y at
 // eight points 313, 302, 316 (the last whole lines).
-inline int tile_segment(int axis, int n, int nx, int ny, int nz, int bc, int waves_per_simd) {
+inline int tile_segment(int axis, int n, int nx, int ny, int nz, int bc) {
   const double lines = (double)tile_count(axis, nx, ny, nz);
-  const double slots = 256.0 * waves_per_simd;  // 256 CUs, one wavefront of a workgroup per SIMD
+  const double slots = 256.0 * kFaceWaves;  // 256 CUs, one wavefront of a workgroup per SIMD
   constexpr double start = 0.15;
   int best = n;
   double best_t = 0.0;
@@ -313,7 +310,7 @@ struct SweepTile {
 };
 
 template <int NF, int K, int LIM, bool ADAPT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RowOccupancy<NF, K>::WAVES)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFaceWaves)))
 void k_sweep_tile(SweepParams<NF> p, int axis) {
   using S = SweepTile<NF, K>;
   constexpr int TX = S::TX, FJ = S::FJ;
@@ -467,7 +464,7 @@ struct FacesParams {
 };
 
 template <int NF, int K, int LIM, bool ADAPT, int TX, bool FLAGS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RowOccupancy<NF, K>::WAVES)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFaceWaves)))
 void k_faces(FacesParams<NF> p) {
   constexpr int FJ = 256 / TX;
   constexpr int ROWS = FJ + K - 1, NC = ROWS * TX;
@@ -806,7 +803,7 @@ hipError_t launch_tile(const SweepLaunch& a) {
   for (int q = 0; q < NF; ++q) p.fld[q] = a.fld[q];
   if (a.axis < 0 || a.axis > 2) return hipErrorInvalidValue;
   p.n = (a.axis == 0) ? a.nx : (a.axis == 1) ? a.ny : a.nz;
-  p.seg = tile_segment(a.axis, p.n, a.nx, a.ny, a.nz, a.bc, RowOccupancy<NF, K>::WAVES);
+  p.seg = tile_segment(a.axis, p.n, a.nx, a.ny, a.nz, a.bc);
   p.nseg = (p.n + p.seg - 1) / p.seg;
   const long tiles = tile_count(a.axis, a.nx, a.ny, a.nz) * p.nseg;
   hipLaunchKernelGGL((k_sweep_tile<NF, K, LIM, ADAPT>), dim3((unsigned)tiles), dim3(256), 0, a.stream, p, a.axis);
