@@ -292,6 +292,12 @@ constexpr double kVaDenMin = 2.2250738585072014e-308;
 
 __device__ __forceinline__ double va_den(double dm, double dp) { return fmax(fma(dp, dp, dm * dm), kVaDenMin); }
 
+// Smoothness bits of a constant stencil: every gamma_k is 1.
+template <int K, bool ADAPT>
+__device__ __forceinline__ uint32_t teno_flat_bits(const TenoParams& tp) {
+  return (ADAPT || !(1.0 < tp.C_T * (double)(K - 2))) ? (1u << (K - 2)) - 1u : 0u;
+}
+
 // One TENO-M reconstruction (Secs. 2.2-3.3).  With SKIP, a wavefront in
 // which teno_all_smooth holds in every lane skips the cutoff and the limiter,
 // which only reaches nonsmooth candidates, and assembles the linear scheme;
@@ -601,49 +607,72 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
     // reconstructions.  The same operations in the same order as below: the
     // same bits.
     double alpha = 0.0;
-#pragma unroll
-    for (int m = 0; m < K; ++m) alpha = fmax(alpha, prov.speed(m));
-    auto group = [&](uint32_t mask) {
-      const P pq = prov.fresh();
-      double vp[NF][K], vm[NF][K];
-#pragma unroll
-      for (int m = 0; m < K; ++m) {
-        double X[NF], F[NF], w[NF], g[NF];
-        pq.state_flux(m, X, F);
-        project(X, w);
-        project(F, g);
-#pragma unroll
-        for (int q = 0; q < NF; ++q)
-          if ((mask >> q) & 1u) lf_split2(g[q], alpha, w[q], vp[q][m], vm[q][K - 1 - m]);
-      }
+    bool uniform = false;
+    if constexpr (P::kUniform) uniform = prov.uniform();
+    if (uniform) {  // uniform across the wavefront, too
+      // Every face of the wavefront sees K equal cells (the constant states
+      // of a Riemann problem, which most wavefronts of the batched problems
+      // hold: 97 % of them in the first hundred steps).  All differences are
+      // zero, so each reconstruction is its split value, bit for bit, whatever
+      // the cutoff and the limiter: one projection instead of K and no
+      // reconstruction.
+      alpha = fmax(alpha, prov.speed(0));
+      double X[NF], F[NF], w[NF], g[NF];
+      prov.state_flux(0, X, F);
+      project(X, w);
+      project(F, g);
 #pragma unroll
       for (int q = 0; q < NF; ++q) {
-        if ((mask >> q) & 1u) {
-          bits[0][q] = bits[1][q] = 0u;
-          if (q == 0 || q == NF - 1)
-            fc[q] = 0.25 * (teno_m<K, LIM, FLAGS, ADAPT, true, 4>(vp[q], tp, bits[0][q]) +
-                            teno_m<K, LIM, FLAGS, ADAPT, true, 4>(vm[q], tp, bits[1][q]));
-          else
-            fc[q] = 0.5 * (teno_m<K, LIM, FLAGS, ADAPT, true>(vp[q], tp, bits[0][q]) +
-                           teno_m<K, LIM, FLAGS, ADAPT, true>(vm[q], tp, bits[1][q]));
-        }
+        double vp, vm;
+        lf_split2(g[q], alpha, w[q], vp, vm);
+        fc[q] = ((q == 0 || q == NF - 1) ? 0.25 : 0.5) * ((vp + 0.0) + (vm + 0.0));
+        bits[0][q] = bits[1][q] = FLAGS ? teno_flat_bits<K, ADAPT>(tp) : 0u;
       }
-    };
-    // The acoustic and entropy fields share their projection's terms.  At six
-    // points in 2D and 3D they form one group and each shear field is alone
-    // (130 VGPRs instead of 150 with the entropy field alone too, but no gain:
-    // 2D at four wavefronts per SIMD 1 % slower).  At eight points, and in 1D,
-    // the acoustic pair is one group and every other field alone: the sweeps
-    // then fit three wavefronts per SIMD instead of two (256^3 Euler x 1573 ->
-    // 1394 us, y 1322 -> 1175, z 1412 -> 1243).
-    if constexpr (NF == 3 || K == 8) {
-      group(1u | (1u << (NF - 1)));
-#pragma unroll
-      for (int q = 1; q < NF - 1; ++q) group(1u << q);
     } else {
-      group(3u | (1u << (NF - 1)));
 #pragma unroll
-      for (int q = 2; q < NF - 1; ++q) group(1u << q);
+      for (int m = 0; m < K; ++m) alpha = fmax(alpha, prov.speed(m));
+      auto group = [&](uint32_t mask) {
+        const P pq = prov.fresh();
+        double vp[NF][K], vm[NF][K];
+#pragma unroll
+        for (int m = 0; m < K; ++m) {
+          double X[NF], F[NF], w[NF], g[NF];
+          pq.state_flux(m, X, F);
+          project(X, w);
+          project(F, g);
+#pragma unroll
+          for (int q = 0; q < NF; ++q)
+            if ((mask >> q) & 1u) lf_split2(g[q], alpha, w[q], vp[q][m], vm[q][K - 1 - m]);
+        }
+#pragma unroll
+        for (int q = 0; q < NF; ++q) {
+          if ((mask >> q) & 1u) {
+            bits[0][q] = bits[1][q] = 0u;
+            if (q == 0 || q == NF - 1)
+              fc[q] = 0.25 * (teno_m<K, LIM, FLAGS, ADAPT, true, 4>(vp[q], tp, bits[0][q]) +
+                              teno_m<K, LIM, FLAGS, ADAPT, true, 4>(vm[q], tp, bits[1][q]));
+            else
+              fc[q] = 0.5 * (teno_m<K, LIM, FLAGS, ADAPT, true>(vp[q], tp, bits[0][q]) +
+                             teno_m<K, LIM, FLAGS, ADAPT, true>(vm[q], tp, bits[1][q]));
+          }
+        }
+      };
+      // The acoustic and entropy fields share their projection's terms.  At six
+      // points in 2D and 3D they form one group and each shear field is alone
+      // (130 VGPRs instead of 150 with the entropy field alone too, but no gain:
+      // 2D at four wavefronts per SIMD 1 % slower).  At eight points, and in 1D,
+      // the acoustic pair is one group and every other field alone: the sweeps
+      // then fit three wavefronts per SIMD instead of two (256^3 Euler x 1573 ->
+      // 1394 us, y 1322 -> 1175, z 1412 -> 1243).
+      if constexpr (NF == 3 || K == 8) {
+        group(1u | (1u << (NF - 1)));
+#pragma unroll
+        for (int q = 1; q < NF - 1; ++q) group(1u << q);
+      } else {
+        group(3u | (1u << (NF - 1)));
+#pragma unroll
+        for (int q = 2; q < NF - 1; ++q) group(1u << q);
+      }
     }
   } else {
     // stencil cells: characteristic projections of U and F, Rusanov alpha

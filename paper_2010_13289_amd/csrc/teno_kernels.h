@@ -120,6 +120,7 @@ struct RowStage {
 template <int NF, int K, int CS = 1, bool REREAD = false>
 struct StagedCells {
   static constexpr bool kReread = REREAD;  // the face reads the cells again per group of fields
+  static constexpr bool kUniform = REREAD && NF == 3 && CS == 1;  // 1D: constant states skip the face
   const double* s;  // LDS: [NE][NC]
   int nc;           // row pitch of the staging array
   int c0;           // staging index of window cell 0
@@ -138,6 +139,19 @@ struct StagedCells {
       X[q] = at(q, c);
       F[q] = at(NF + q, c);
     }
+  }
+  // Whether all cells that the wavefront's faces read are equal, bit for bit.
+  // The active lanes hold consecutive faces from lane 0 on: lane l compares the
+  // pairs (l, l + 1) and (l + K - 2, l + K - 1) of the wavefront's cells, which
+  // cover all of them when at least K - 2 lanes are active.
+  __device__ __forceinline__ bool uniform() const {
+    bool differ = false;
+#pragma unroll
+    for (int q = 0; q < NF; ++q) {
+      differ |= __double_as_longlong(at(q, c0)) != __double_as_longlong(at(q, c0 + CS));
+      differ |= __double_as_longlong(at(q, c0 + (K - 2) * CS)) != __double_as_longlong(at(q, c0 + (K - 1) * CS));
+    }
+    return __builtin_amdgcn_ballot_w64(differ) == 0 && __popcll(__builtin_amdgcn_ballot_w64(true)) >= K - 2;
   }
   __device__ __forceinline__ double speed(int m) const { return at(2 * NF, c0 + m * CS); }
   __device__ __forceinline__ void cell(int m, double (&X)[NF], double (&F)[NF], double& lam) const {
