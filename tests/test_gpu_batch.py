@@ -385,3 +385,50 @@ def test_batched_4096_problems_graph_100_steps(T, orc):
         tv = np.sum(np.abs(np.diff(rho_ex)))
         assert l1_cells <= 1.5 * tv, (p, l1_cells, tv)
     plan.close()
+
+
+# left and right states (rho, u, p) with long constant runs: at rest with signed
+# zero momentum, equal on both sides, and states whose flux arithmetic is not
+# finite or nearly cancels (a run of those may not be taken for a zero divergence)
+FLAT_STATES = [((1.0, 0.0, 1.0), (0.125, -0.0, 0.1)), ((0.5, 0.3, 0.4), (0.5, 0.3, 0.4)),
+               ((1.0, 1.0, 1e-9), (1.0, 1.0, 1e-9)), ((1e-120, 0.1, 1e-120), (1e-120, 0.1, 1e-120)),
+               ((0.8, -0.9, 0.6), (0.3, 0.7, 0.9))]
+
+
+@pytest.mark.parametrize("scheme,lim,C_T,bc", [(6, 1, 1e-5, 1), (8, 1, 1e-7, 0), (8, 2, 0.3, 1), (8 | 0x100, 3, 0.0, 1)])
+def test_constant_runs_against_the_single_grid_step(T, scheme, lim, C_T, bc):
+    """Problems whose segments are constant, partly constant (the jump inside
+    the last halo of a segment, at its edges, in its middle) or made of
+    extreme constant states: every tile and the persistent launch give the
+    bits of the single-grid step by the tile sweep, which has no path for
+    constant states, at the step sizes the batch took."""
+    sizes, parts = [], []
+    for n in (64, 256, 700, 1025):
+        for left, right in FLAT_STATES:
+            for x0 in (0.5, (n - 3.0) / n, (min(n, 255) + 1.5) / n, 62.0 / n):
+                U, _ = W.riemann_problem(n, left, right, gamma=GAMMA, x0=min(x0, 1.0))
+                sizes.append(n)
+                parts.append(U)
+    U = np.concatenate(parts, axis=1)
+    dx = 1.0 / np.array(sizes)
+    plan = T.BatchPlan(sizes, dx, bc)
+    outs = []
+    for tile in range(T.BATCH_TILES):
+        plan.tile = tile
+        outs.append(to_host(plan.rk3(to_dev(U), scheme, lim, C_T, GAMMA, CFL, steps=1)))
+    _, dt = plan.times()
+    outs.append(to_host(plan.rk3_persistent(to_dev(U), scheme, lim, C_T, GAMMA, CFL, steps=1)))
+    T.set_sweep_kernel(T.SWEEP_TILE)
+    try:
+        for p, n in enumerate(sizes):
+            if not np.isfinite(dt[p]):
+                continue
+            V = to_dev(parts[p])
+            T.rk3_step(V, grid_of(n, dx[p], bc), scheme, lim, C_T, GAMMA, dt[p])
+            ref = to_host(V)
+            for o in outs:
+                got = problem(o, plan, p)
+                assert np.array_equal(got.view(np.int64), ref.view(np.int64)), (p, n, FLAT_STATES[(p // 4) % 5])
+    finally:
+        T.set_sweep_kernel(T.SWEEP_AUTO)
+    plan.close()
