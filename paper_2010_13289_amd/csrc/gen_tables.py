@@ -252,6 +252,15 @@ def emit(K: int, literal: bool) -> str:
         expr = f"fma({lit(tot[mid - m])}, D[{mid - m}] - D[{mid + m}], {expr})"
     w(f"    return {expr};")
     w("  }")
+    fw = face_coeffs(lo_full, K // 2)
+    assert fw == fw[::-1]
+    w("  // weights of the linear scheme's cells (symmetric)")
+    w("  static __device__ __forceinline__ constexpr double face(int m) {")
+    expr = lit(fw[0])
+    for m in range(1, K // 2):
+        expr = f"m == {m} || m == {K - 1 - m} ? {lit(fw[m])} : {expr}"
+    w(f"    return {expr};")
+    w("  }")
     # transpose of the candidate map, for the adjoint: Dbar += C^T cbar
     w("  // adjoint of candidates: Dbar[j] += sum_k (d c_k / d D_j) cbar[k]")
     w("  static __device__ __forceinline__ void candidates_vjp(const double* cbar, double* Dbar) {")

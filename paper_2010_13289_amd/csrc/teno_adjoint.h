@@ -13,11 +13,12 @@
 // and nowhere otherwise; alpha takes the first maximising cell; |u_n| in
 // the signal speed passes sgn(u_n), 0 at u_n = 0.
 //
-//  k_vjp_tile    Euler system: one workgroup per line tile; the tile's cells
-//                are staged in LDS, each thread recomputes one face and
-//                pushes its cotangent (from the cotangent of dU/dt) back to
-//                the K stencil cells through LDS accumulators, and each cell
-//                applies its flux Jacobian once and writes out.
+//  k_vjp_wave    Euler system: one wavefront per line tile; faces whose
+//                reconstructions are all smooth reduce to the linear scheme,
+//                which the cells gather, and only rough fields are reversed.
+//  k_vjp_tile    the same for grids with few tiles: one workgroup per line
+//                tile, a wavefront per field; every face pushes its cotangent
+//                back to its stencil cells through LDS accumulators.
 //  k_faces_vjp_scalar, k_gather_vjp   scalar system: one thread per face
 //                writes the K stencil contributions per face and slot; one
 //                thread per cell sums those of the faces whose stencils hold
@@ -890,6 +891,144 @@ __device__ __forceinline__ void field_rev(const double* sX, const double* sF, in
   project_row_vjp<NF, Q>(s, SF, 1.0, dummy, b);
 }
 
+// Accumulators of a tile: slot lane + m of each row collects stencil cell m of
+// the face of `lane`.
+struct TileAcc {
+  double* x;    // cotangent of the cell state (direct part)
+  double* f;    // cotangent of the cell's physical flux
+  double* lam;  // cotangent of the cell's signal speed
+  int lane;
+  bool live;
+};
+
+// Reverse of field q's departure from the central linear scheme: fcbar -> the
+// cotangents of the field's split values (from the decision codes, less the
+// linear scheme's), then of the stencil states and fluxes through row q of L
+// (added to the tile's accumulators), of alpha, and of the eigenvector
+// constants (b).  A side whose candidates are all smooth has no departure.
+template <int NF, int K, int LIM, int P, int AP>
+__device__ __forceinline__ void field_departure_rev(int q, const double* sX, const double* sF, int t, const FaceState<NF>& s,
+                                          const TenoParams& tp, const double (&vp)[K], const double (&vm)[K],
+                                          const double (&W)[K], uint32_t cp, uint32_t cm, double fcbar,
+                                          const TileAcc& a, FaceBars<NF>& b) {
+  constexpr uint32_t kSmooth = (1u << (K - 2)) - 1u;
+  const double rp = (cp & kSmooth) == kSmooth ? 0.0 : 0.5 * fcbar;
+  const double rm = (cm & kSmooth) == kSmooth ? 0.0 : 0.5 * fcbar;
+  double vpbar[K], vmbar[K];
+#pragma unroll
+  for (int m = 0; m < K; ++m) {
+    vpbar[m] = -TenoTables<K>::face(m) * rp;
+    vmbar[m] = -TenoTables<K>::face(m) * rm;
+  }
+  if constexpr (LIM == LIM_VA) {
+    teno_m_vjp_given<K, LIM>(vp, tp, cp, rp, vpbar);
+    teno_m_vjp_given<K, LIM>(vm, tp, cm, rm, vmbar);
+  } else {
+    teno_m_vjp_code<K, LIM, true>(cp, tp, rp, vpbar);
+    teno_m_vjp_code<K, LIM, true>(cm, tp, rm, vmbar);
+  }
+  // The constants' cotangents are bilinear in (row cotangent, projected
+  // vector): accumulate sum_m Wb_m U_m and sum_m Gb_m F_m and take the
+  // row's adjoint once with cotangent 1.
+  double SX[NF], SF[NF];
+#pragma unroll
+  for (int r = 0; r < NF; ++r) SX[r] = SF[r] = 0.0;
+  // vp[m] = G + alpha W, vm[K-1-m] = G - alpha W: the field's part of alphabar
+  // first, so that it joins the stencil step of the maximising cell
+  double alphabar = 0.0;
+#pragma unroll
+  for (int m = 0; m < K; ++m) alphabar += W[m] * (vpbar[m] - vmbar[K - 1 - m]);
+  double g[NF];
+  bool full = true;
+  switch (q) {
+    case 0: project_row_grad<NF, 0>(s, g); break;
+    case 1: project_row_grad<NF, 1>(s, g); break;
+    case NF - 1: project_row_grad<NF, NF - 1>(s, g); break;
+    default: {
+      // shear field: the density and its own momentum (coefficient 1)
+      full = false;
+#pragma unroll
+      for (int r = 0; r < NF; ++r) g[r] = 0.0;
+#pragma unroll
+      for (int r = 2; r < NF - 1; ++r)
+        if (q == r) g[0] = -s.ut[r - 1];
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < K; ++m) {
+    const double pb = vpbar[m], mb = vmbar[K - 1 - m];
+    const double Wb = s.alpha * (pb - mb), Gb = pb + mb;
+    wave_lds_order();
+#pragma unroll
+    for (int r = 0; r < NF; ++r) {
+      SX[r] = fma(Wb, sX[r * P + t + m], SX[r]);
+      SF[r] = fma(Gb, sF[r * P + t + m], SF[r]);
+    }
+    if (a.live) {
+      if (full) {
+#pragma unroll
+        for (int r = 0; r < NF; ++r) {
+          a.x[r * AP + a.lane + m] += Wb * g[r];
+          a.f[r * AP + a.lane + m] += Gb * g[r];
+        }
+      } else {
+        a.x[a.lane + m] += Wb * g[0];
+        a.f[a.lane + m] += Gb * g[0];
+        a.x[q * AP + a.lane + m] += Wb;
+        a.f[q * AP + a.lane + m] += Gb;
+      }
+      if (m == s.mstar) a.lam[a.lane + m] += alphabar;
+    }
+  }
+  double dummy[NF];
+  switch (q) {
+    case 0:
+      project_row_vjp<NF, 0>(s, SX, 1.0, dummy, b);
+      project_row_vjp<NF, 0>(s, SF, 1.0, dummy, b);
+      break;
+    case 1:
+      project_row_vjp<NF, 1>(s, SX, 1.0, dummy, b);
+      project_row_vjp<NF, 1>(s, SF, 1.0, dummy, b);
+      break;
+    case NF - 1:
+      project_row_vjp<NF, NF - 1>(s, SX, 1.0, dummy, b);
+      project_row_vjp<NF, NF - 1>(s, SF, 1.0, dummy, b);
+      break;
+    default:
+#pragma unroll
+      for (int r = 2; r < NF - 1; ++r)
+        if (q == r) b.ut[r - 1] -= SX[0] + SF[0];
+  }
+}
+
+// Whether the all-smooth test holds for the reconstruction of doubled split
+// values v.
+template <int K>
+__device__ __forceinline__ bool teno_smooth_side(const double (&v)[K], const TenoParams& tp) {
+  double D[K - 1], beta[K - 2], tau;
+#pragma unroll
+  for (int j = 0; j < K - 1; ++j) D[j] = v[j + 1] - v[j];
+  teno_indicators<K>(D, beta, tau);
+  return teno_all_smooth<K, 2>(beta, tau, tp);
+}
+
+// Departure of one reconstruction (doubled split values) from the linear
+// scheme, with its decision code: zero where every candidate is smooth.
+template <int K, int LIM, bool ADAPT>
+__device__ __forceinline__ double teno_departure(const double (&v)[K], const TenoParams& tp, uint32_t& code) {
+  constexpr uint32_t kSmooth = (1u << (K - 2)) - 1u;
+  double D[K - 1], u[K];
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    u[j] = v[j];
+    asm volatile("" : "+v"(u[j]));  // the test's indicators are not held for this
+  }
+#pragma unroll
+  for (int j = 0; j < K - 1; ++j) D[j] = u[j + 1] - u[j];
+  const double r = teno_m<K, LIM, true, ADAPT, false, 2, false>(u, tp, code);
+  return (code & kSmooth) == kSmooth ? 0.0 : (r - u[K / 2 - 1]) - TenoTables<K>::linear(D);
+}
+
 // Tiled Euler adjoint along one axis, one characteristic field per
 // wavefront.  A workgroup of (FW faces) x (NF fields) threads owns the cells
 // [c0, c1) of one line (c1 - c0 <= FW + 1 - K).
@@ -964,15 +1103,9 @@ struct VjpOut {
 
 // Occupancy the tile kernel is compiled for: 3 wavefronts per SIMD (at most
 // 168 VGPRs; three 4-wavefront blocks of 46 KB LDS per CU), measured 20%
-// faster than 2 without spills; the 5-field tile (65 KB LDS, two blocks per
-// CU) cannot reach 3 and keeps 256 VGPRs.
-template <int NF>
-struct VjpOccupancy {
-  static constexpr int WAVES = NF >= 5 ? 2 : 3;
-};
-
+// faster than 2 without spills.
 template <int NF, int K, int LIM, bool ADAPT>
-__global__ __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(VjpOccupancy<NF>::WAVES))) void k_vjp_tile(const double* __restrict__ U,
+__global__ __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(3))) void k_vjp_tile(const double* __restrict__ U,
                                                        const double* __restrict__ Lbar, VjpOut vo,
                                                        VjpAxis ax, VjpTiles tl, int fld0, int fld1, int fld2,
                                                        int fld3, int fld4, FaceParams fp) {
@@ -1210,6 +1343,316 @@ __global__ __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(VjpOccu
   }
 }
 
+// Tiled Euler adjoint along one axis, one wavefront per tile of 64 faces.  The
+// tile owns the cells [c0, c1) of one line (c1 - c0 <= FW + 1 - K).
+//
+// With R L = I, a face whose reconstructions are all smooth has the central
+// linear scheme of the physical fluxes, whatever its eigenvectors; every other
+// face adds R delta, delta the departures of its rough fields.  So the flux's
+// transpose splits into the linear scheme's, which each cell gathers from the
+// face cotangents, and that of R delta, which only the fields with a rough
+// reconstruction in the wavefront take through the limiter, the eigenvectors
+// and alpha.
+//  1. stage the positions the tile's faces read: state, physical flux, signal
+//     speed, and the cotangent of dU/dt (0 beyond a transmissive end);
+//  2. each lane tests the fields of its face: which of the wavefront's fields
+//     have a reconstruction that may not be all smooth;
+//  3. for each of these, the departures with their decision codes, and the
+//     reverse from the codes: the stencil contributions (row q of L
+//     transposed) go to LDS accumulators (in step m lane l adds to slot l + m,
+//     so the lanes of a step meet nowhere), those to the eigenvector constants
+//     stay with the lane; then the Roe average once per face, into the slots
+//     of its two cells;
+//  4. one owned cell per lane: it gathers the linear scheme's part, adds the
+//     cell's slots (and, at an end of a transmissive line, the clamped
+//     positions beyond it), applies the flux Jacobian and the signal speed's
+//     derivative once, and writes out.
+// Nothing crosses wavefronts, so there is no barrier, and the order of every
+// sum is fixed.  Blocks on one XCD (blockIdx mod 8) take consecutive lines, so
+// the lines of a strided axis that share cache lines meet in one L2.
+// Bound by VALU issue and, on smooth data, by the latency of the loads.  2D
+// 1024^2 at six points, both axes: one field per wavefront, every field
+// reversed in full, 519 us; this, 393 us on a
+// moving smooth state, 180 where the acoustic fields are flat; 72x64x56 318 -> 141 us
+// an axis.
+template <int NF, int K, int LIM, bool ADAPT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_vjp_wave(
+    const double* __restrict__ U, const double* __restrict__ Lbar, VjpOut vo, VjpAxis ax, VjpTiles tl, int fld0,
+    int fld1, int fld2, int fld3, int fld4, FaceParams fp) {
+  using S = VjpTileShape<NF, K>;
+  using T = TenoTables<K>;
+  constexpr int FW = S::FW, P = S::P, AP = S::AP, H = K / 2;
+  __shared__ double sX[NF * P], sF[NF * P], sLam[P], sLb[NF * P];
+  __shared__ double aX[NF * AP], aF[NF * AP], aL[AP];
+  __shared__ double sB[(NF + 4) * FW], sD[NF * FW];
+  long g = blockIdx.x;
+  const long B = gridDim.x;
+  if ((B & 7) == 0) g = (g & 7) * (B >> 3) + (g >> 3);
+  const long line = g % tl.nlines;
+  const int tile = (int)(g / tl.nlines);
+  Line L;
+  if (ax.axis == 0) {
+    L = Line{line * ax.nx, 1, ax.n, ax.bc};
+  } else if (ax.axis == 1) {
+    const long x = line % ax.nx, z = line / ax.nx;
+    L = Line{x + (long)ax.nx * ax.ny * z, ax.nx, ax.n, ax.bc};
+  } else {
+    L = Line{line, (long)ax.nx * ax.ny, ax.n, ax.bc};
+  }
+  const int fall[5] = {fld0, fld1, fld2, fld3, fld4};
+  int fld[NF];
+#pragma unroll
+  for (int q = 0; q < NF; ++q) fld[q] = fall[q];
+  const long N = (long)ax.nx * ax.ny * ax.nz;
+  const bool per = (ax.bc == 0);
+  const int n = ax.n;
+  // a periodic line of at most FW cells wraps in one tile (own = n): its n
+  // faces are each there once, and a cell near an end holds two slots
+  const bool wrap = per && tl.own == n;
+  const int c0 = tile * tl.own;
+  const int ncell = min(n, c0 + tl.own) - c0;
+  const int nface = wrap ? n : ncell + K - 1;
+  const int npos = nface + K - 1;
+  const int pp0 = wrap ? -H : c0 - K + 1;  // position of slot 0
+  const int f = threadIdx.x;
+
+  __builtin_amdgcn_s_setprio(3);  // high while loads and stores issue (entry, staging, the write)
+  // 1. staging
+  for (int i = f; i < npos; i += FW) {
+    const int pos = pp0 + i;
+    const long cell = cell_at(L, pos);
+    const bool inside = per || (pos >= 0 && pos < n);
+    double X[NF], F[NF], lam, lb[NF];
+#pragma unroll
+    for (int r = 0; r < NF; ++r) {
+      X[r] = U[fld[r] * N + cell];
+      lb[r] = inside ? Lbar[fld[r] * N + cell] : 0.0;
+    }
+    cell_physics<NF>(X, fp.gamma, F, lam);
+#pragma unroll
+    for (int r = 0; r < NF; ++r) {
+      sX[r * P + i] = X[r];
+      sF[r * P + i] = F[r];
+      sLb[r * P + i] = lb[r];
+    }
+    sLam[i] = lam;
+  }
+  __syncthreads();
+  __builtin_amdgcn_s_setprio(0);
+
+  // 2. the shared state of face f and the test of its fields
+  const int j = pp0 + H + f;  // face of this lane: between positions j-1 and j
+  const bool live = f < nface && (per || (j >= 0 && j <= n));
+  const int t = f < nface ? f : nface - 1;  // staged slots for every lane
+  FaceState<NF> s;
+  s.alpha = 0.0;
+  s.mstar = 0;
+#pragma unroll
+  for (int m = 0; m < K; ++m) {
+    const double lam = sLam[t + m];
+    if (!(s.alpha >= lam)) {  // alpha = fmax(alpha, lam): the first maximum
+      s.alpha = lam;
+      s.mstar = m;
+    }
+  }
+  {
+    double Xa[NF], Xb[NF];
+#pragma unroll
+    for (int r = 0; r < NF; ++r) {
+      Xa[r] = sX[r * P + t + H - 1];
+      Xb[r] = sX[r * P + t + H];
+    }
+    roe_state<NF>(Xa, Xb, fp.gamma, s);
+  }
+  uint32_t rough = 0;  // bit q: field q is rough somewhere in the wavefront (uniform)
+  // the acoustic pair, which shares its projection's terms, then each other field
+  auto test = [&](uint32_t mask) {
+    double vp[NF][K], vm[NF][K];
+    int tf = t;
+    asm volatile("" : "+v"(tf));  // fresh reads: no other group's values are held
+#pragma unroll
+    for (int m = 0; m < K; ++m) {
+      double X[NF], F[NF], w[NF], gf[NF];
+#pragma unroll
+      for (int r = 0; r < NF; ++r) {
+        X[r] = sX[r * P + tf + m];
+        F[r] = sF[r * P + tf + m];
+      }
+      project_all<NF>(s, X, w);
+      project_all<NF>(s, F, gf);
+#pragma unroll
+      for (int q = 0; q < NF; ++q)
+        if ((mask >> q) & 1u) lf_split2(gf[q], s.alpha, w[q], vp[q][m], vm[q][K - 1 - m]);
+    }
+#pragma unroll
+    for (int q = 0; q < NF; ++q) {
+      if ((mask >> q) & 1u) {
+        const bool lane_rough = live && !(teno_smooth_side<K>(vp[q], fp.tp) && teno_smooth_side<K>(vm[q], fp.tp));
+        rough |= __builtin_amdgcn_ballot_w64(lane_rough) != 0 ? 1u << q : 0u;
+      }
+    }
+  };
+  test(1u | (1u << (NF - 1)));
+#pragma unroll
+  for (int q = 1; q < NF - 1; ++q) test(1u << q);
+
+  // 3. the rough fields' departures and their reverse
+  if (rough != 0) {
+    for (int e = f; e < AP; e += FW) {
+#pragma unroll
+      for (int r = 0; r < NF; ++r) aX[r * AP + e] = aF[r * AP + e] = 0.0;
+      aL[e] = 0.0;
+    }
+    auto add_bars = [&](const FaceBars<NF>& b) {
+#pragma unroll
+      for (int d = 0; d < NF - 2; ++d) sB[d * FW + f] += b.ut[d];
+      sB[(NF - 2) * FW + f] += b.b1;
+      sB[(NF - 1) * FW + f] += b.b2;
+      sB[NF * FW + f] += b.cinv;
+    };
+    auto zero_bars = [&](FaceBars<NF>& b) {
+#pragma unroll
+      for (int d = 0; d < NF - 2; ++d) b.ut[d] = 0.0;
+      b.b1 = b.b2 = b.cinv = b.ct = b.Ht = b.q2 = 0.0;
+    };
+#pragma unroll
+    for (int r = 0; r < NF; ++r) sD[r * FW + f] = 0.0;
+#pragma unroll
+    for (int r = 0; r < NF + 4; ++r) sB[r * FW + f] = 0.0;
+    auto face_bar = [&](int tt, double (&Fhbar)[NF]) {
+#pragma unroll
+      for (int r = 0; r < NF; ++r) Fhbar[r] = (sLb[r * P + tt + H] - sLb[r * P + tt + H - 1]) * ax.inv_dx;
+    };
+    const TileAcc acc{aX, aF, aL, f, live};
+#pragma unroll 1
+    for (int q = 0; q < NF; ++q) {
+      if (!((rough >> q) & 1u)) continue;
+      double vp[K], vm[K], W[K];
+      int tf = t;
+      asm volatile("" : "+v"(tf));
+      asm volatile("" : "+v"(s.b1), "+v"(s.b2), "+v"(s.cinv));
+#pragma unroll
+      for (int d = 0; d < NF - 2; ++d) asm volatile("" : "+v"(s.ut[d]));
+      switch (q) {
+        case 0: field_split<NF, K, 0, P>(sX, sF, tf, s, vp, vm, W); break;
+        case 1: field_split<NF, K, 1, P>(sX, sF, tf, s, vp, vm, W); break;
+        case 2:
+          if constexpr (NF > 2) field_split<NF, K, 2, P>(sX, sF, tf, s, vp, vm, W);
+          break;
+        case 3:
+          if constexpr (NF > 3) field_split<NF, K, 3, P>(sX, sF, tf, s, vp, vm, W);
+          break;
+        default:
+          if constexpr (NF > 4) field_split<NF, K, 4, P>(sX, sF, tf, s, vp, vm, W);
+          break;
+      }
+      // (no limiter skip in the codes: where most wavefronts are rough, as in a
+      // fluid at rest whose acoustic fields carry rounding noise, the skip's
+      // branches cost the kernel 5 %)
+      uint32_t cp = 0u, cm = 0u;
+      const double dp = teno_departure<K, LIM, ADAPT>(vp, fp.tp, cp);
+      const double dq = 0.5 * (dp + teno_departure<K, LIM, ADAPT>(vm, fp.tp, cm));
+      double fb = 0.0;
+      {
+        double Fhbar[NF], fcbar[NF], none[NF];
+        FaceBars<NF> nb;
+        face_bar(tf, Fhbar);
+#pragma unroll
+        for (int r = 0; r < NF; ++r) none[r] = 0.0;
+        backproj_vjp<NF>(s, none, Fhbar, fcbar, nb, false);
+#pragma unroll
+        for (int r = 0; r < NF; ++r) fb = q == r ? fcbar[r] : fb;
+        sD[q * FW + f] = dq;
+      }
+      FaceBars<NF> b;
+      zero_bars(b);
+      field_departure_rev<NF, K, LIM, P, AP>(q, sX, sF, tf, s, fp.tp, vp, vm, W, cp, cm, fb, acc, b);
+      add_bars(b);
+    }
+    FaceBars<NF> b;
+    b.ct = b.Ht = b.q2 = 0.0;
+#pragma unroll
+    for (int d = 0; d < NF - 2; ++d) b.ut[d] = sB[d * FW + f];
+    b.b1 = sB[(NF - 2) * FW + f];
+    b.b2 = sB[(NF - 1) * FW + f];
+    b.cinv = sB[NF * FW + f];
+    double delta[NF];
+#pragma unroll
+    for (int r = 0; r < NF; ++r) delta[r] = sD[r * FW + f];
+    // the back-projection's part of the constants, then the Roe average: the
+    // left cell of face f sits at slot f + H - 1, the right one at f + H
+    {
+      double Fhbar[NF], fcbar[NF];
+      face_bar(t, Fhbar);
+      backproj_vjp<NF>(s, delta, Fhbar, fcbar, b, true);
+    }
+    double Xa[NF], Xb[NF], xa[NF], xb[NF];
+#pragma unroll
+    for (int r = 0; r < NF; ++r) {
+      Xa[r] = sX[r * P + t + H - 1];
+      Xb[r] = sX[r * P + t + H];
+      xa[r] = xb[r] = 0.0;
+    }
+    FaceState<NF> sr;  // the Roe inputs again (cheaper than keeping them live)
+    roe_state<NF>(Xa, Xb, fp.gamma, sr);
+    shared_vjp<NF>(Xa, Xb, sr, fp.gamma, b, xa, xb);
+    wave_lds_order();
+    if (live) {
+#pragma unroll
+      for (int r = 0; r < NF; ++r) aX[r * AP + f + H - 1] += xa[r];
+    }
+    wave_lds_order();
+    if (live) {
+#pragma unroll
+      for (int r = 0; r < NF; ++r) aX[r * AP + f + H] += xb[r];
+    }
+    wave_lds_order();
+  }
+
+  // 4. the owned cell of this lane
+  if (f >= ncell) return;
+  const int i = c0 - pp0 + f;  // its slot
+  const int c = c0 + f;
+  const long cell = L.base + (long)c * L.stride;
+  double prev[NF], X[NF], fs[NF], xs[NF], ls = 0.0;
+#pragma unroll
+  for (int r = 0; r < NF; ++r) {
+    prev[r] = vo.src ? vo.src[(long)fld[r] * N + cell] : 0.0;
+    X[r] = sX[r * P + i];
+    xs[r] = fs[r] = 0.0;
+  }
+  // its further slots: clamped positions beyond a transmissive end, or the
+  // other end of a wrapped line
+  const int step = wrap ? n : 1;
+  const int lo = (!per && c == 0) ? i - H : (wrap && i >= n ? i - n : i);
+  const int hi = (!per && c == n - 1) ? i + H : (wrap && i + n < npos ? i + n : i);
+  for (int k = lo; k <= hi; k += step) {
+#pragma unroll
+    for (int m = 0; m < K; ++m) {
+      const int fm = k - m;  // the face that holds slot k as its stencil cell m
+      if (fm < 0 || fm >= nface) continue;
+#pragma unroll
+      for (int r = 0; r < NF; ++r) fs[r] = fma(T::face(m), sLb[r * P + fm + H] - sLb[r * P + fm + H - 1], fs[r]);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < NF; ++r) fs[r] *= ax.inv_dx;
+  if (rough != 0) {
+    for (int k = lo; k <= hi; k += step) {
+#pragma unroll
+      for (int r = 0; r < NF; ++r) {
+        xs[r] += aX[r * AP + k];
+        fs[r] += aF[r * AP + k];
+      }
+      ls += aL[k];
+    }
+  }
+  cell_physics_vjp<NF>(X, fp.gamma, fs, ls, xs);
+  __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+  for (int r = 0; r < NF; ++r) vo.out[(long)fld[r] * N + cell] = vo.c * prev[r] + vo.scale * xs[r];
+}
+
 // out[f][cell] by the output rule, with s the sum of the contributions of
 // every (face, slot) whose stencil cell is `cell`, faces in increasing order.
 template <int NF, int K>
@@ -1296,12 +1739,27 @@ hipError_t launch_vjp(const VjpLaunch& a) {
     const long N = (long)a.ax.nx * a.ax.ny * a.ax.nz;
     VjpTiles tl;
     tl.nlines = N / a.ax.n;
-    tl.own = VjpTileShape<NF, K>::FW - K + 1;
+    constexpr int FW = VjpTileShape<NF, K>::FW;
+    tl.own = FW - K + 1;
     const long ntile = (a.ax.n + tl.own - 1) / tl.own;
-    hipLaunchKernelGGL((k_vjp_tile<NF, K, LIM, ADAPT>), dim3((unsigned)(tl.nlines * ntile)),
-                       dim3(VjpTileShape<NF, K>::FW, NF), 0,
-                       a.stream, a.U, a.Lbar, a.out, a.ax, tl, a.fld[0], a.fld[1], a.fld[2], a.fld[3], a.fld[4],
-                       a.fp);
+    // One wavefront per tile does far less work, but takes its rough fields one
+    // after the other: it wins once the tiles fill the chip (the fields of a
+    // tile otherwise run side by side in their own wavefronts).  Measured per
+    // axis, us (a wavefront per field, per tile): six points 256^2 (1,280
+    // tiles) 28, 42; 512^2 (4,608) 82, 84; 768^2 (10,752) 174, 144; 1024^2 277,
+    // 198; eight points 256^2 48, 54; 1024^2 498, 249.  In 3D always: 32^3 50,
+    // 38; 72x64x56 319, 141.
+    if (NF == 5 || tl.nlines * ntile >= (K == 6 ? 5120 : 2048)) {
+      if (a.ax.bc == 0 && a.ax.n <= FW) tl.own = a.ax.n;
+      const long tiles = tl.nlines * ((a.ax.n + tl.own - 1) / tl.own);
+      hipLaunchKernelGGL((k_vjp_wave<NF, K, LIM, ADAPT>), dim3((unsigned)tiles), dim3(FW), 0, a.stream, a.U, a.Lbar,
+                         a.out, a.ax, tl, a.fld[0], a.fld[1], a.fld[2], a.fld[3], a.fld[4], a.fp);
+      return hipGetLastError();
+    }
+    if constexpr (NF < 5)
+      hipLaunchKernelGGL((k_vjp_tile<NF, K, LIM, ADAPT>), dim3((unsigned)(tl.nlines * ntile)), dim3(FW, NF), 0,
+                         a.stream, a.U, a.Lbar, a.out, a.ax, tl, a.fld[0], a.fld[1], a.fld[2], a.fld[3], a.fld[4],
+                         a.fp);
   }
   return hipGetLastError();
 }

@@ -26,6 +26,10 @@ template <> struct TenoTables<6> {
   static __device__ __forceinline__ double linear(const double* D) {
     return fma((-1.0 / 60.0), D[0] - D[4], fma((7.0 / 60.0), D[1] - D[3], 0.5 * D[2]));
   }
+  // weights of the linear scheme's cells (symmetric)
+  static __device__ __forceinline__ constexpr double face(int m) {
+    return m == 2 || m == 3 ? (37.0 / 60.0) : m == 1 || m == 4 ? (-2.0 / 15.0) : (1.0 / 60.0);
+  }
   // adjoint of candidates: Dbar[j] += sum_k (d c_k / d D_j) cbar[k]
   static __device__ __forceinline__ void candidates_vjp(const double* cbar, double* Dbar) {
     Dbar[0] = (-1.0 / 3.0) * cbar[2] + Dbar[0];
@@ -88,6 +92,10 @@ template <> struct TenoTables<8> {
   // sum_k d_k c_k: the linear scheme all smooth candidates assemble to, minus v_i
   static __device__ __forceinline__ double linear(const double* D) {
     return fma((1.0 / 280.0), D[0] - D[6], fma((-13.0 / 420.0), D[1] - D[5], fma((113.0 / 840.0), D[2] - D[4], 0.5 * D[3])));
+  }
+  // weights of the linear scheme's cells (symmetric)
+  static __device__ __forceinline__ constexpr double face(int m) {
+    return m == 3 || m == 4 ? (533.0 / 840.0) : m == 2 || m == 5 ? (-139.0 / 840.0) : m == 1 || m == 6 ? (29.0 / 840.0) : (-1.0 / 280.0);
   }
   // adjoint of candidates: Dbar[j] += sum_k (d c_k / d D_j) cbar[k]
   static __device__ __forceinline__ void candidates_vjp(const double* cbar, double* Dbar) {

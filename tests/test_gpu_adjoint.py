@@ -97,6 +97,39 @@ def test_vjp_on_smooth_data_matches_reference(T, orc, K, lim, C_T):
     assert_close_fields(got, ref, exclude=excl, what=f"smooth 2D VJP K={K} lim={lim}")
 
 
+# one wavefront per tile: 3D lines that wrap in one tile (up to 64 cells,
+# periodic), fill it (59 cells at six points, 57 at eight), and leave one cell
+# for a second or third; 2D grids with enough tiles along one axis
+WAVE_CASES = [((64, 8, 8), [0, 0, 0], 6, 1), ((8, 65, 8), [0, 0, 1], 6, 1), ((8, 8, 63), [0, 1, 1], 6, 3),
+              ((59, 6, 8), [1, 0, 1], 6, 2), ((60, 6, 8), [0, 0, 1], 6, 0), ((8, 119, 6), [0, 1, 0], 6, 4),
+              ((64, 8, 8), [1, 1, 0], 8, 1), ((8, 58, 8), [0, 0, 0], 8 | 0x100, 1), ((8, 8, 58), [1, 0, 0], 8, 3),
+              ((8, 5200), [0, 0], 6, 1), ((5200, 8), [1, 0], 6, 1), ((2100, 70), [0, 1], 8, 6)]
+
+
+@pytest.mark.parametrize("kind", ["mixed", "smooth"])
+@pytest.mark.parametrize("shape,bc,K,lim", WAVE_CASES,
+                         ids=[f"{'x'.join(map(str, c[0]))}-{''.join(map(str, c[1]))}-{c[2]}-{c[3]}" for c in WAVE_CASES])
+def test_wave_tiles_match_reference(T, orc, shape, bc, K, lim, kind):
+    """Rough data (every field reversed) and smooth data with one jump (most
+    tiles reduce to the linear scheme, some reverse single fields)."""
+    n = list(reversed(shape))
+    grid = dict(ndim=len(n), n=n, dx=[0.05, 0.06, 0.07][:len(n)], bc=bc, system=1)
+    C_T = 1e-5 if K == 6 else 1e-7
+    print(f"[vjp wave] n={n} bc={bc} K={K} lim={lim} {kind}", flush=True)
+    case = (None, shape, grid, K, lim, C_T)
+    if kind == "mixed":
+        U = state(case, 4)
+    else:
+        U = W.random_euler_state(shape, seed=9, kind="smooth")
+        U[..., : shape[-1] // 2] *= 1.1
+    Lbar = np.random.default_rng(5).standard_normal(U.shape)
+    ref = RA.flux_divergence_vjp(U, Lbar, grid, K, lim, C_T, GAMMA)
+    got = to_host(T.flux_divergence_vjp(to_dev(U), to_dev(Lbar), grid, K, lim, C_T, GAMMA))
+    excl = band_cells(orc, U, grid, K, lim, C_T, K & 0xFF)
+    assert excl.sum() <= excl.size // 10
+    assert_close_fields(got, ref, exclude=excl, what="wave VJP")
+
+
 def test_vjp_scale_accumulate_and_determinism(T):
     case = CASES[3]
     name, shape, grid, K, lim, C_T = case
