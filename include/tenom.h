@@ -406,7 +406,10 @@ int tenom_version(void);
  * for y and z, y rows for x) by a chunk of the line in LDS and walks a segment
  * of the lines, or the lines whole.  TENOM_SWEEP_AUTO (the default): the tile
  * kernel in 2D and 3D, except along x where the rows fill at most 512
- * workgroups of the line kernel; the line kernel in 1D.
+ * workgroups of the line kernel.  In 1D it is a whole step in one launch where
+ * the line is one workgroup (256 faces of the Euler equations, 1024 of the
+ * scalar equation), one wavefront per field on Euler lines of at most 40,960
+ * cells, and the line kernel otherwise.
  * Returns TENOM_EINVAL for any other value.  The setting is process-wide;
  * calls made while another thread changes it may use either kernel.
  */
@@ -420,7 +423,8 @@ int tenom_set_sweep_kernel(int kind);
  * bracketed by HIP events recorded on the same stream.  tenom_profile_read
  * synchronises those events and returns, per kernel kind, the number of
  * launches and their summed duration in milliseconds since the last reset.
- * Kinds: 0 face fluxes (reconstruct_faces), 1 x-sweep, 2 y-sweep,
+ * Kinds: 0 face fluxes (reconstruct_faces), 1 x-sweep (a whole step where the
+ * automatic choice runs a short 1D line's in one launch), 2 y-sweep,
  * 3 z-sweep, 4 batched sweep, 5 batched step size, 6 one replay of a batched
  * graph (kernels inside a graph are not bracketed one by one), 7 one axis of
  * an adjoint (face kernel + gather), 8 one persistent batched launch.  At

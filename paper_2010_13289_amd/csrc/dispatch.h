@@ -4,7 +4,7 @@
 // parallel; the C-ABI layer picks one by table lookup.
 #pragma once
 
-#include "teno_kernels.h"
+#include "teno_line.h"
 
 // lim: limiter kind (tenom::LIM_*), adapt: 1 for the adaptive cutoff (K = 8)
 #define TENOM_DECLARE_UNIT(NF, K)                                                          \
@@ -20,3 +20,15 @@ TENOM_DECLARE_UNIT(4, 6)
 TENOM_DECLARE_UNIT(4, 8)
 TENOM_DECLARE_UNIT(5, 6)
 TENOM_DECLARE_UNIT(5, 8)
+
+// Single-line kernels of the scalar and 1D Euler units: one whole step, and
+// one sweep with a wavefront per field (Euler).
+#define TENOM_DECLARE_LINE(NF, K) hipError_t tenom_line_nf##NF##_k##K(int lim, int adapt, const tenom::LineLaunch& a);
+
+TENOM_DECLARE_LINE(1, 6)
+TENOM_DECLARE_LINE(1, 8)
+TENOM_DECLARE_LINE(3, 6)
+TENOM_DECLARE_LINE(3, 8)
+
+hipError_t tenom_fields_nf3_k6(int lim, int adapt, const tenom::SweepLaunch& a);
+hipError_t tenom_fields_nf3_k8(int lim, int adapt, const tenom::SweepLaunch& a);

@@ -147,21 +147,7 @@ __device__ __forceinline__ void batch_segment(const SegIn& g, const FaceParams& 
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int c = t + i * TPB;
-      if (c < nstage) {
-#pragma unroll
-        for (int q = 0; q < NF; ++q) stage[q * NC + c] = X[i][q];
-        double F[NF], lam;
-        RoeIn<NF> r;
-        cell_physics<NF>(X[i], fp.gamma, F, lam);
-        roe_input<NF>(X[i], fp.gamma, r);
-#pragma unroll
-        for (int q = 0; q < NF; ++q) stage[(NF + q) * NC + c] = F[q];
-        stage[(2 * NF) * NC + c] = lam;
-        stage[(2 * NF + 1) * NC + c] = r.rs;
-#pragma unroll
-        for (int d = 0; d < NF - 2; ++d) stage[(2 * NF + 2 + d) * NC + c] = r.u[d];
-        stage[(3 * NF) * NC + c] = r.H;
-      }
+      if (c < nstage) stage_put<NF>(stage, NC, c, X[i], fp.gamma);
     }
   }
   __syncthreads();

@@ -545,47 +545,18 @@ __device__ __forceinline__ void roe_input(const double (&X)[NF], double gamma, R
   r.rs = sqrt(X[0]);
 }
 
-// ---------------------------------------------------------------------------
-// Euler face flux from a cell provider P:
-//   prov.cell(m, X, F, lam)  window cell m = 0..K-1 (cells i-K/2+1 .. i+K/2)
-//   prov.roe(s, r)           Roe input of cell i (s = 0) and i+1 (s = 1)
-// Characteristic fields are ordered (u_n - c, entropy, shear waves in
-// ascending axis order, u_n + c).
-// ---------------------------------------------------------------------------
-template <int NF, int K, int LIM, bool FLAGS, bool ADAPT, class P>
-__device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoParams& tp, double (&Fh)[NF],
-                                           uint32_t (&bits)[2][NF]) {
-  constexpr int ND = NF - 2;
-  const double gm1 = gamma - 1.0;
-
-  // Roe average of cells i and i+1
-  double ut[ND], Ht, ct;
-  {
-    RoeIn<NF> a, b;
-    prov.roe(0, a);
-    prov.roe(1, b);
-    const double w = rcp(a.rs + b.rs);
-#pragma unroll
-    for (int d = 0; d < ND; ++d) ut[d] = fma(a.rs, a.u[d], b.rs * b.u[d]) * w;
-    Ht = fma(a.rs, a.H, b.rs * b.H) * w;
-    double q2 = 0.0;
-#pragma unroll
-    for (int d = 0; d < ND; ++d) q2 = fma(ut[d], ut[d], q2);
-    ct = sqrt(gm1 * fma(-0.5, q2, Ht));
-  }
-  const double cinv = rcp(ct);
-  const double b1 = gm1 * cinv * cinv;
-  double q2t = 0.0;
-#pragma unroll
-  for (int d = 0; d < ND; ++d) q2t = fma(ut[d], ut[d], q2t);
-  const double b2 = 0.5 * q2t * b1;
+// Roe average of a face's two cells and the constants of its eigenvectors.
+template <int NF>
+struct RoeFrame {
+  double ut[NF - 2], Ht, ct, cinv, b1, b2, q2t;
 
   // left eigenvectors applied to a conservative vector X, the acoustic rows
   // doubled: their fields are reconstructed at SC = 4, and the halving joins
   // the one of the reconstructed sum (exact factors, the same bits)
   // (no contraction: the same roundings for every stencil cell)
-  auto project = [&](const double (&X)[NF], double (&w)[NF]) {
+  __device__ __forceinline__ void project(const double (&X)[NF], double (&w)[NF]) const {
 #pragma clang fp contract(off)
+    constexpr int ND = NF - 2;
     double um = 0.0;
 #pragma unroll
     for (int d = 0; d < ND; ++d) um = fma(ut[d], X[1 + d], um);
@@ -596,7 +567,82 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
 #pragma unroll
     for (int t = 1; t < ND; ++t) w[1 + t] = fma(-ut[t], X[0], X[1 + t]);
     w[NF - 1] = fma(-Bn, cinv, A);
-  };
+  }
+
+  // right eigenvectors: characteristic fluxes to conservative variables
+  __device__ __forceinline__ void back_project(const double (&fc)[NF], double (&Fh)[NF]) const {
+    constexpr int ND = NF - 2;
+    const double s = fc[0] + fc[1] + fc[NF - 1];
+    const double dlr = fc[NF - 1] - fc[0];
+    Fh[0] = s;
+    Fh[1] = fma(ut[0], s, ct * dlr);
+    double e = fma(Ht, fc[0] + fc[NF - 1], ut[0] * ct * dlr);
+    e = fma(0.5 * q2t, fc[1], e);
+#pragma unroll
+    for (int t = 1; t < ND; ++t) {
+      Fh[1 + t] = fma(ut[t], s, fc[1 + t]);
+      e = fma(ut[t], fc[1 + t], e);
+    }
+    Fh[NF - 1] = e;
+  }
+};
+
+template <int NF, class P>
+__device__ __forceinline__ void roe_frame(P& prov, double gamma, RoeFrame<NF>& fr) {
+  constexpr int ND = NF - 2;
+  const double gm1 = gamma - 1.0;
+  RoeIn<NF> a, b;
+  prov.roe(0, a);
+  prov.roe(1, b);
+  const double w = rcp(a.rs + b.rs);
+#pragma unroll
+  for (int d = 0; d < ND; ++d) fr.ut[d] = fma(a.rs, a.u[d], b.rs * b.u[d]) * w;
+  fr.Ht = fma(a.rs, a.H, b.rs * b.H) * w;
+  double q2 = 0.0;
+#pragma unroll
+  for (int d = 0; d < ND; ++d) q2 = fma(fr.ut[d], fr.ut[d], q2);
+  fr.ct = sqrt(gm1 * fma(-0.5, q2, fr.Ht));
+  fr.cinv = rcp(fr.ct);
+  fr.b1 = gm1 * fr.cinv * fr.cinv;
+  fr.q2t = q2;
+  fr.b2 = 0.5 * q2 * fr.b1;
+}
+
+// Characteristic flux of field Q alone, by the expressions of euler_face (the
+// same bits): a face's fields can be taken by different wavefronts.
+template <int NF, int K, int LIM, bool ADAPT, int Q, class P>
+__device__ __forceinline__ double euler_field(P& prov, const RoeFrame<NF>& fr, const TenoParams& tp) {
+  constexpr int SC = (Q == 0 || Q == NF - 1) ? 4 : 2;
+  double alpha = 0.0;
+#pragma unroll
+  for (int m = 0; m < K; ++m) alpha = fmax(alpha, prov.speed(m));
+  double vp[K], vm[K];
+#pragma unroll
+  for (int m = 0; m < K; ++m) {
+    double X[NF], F[NF], w[NF], g[NF];
+    prov.state_flux(m, X, F);
+    fr.project(X, w);
+    fr.project(F, g);
+    lf_split2(g[Q], alpha, w[Q], vp[m], vm[K - 1 - m]);
+  }
+  uint32_t bits = 0u;
+  return (1.0 / SC) * (teno_m<K, LIM, false, ADAPT, true, SC>(vp, tp, bits) +
+                       teno_m<K, LIM, false, ADAPT, true, SC>(vm, tp, bits));
+}
+
+// ---------------------------------------------------------------------------
+// Euler face flux from a cell provider P:
+//   prov.cell(m, X, F, lam)  window cell m = 0..K-1 (cells i-K/2+1 .. i+K/2)
+//   prov.roe(s, r)           Roe input of cell i (s = 0) and i+1 (s = 1)
+// Characteristic fields are ordered (u_n - c, entropy, shear waves in
+// ascending axis order, u_n + c).
+// ---------------------------------------------------------------------------
+template <int NF, int K, int LIM, bool FLAGS, bool ADAPT, class P>
+__device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoParams& tp, double (&Fh)[NF],
+                                           uint32_t (&bits)[2][NF]) {
+  RoeFrame<NF> fr;
+  roe_frame<NF>(prov, gamma, fr);
+  auto project = [&](const double (&X)[NF], double (&w)[NF]) { fr.project(X, w); };
 
   double fc[NF];
   if constexpr (P::kReread) {
@@ -702,19 +748,7 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
     }
   }
 
-  // back to conservative variables with the right eigenvectors
-  const double s = fc[0] + fc[1] + fc[NF - 1];
-  const double dlr = fc[NF - 1] - fc[0];
-  Fh[0] = s;
-  Fh[1] = fma(ut[0], s, ct * dlr);
-  double e = fma(Ht, fc[0] + fc[NF - 1], ut[0] * ct * dlr);
-  e = fma(0.5 * q2t, fc[1], e);
-#pragma unroll
-  for (int t = 1; t < ND; ++t) {
-    Fh[1 + t] = fma(ut[t], s, fc[1 + t]);
-    e = fma(ut[t], fc[1 + t], e);
-  }
-  Fh[NF - 1] = e;
+  fr.back_project(fc, Fh);
 }
 
 // ---------------------------------------------------------------------------

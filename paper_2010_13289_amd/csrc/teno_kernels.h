@@ -173,14 +173,10 @@ struct StagedCells {
   __device__ __forceinline__ double value(int m) const { return at(0, c0 + m * CS); }
 };
 
-// Stage cell `cell` of the grid at staging index c: its state and, for the
-// Euler equations, its flux, signal speed and Roe inputs.
+// Stage a cell of state X at staging index c: its state and, for the Euler
+// equations, its flux, signal speed and Roe inputs.
 template <int NF>
-__device__ __forceinline__ void stage_cell(double* stage, int nc, int c, const double* __restrict__ U,
-                                           const int (&fld)[NF], double gamma, long N, long cell) {
-  double X[NF];
-#pragma unroll
-  for (int q = 0; q < NF; ++q) X[q] = U[fld[q] * N + cell];
+__device__ __forceinline__ void stage_put(double* stage, int nc, int c, const double (&X)[NF], double gamma) {
 #pragma unroll
   for (int q = 0; q < NF; ++q) stage[q * nc + c] = X[q];
   if constexpr (NF > 1) {
@@ -196,6 +192,16 @@ __device__ __forceinline__ void stage_cell(double* stage, int nc, int c, const d
     for (int d = 0; d < NF - 2; ++d) stage[(2 * NF + 2 + d) * nc + c] = r.u[d];
     stage[(3 * NF) * nc + c] = r.H;
   }
+}
+
+// Load cell `cell` of the grid and stage it.
+template <int NF>
+__device__ __forceinline__ void stage_cell(double* stage, int nc, int c, const double* __restrict__ U,
+                                           const int (&fld)[NF], double gamma, long N, long cell) {
+  double X[NF];
+#pragma unroll
+  for (int q = 0; q < NF; ++q) X[q] = U[fld[q] * N + cell];
+  stage_put<NF>(stage, nc, c, X, gamma);
 }
 
 // Waves per SIMD the face, row and tile kernels are compiled for: at most 168
@@ -756,9 +762,9 @@ hipError_t launch_faces(const FacesLaunch& a) {
   if constexpr (NF != 3) return launch_faces_tx<NF, K, LIM, ADAPT, kTileColumns>(a);
 }
 
-template <int NF, int K, int LIM, bool ADAPT>
-hipError_t launch_sweep(const SweepLaunch& a) {
-  SweepParams<NF> p;
+// what every sweep kernel takes over from the launch
+template <int NF>
+void fill_sweep(const SweepLaunch& a, SweepParams<NF>& p) {
   p.U = a.U;
   p.R = a.R;
   p.U0 = a.U0;
@@ -775,6 +781,12 @@ hipError_t launch_sweep(const SweepLaunch& a) {
   p.inv_dx = a.inv_dx;
   p.fp = a.fp;
   for (int q = 0; q < NF; ++q) p.fld[q] = a.fld[q];
+}
+
+template <int NF, int K, int LIM, bool ADAPT>
+hipError_t launch_sweep(const SweepLaunch& a) {
+  SweepParams<NF> p;
+  fill_sweep<NF>(a, p);
   if (a.axis == 0) {
     p.n = a.nx;
     p.seg = (a.bc == 0 && a.nx <= 256) ? a.nx : 255;
@@ -799,22 +811,7 @@ hipError_t launch_sweep(const SweepLaunch& a) {
 template <int NF, int K, int LIM, bool ADAPT>
 hipError_t launch_tile(const SweepLaunch& a) {
   SweepParams<NF> p;
-  p.U = a.U;
-  p.R = a.R;
-  p.U0 = a.U0;
-  p.Uout = a.Uout;
-  p.a = a.a;
-  p.b = a.b;
-  p.dt = a.dt;
-  p.dtp = a.dtp;
-  p.mode = a.mode;
-  p.nx = a.nx;
-  p.ny = a.ny;
-  p.nz = a.nz;
-  p.bc = a.bc;
-  p.inv_dx = a.inv_dx;
-  p.fp = a.fp;
-  for (int q = 0; q < NF; ++q) p.fld[q] = a.fld[q];
+  fill_sweep<NF>(a, p);
   if (a.axis < 0 || a.axis > 2) return hipErrorInvalidValue;
   p.n = (a.axis == 0) ? a.nx : (a.axis == 1) ? a.ny : a.nz;
   p.seg = tile_segment(a.axis, p.n, a.nx, a.ny, a.nz, a.bc);

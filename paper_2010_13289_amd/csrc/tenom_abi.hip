@@ -210,6 +210,9 @@ int comb3(double* out, double c0, const double* x, double c1, const double* y1, 
   return e == hipSuccess ? TENOM_OK : hip_fail(e, "combination launch");
 }
 
+// longest 1D Euler line swept with one wavefront per field
+constexpr int kFieldsCells = 40960;
+
 // kernel of the sweeps (tenom_set_sweep_kernel)
 std::atomic<int> g_sweep_kernel{TENOM_SWEEP_AUTO};
 
@@ -281,13 +284,63 @@ int sweep(const tenom_grid* g, int scheme, int limiter, double C_T, double gamma
   field_map(g, axis, L.fld);
   L.fp = face_params(g, scheme, axis, limiter, C_T, gamma);
   L.stream = stream;
+  // A 1D Euler line of at most kFieldsCells leaves the chip part empty: one
+  // wavefront per field shortens the pass.  Sweep by fields against the row
+  // sweep, us, shock tube and rough data alike: six points 1000 cells 7.2 and
+  // 8.9, 65,000 8.5 and 9.6 (rough 10.4 and 9.9); eight points 4096 7.4 and
+  // 10.6, 20,000 7.9 and 10.8 (9.4 and 11.3), 65,000 9.5 and 11.6 (12.9 and 11.9).
+  const bool fields = choice == TENOM_SWEEP_AUTO && g->ndim == 1 && nf == 3 && d.nx <= kFieldsCells;
   hipError_t e;
   {
     ProfScope ps(1 + axis, stream);
-    e = (tile ? tf : sf)(kind, adaptive ? 1 : 0, L);
+    if (fields)
+      e = (K == 6 ? tenom_fields_nf3_k6 : tenom_fields_nf3_k8)(kind, adaptive ? 1 : 0, L);
+    else
+      e = (tile ? tf : sf)(kind, adaptive ? 1 : 0, L);
   }
   if (e != hipSuccess) return hip_fail(e, "sweep launch");
   return TENOM_OK;
+}
+
+// Whether the whole step of this grid runs as one launch (step_line).
+bool step_line_fits(const tenom_grid* g) {
+  return g->ndim == 1 && line_fits(nfields(g), g->n[0], g->bc[0]) &&
+         g_sweep_kernel.load(std::memory_order_relaxed) == TENOM_SWEEP_AUTO;
+}
+
+// One SSP-RK3 step of a line of at most one workgroup (step_line_fits): with
+// cfl > 0 its step size too, written to dt_ws (and dt_out), else dt.  U1 and U2
+// receive the stage states where not NULL.
+int step_line(const tenom_grid* g, int scheme, int limiter, double C_T, double gamma, double dt, double cfl, double* U,
+              double* U1, double* U2, double* dt_ws, double* dt_out, hipStream_t stream) {
+  const int nf = nfields(g);
+  bool adaptive;
+  const int K = scheme_K(scheme, &adaptive);
+  int kind;
+  double beta;
+  limiter_kind(limiter, &kind, &beta);
+  LineLaunch L;
+  L.p.U = U;
+  L.p.U1 = U1;
+  L.p.U2 = U2;
+  L.p.n = g->n[0];
+  L.p.bc = g->bc[0];
+  L.p.inv_dx = 1.0 / g->dx[0];
+  L.p.dt = dt;
+  L.p.cfl = cfl;
+  L.p.dt_ws = dt_ws;
+  L.p.dt_out = dt_out;
+  L.p.fp = face_params(g, scheme, 0, limiter, C_T, gamma);
+  L.stream = stream;
+  using LineFn = hipError_t (*)(int, int, const LineLaunch&);
+  const LineFn fn = nf == 1 ? (K == 6 ? tenom_line_nf1_k6 : tenom_line_nf1_k8)
+                            : (K == 6 ? tenom_line_nf3_k6 : tenom_line_nf3_k8);
+  hipError_t e;
+  {
+    ProfScope ps(1, stream);
+    e = fn(kind, adaptive ? 1 : 0, L);
+  }
+  return e == hipSuccess ? TENOM_OK : hip_fail(e, "line step launch");
 }
 
 // small per-device buffer for the reductions
@@ -582,6 +635,7 @@ namespace {
 int rk3_stages(const tenom_grid* g, int scheme, int limiter, double C_T, double gamma, double dt, double* U, double* R,
                double* U1, double* U2, hipStream_t s, const double* dtp = nullptr) {
   const int nd = g->ndim;
+  if (!dtp && step_line_fits(g)) return step_line(g, scheme, limiter, C_T, gamma, dt, 0.0, U, U1, U2, nullptr, nullptr, s);
   // (a, b) of U_out = a U^n + b (U_s + dt L(U_s)), stage inputs and outputs
   const double A[3] = {0.0, 0.75, 1.0 / 3.0};
   const double B[3] = {1.0, 0.25, 2.0 / 3.0};
@@ -648,6 +702,8 @@ int tenom::abi::rk3_step_cfl_ws(const tenom_grid* grid, int scheme, int limiter,
   double* U2 = (double*)((char*)ws + 2 * state);
   unsigned long long* part = (unsigned long long*)((char*)ws + 3 * state);
   double* dt_dev = (double*)(part + kRateBlocks);
+  if (step_line_fits(grid))
+    return step_line(grid, scheme, limiter, C_T, gamma, 0.0, cfl, U, nullptr, nullptr, dt_dev, dt_out, s);
   const long N = dims(grid).N;
   hipError_t e = launch_rate(grid, gamma, U, N, nullptr, part, s);
   if (e != hipSuccess) return hip_fail(e, "wave-speed kernel launch");

@@ -1,6 +1,7 @@
 // One instantiation unit: every limiter kind (and, for K = 8, the adaptive
 // cutoff) for TENOM_NF fields and K = TENOM_K; with TENOM_TILE_UNIT the
-// tile sweeps, else the face kernel and the row and march sweeps.
+// tile sweeps, else the face kernel, the row and march sweeps and the
+// single-line kernels.
 #include <type_traits>
 
 #include "dispatch.h"
@@ -65,4 +66,23 @@ hipError_t TENOM_EXPAND_SWEEP(TENOM_NF, TENOM_K)(int lim, int adapt, const Sweep
     return launch_sweep<TENOM_NF, TENOM_K, decltype(L)::value, decltype(A)::value>(x);
   });
 }
+
+#if TENOM_NF == 1 || TENOM_NF == 3
+#define TENOM_UNIT_LINE(nf, k) TENOM_NAME(line, nf, k)
+#define TENOM_EXPAND_LINE(nf, k) TENOM_UNIT_LINE(nf, k)
+hipError_t TENOM_EXPAND_LINE(TENOM_NF, TENOM_K)(int lim, int adapt, const LineLaunch& a) {
+  return by_scheme(lim, adapt, a, [](auto L, auto A, const LineLaunch& x) {
+    return launch_step_line<TENOM_NF, TENOM_K, decltype(L)::value, decltype(A)::value>(x);
+  });
+}
+#endif
+#if TENOM_NF == 3
+#define TENOM_UNIT_FIELDS(nf, k) TENOM_NAME(fields, nf, k)
+#define TENOM_EXPAND_FIELDS(nf, k) TENOM_UNIT_FIELDS(nf, k)
+hipError_t TENOM_EXPAND_FIELDS(TENOM_NF, TENOM_K)(int lim, int adapt, const SweepLaunch& a) {
+  return by_scheme(lim, adapt, a, [](auto L, auto A, const SweepLaunch& x) {
+    return launch_sweep_fields<TENOM_K, decltype(L)::value, decltype(A)::value>(x);
+  });
+}
+#endif
 #endif

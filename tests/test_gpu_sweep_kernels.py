@@ -161,3 +161,84 @@ def test_segments_agree_with_the_march(T, shape, bc, K):
     U = W.random_euler_state(shape, seed=sum(shape) + K, kind="mixed")
     print(f"[segments] n={n} bc={bc} K={K}", flush=True)
     check_identical(T, grid, U, K, 1, 1e-5 if K == 6 else 1e-7, "segments")
+
+
+# 1D lines, where the automatic choice takes a whole step in one launch (up to
+# 256 faces of the Euler equations, 1024 of the scalar equation) and, above,
+# sweeps with one wavefront per field (workgroups of 63 cells, or a periodic
+# line of at most 64 whole), against the row sweep that the line setting
+# forces.  A periodic line has n faces, a transmissive one n + 1.
+LINES = [(n, bc, 1, K, lim) for n, K, lim in ((8, 8, 0), (63, 6, 1), (64, 8, 2), (65, 6, 3), (127, 8 | 0x100, 1),
+                                               (255, 6, 7), (256, 8, 1), (257, 8, 3), (378, 6, 0), (1001, 8 | 0x100, 2),
+                                               (40960, 6, 1), (40961, 8, 1)) for bc in (0, 1)]
+LINES += [(n, bc, 0, K, lim) for n, K, lim in ((6, 6, 0), (65, 8, 1), (200, 6, 1), (1023, 8 | 0x100, 2), (1024, 6, 3),
+                                               (1025, 8, 1)) for bc in (0, 1)]
+
+
+def line_case(n, bc, system, seed):
+    grid = dict(ndim=1, n=[n], dx=[1.0 / n], bc=[bc], system=system, adv=[-0.7, 0.0, 0.0])
+    if system == 1:
+        return grid, W.random_euler_state((n,), seed=seed, kind="mixed")
+    x = (np.arange(n) + 0.5) / n
+    U = np.sin(2 * np.pi * x) + (np.abs(x - 0.5) < 0.2) + 1e-3 * np.random.default_rng(seed).standard_normal(n)
+    return grid, U[None]
+
+
+@pytest.mark.parametrize("n,bc,system,K,lim", LINES, ids=["-".join(map(str, c)) for c in LINES])
+def test_line_kernels_agree_with_the_row_sweep(T, n, bc, system, K, lim):
+    import torch
+    C_T = 0.0 if K & 0x100 else (1e-5 if K == 6 else 1e-7)
+    grid, U = line_case(n, bc, system, seed=n + K)
+    print(f"[lines] n={n} bc={bc} system={system} K={K} lim={lim}", flush=True)
+    dt = 0.4 / T.max_wave_speed(to_dev(U), grid, GAMMA)
+
+    def results():
+        Ud = to_dev(U)
+        out = [to_host(T.flux_divergence(Ud, grid, K, lim, C_T, GAMMA))]
+        T.rk3_step(Ud, grid, K, lim, C_T, GAMMA, dt)
+        out.append(to_host(Ud))
+        dts = torch.zeros(1, dtype=torch.float64, device="cuda")
+        for _ in range(2):
+            T.rk3_step_cfl(Ud, grid, K, lim, C_T, GAMMA, 0.4, dt_out=dts)
+            out += [to_host(Ud), dts.cpu().numpy()]
+        return out
+
+    got = {}
+    for kind in (T.SWEEP_AUTO, T.SWEEP_MARCH):
+        T.set_sweep_kernel(kind)
+        try:
+            got[kind] = results()
+        finally:
+            T.set_sweep_kernel(T.SWEEP_AUTO)
+    names = ("divergence", "RK3 step", "CFL step", "dt", "second CFL step", "second dt")
+    for name, a, b in zip(names, got[T.SWEEP_AUTO], got[T.SWEEP_MARCH]):
+        assert np.array_equal(a, b), f"{name} differs between the line kernels and the row sweep"
+
+
+@pytest.mark.parametrize("n,system", [(200, 1), (500, 1), (300, 0)])
+def test_line_steps_in_a_captured_graph(T, n, system):
+    """Three CFL steps captured once and replayed, with eager steps of another
+    state and a synchronisation between the replays: the eager result, bit for
+    bit, after each."""
+    import torch
+    grid, U = line_case(n, 0, system, seed=n)
+    args = (grid, 6, 1, 1e-5, GAMMA, 0.4)
+    print(f"[line graph] n={n} system={system}", flush=True)
+    Ug, Ue, other = to_dev(U), to_dev(U), to_dev(U)
+    wsg, wse = T.Workspace(grid, 6), T.Workspace(grid, 6)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        T.rk3_step_cfl(other, *args, workspace=wsg, stream=side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        for _ in range(3):
+            T.rk3_step_cfl(Ug, *args, workspace=wsg, stream=side)
+    for replay in range(3):
+        graph.replay()
+        T.rk3_step_cfl(other, *args, workspace=wse)
+        for _ in range(3):
+            T.rk3_step_cfl(Ue, *args, workspace=wse)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(Ug), to_host(Ue)), f"replay {replay}"
