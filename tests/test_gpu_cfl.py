@@ -100,3 +100,31 @@ def test_nonfinite_state_gives_nonfinite_step(T):
     T.rk3_step_cfl(Ud, grid, K, lim, C_T, GAMMA, CFL, workspace=T.Workspace(grid, K), dt_out=dto)
     assert np.isnan(dto.item())
     assert not T.check_finite(Ud, grid)
+
+
+# One block forms the step size where cells times fields are at most 20,480 (and
+# of any scalar grid), a thread every 1024th cell; two launches above.
+RATE_GRIDS = [((20, 12), 1), ((31, 33), 1), ((64, 80), 1), ((64, 81), 1), ((16, 16, 16), 1), ((16, 17, 16), 1),
+              ((341,), 1), ((1025,), 1), ((6826,), 1), ((6827,), 1), ((40, 50), 0), ((9, 10, 11), 0), ((2000,), 0)]
+
+
+@pytest.mark.parametrize("bad", [None, "nan"])
+@pytest.mark.parametrize("shape,system", RATE_GRIDS, ids=[f"{'x'.join(map(str, s))}-{e}" for s, e in RATE_GRIDS])
+def test_step_size_is_cfl_over_the_largest_rate(T, shape, system, bad):
+    import torch
+    nd = len(shape)
+    grid = dict(ndim=nd, n=list(reversed(shape)), dx=[0.05, 0.07, 0.06][:nd], bc=[0] * nd, system=system,
+                adv=[0.3, -0.9, 0.7])
+    if system == 1:
+        U = W.random_euler_state(shape, seed=len(shape), kind="mixed")
+        if bad:
+            U.reshape(nd + 2, -1)[0, -1] = np.nan
+        want = CFL / T.max_wave_speed(to_dev(U), grid, GAMMA)
+    else:
+        U = np.ones((1,) + shape)
+        want = CFL / T.max_wave_speed(to_dev(U), grid, GAMMA)
+    print(f"[step size] {shape} {system} {bad}", flush=True)
+    dto = torch.zeros(1, dtype=torch.float64, device="cuda")
+    T.rk3_step_cfl(to_dev(U), grid, 6, 1, 1e-5, GAMMA, CFL, dt_out=dto)
+    assert dto.item() == want or (np.isnan(want) and np.isnan(dto.item()))
+    assert np.isnan(want) == (bad is not None and system == 1)
