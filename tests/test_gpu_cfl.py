@@ -128,3 +128,22 @@ def test_step_size_is_cfl_over_the_largest_rate(T, shape, system, bad):
     T.rk3_step_cfl(to_dev(U), grid, 6, 1, 1e-5, GAMMA, CFL, dt_out=dto)
     assert dto.item() == want or (np.isnan(want) and np.isnan(dto.item()))
     assert np.isnan(want) == (bad is not None and system == 1)
+
+
+# Per-block maxima: one cell a thread up to 1024 blocks of 256, then 1024 blocks
+# up to four cells a thread, then blocks of 1024 cells up to 4096 of them; the
+# largest rate in the first, a middle and the last cell.
+@pytest.mark.parametrize("where", [0, 0.5, 1])
+@pytest.mark.parametrize("n", [262144, 262145, 300000, 1048576, 1048577, 1100000, 4194304, 4194305])
+def test_step_size_over_many_blocks(T, n, where):
+    import torch
+    grid = dict(ndim=1, n=[n], dx=[0.01], bc=[0], system=1)
+    U = np.empty((3, n))
+    U[0], U[1], U[2] = 1.0, 0.5, 2.0
+    U[1, int(where * (n - 1))] = -0.75
+    print(f"[step size] {n} {where}", flush=True)
+    dto = torch.zeros(1, dtype=torch.float64, device="cuda")
+    T.rk3_step_cfl(to_dev(U), grid, 6, 1, 1e-5, GAMMA, CFL, dt_out=dto)
+    assert dto.item() == CFL / T.max_wave_speed(to_dev(U), grid, GAMMA)
+    p = (GAMMA - 1.0) * (2.0 - 0.5 * 0.75**2)
+    np.testing.assert_allclose(dto.item(), CFL * 0.01 / (0.75 + np.sqrt(GAMMA * p)), rtol=1e-14)
