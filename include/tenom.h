@@ -318,7 +318,9 @@ int tenom_batch_tile_shape(int tile, int* threads, int* faces_per_thread);
  * no-op).  n, dx: HOST arrays of count entries, n[p] >= 6, dx[p] > 0.
  * bc: TENOM_BC_PERIODIC or TENOM_BC_TRANSMISSIVE for every problem.
  * Allocates the plan's device memory (about 48 * total bytes plus small
- * tables); clocks start at 0; the tile is 3 until set or autotuned.
+ * tables); clocks start at 0; the tile is 3 until set or autotuned,
+ * and until then calls on at most 1536 segments of 63 cells run one wavefront
+ * per field instead of a tile (the same bits).
  * Errors: EINVAL for bad arguments (no allocation), EHIP if an allocation
  * fails.
  */

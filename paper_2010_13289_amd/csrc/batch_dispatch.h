@@ -19,3 +19,8 @@ TENOM_DECLARE_BATCH_TILE(5)
 // The persistent batched kernel (tenom_batch_inst.hip with -DTENOM_PERSIST):
 // K = 6, K = 8 and the adaptive K = 8 for every limiter.
 hipError_t tenom_batch_persist(int K, int lim, int adapt, const tenom::PersistLaunch& a);
+
+// The batched sweep with one wavefront per field (the three-field units of
+// tenom_inst.hip).
+hipError_t tenom_batch_fields_nf3_k6(int lim, int adapt, const tenom::BatchLaunch& a);
+hipError_t tenom_batch_fields_nf3_k8(int lim, int adapt, const tenom::BatchLaunch& a);

@@ -423,9 +423,7 @@ struct BatchLaunch {
   hipStream_t stream;
 };
 
-template <int K, int LIM, bool ADAPT, int TPB, int FPT>
-hipError_t launch_batch_row(const BatchLaunch& a) {
-  if (a.nseg <= 0) return hipSuccess;
+inline BatchParams<3> batch_params(const BatchLaunch& a) {
   BatchParams<3> p;
   p.U = a.U;
   p.U0 = a.U0;
@@ -439,7 +437,13 @@ hipError_t launch_batch_row(const BatchLaunch& a) {
   p.total = a.total;
   p.bc = a.bc;
   p.fp = a.fp;
-  hipLaunchKernelGGL((k_batch_row<3, K, LIM, ADAPT, TPB, FPT>), dim3(a.nseg), dim3(TPB), 0, a.stream, p);
+  return p;
+}
+
+template <int K, int LIM, bool ADAPT, int TPB, int FPT>
+hipError_t launch_batch_row(const BatchLaunch& a) {
+  if (a.nseg <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_batch_row<3, K, LIM, ADAPT, TPB, FPT>), dim3(a.nseg), dim3(TPB), 0, a.stream, batch_params(a));
   return hipGetLastError();
 }
 

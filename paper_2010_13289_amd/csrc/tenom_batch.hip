@@ -36,6 +36,7 @@ struct tenom_batch_plan {
     std::vector<int> first;  // [count + 1] first segment of each problem
   } tiling[kNumTiles];
   int tile = 3;
+  bool tile_set = false;  // by the caller or the autotuner
   // persistent path: the problems longest first, and the queue counters
   int nblk = 0;
   int* order_d = nullptr;
@@ -75,6 +76,14 @@ __global__ __launch_bounds__(256) void k_batch_dt(const double* __restrict__ U, 
 using RowFn = hipError_t (*)(int, int, int, const BatchLaunch&);
 const RowFn kRow[kNumTiles] = {tenom_batch_row_tile0, tenom_batch_row_tile1, tenom_batch_row_tile2,
                                tenom_batch_row_tile3, tenom_batch_row_tile4, tenom_batch_row_tile5};
+
+// Segments of 63 cells up to which a batch whose tile nobody chose runs with one
+// wavefront per field.  us a graph step, that and tile 3, Riemann problems at
+// eight points (MP; rough data in brackets): 172 segments 24.0 and 36.5 (24.4
+// and 36.8), 598 29.5 and 36.9 (33.2 and 37.6), 1300 37.3 and 46.3 (45.5 and
+// 50.4), 2530 53.0 and 50.2 (67.0 and 66.0), 5100 83 and 64 (115 and 110); six
+// points cross between the same counts.
+constexpr int kFieldsSegments = 1536;
 
 // Segments of one tile: (problem, first cell).  A segment covers FACES - 1
 // cells; a periodic problem of at most FACES cells is one wrapped segment
@@ -158,7 +167,10 @@ int check_call(const tenom_batch_plan* P, int scheme, int limiter, double C_T, d
 int enqueue(tenom_batch_plan* P, const Method& m, double cfl, int steps, int first, int cnt, double* U,
             hipStream_t s) {
   if (cnt <= 0 || steps <= 0) return TENOM_OK;
-  const auto& T = P->tiling[P->tile];
+  // few segments leave the chip part empty: one wavefront per field, unless a
+  // tile was asked for
+  const bool fields = !P->tile_set && P->tiling[0].first[first + cnt] - P->tiling[0].first[first] <= kFieldsSegments;
+  const auto& T = P->tiling[fields ? 0 : P->tile];
   const int sb = T.first[first], se = T.first[first + cnt];
   BatchLaunch L;
   L.off = P->off_d;
@@ -192,7 +204,10 @@ int enqueue(tenom_batch_plan* P, const Method& m, double cfl, int steps, int fir
       L.b = B[st];
       {
         ProfScope ps(4, s);
-        e = kRow[P->tile](m.K, m.kind, m.adapt ? 1 : 0, L);
+        if (fields)
+          e = (m.K == 6 ? tenom_batch_fields_nf3_k6 : tenom_batch_fields_nf3_k8)(m.kind, m.adapt ? 1 : 0, L);
+        else
+          e = kRow[P->tile](m.K, m.kind, m.adapt ? 1 : 0, L);
       }
       if (e != hipSuccess) return hip_fail(e, "batched sweep launch");
     }
@@ -295,6 +310,7 @@ int tenom_batch_set_tile(tenom_batch_plan* plan, int tile) {
   if (!plan) return fail(TENOM_EINVAL, "plan is NULL");
   if (tile < 0 || tile >= kNumTiles) return fail(TENOM_EINVAL, "tile %d not in [0, %d)", tile, kNumTiles);
   plan->tile = tile;
+  plan->tile_set = true;
   return TENOM_OK;
 }
 
@@ -318,7 +334,7 @@ int tenom_batch_rk3_graph(tenom_batch_plan* plan, int scheme, int limiter, doubl
   int rc = check_call(plan, scheme, limiter, C_T, gamma, cfl, steps, U, &m);
   if (rc) return rc;
   if (plan->count == 0 || steps == 0) return TENOM_OK;
-  tenom_batch_plan::Key k{scheme, limiter, steps, plan->tile, C_T, gamma, cfl, U};
+  tenom_batch_plan::Key k{scheme, limiter, steps, plan->tile_set ? plan->tile : -1, C_T, gamma, cfl, U};
   hipError_t e;
   if (!plan->exec || !(k == plan->key)) {
     if (plan->exec) {
@@ -406,6 +422,8 @@ int tenom_batch_autotune(tenom_batch_plan* plan, int scheme, int limiter, double
   if (e == hipSuccess) e = hipMemcpyAsync(save, plan->t_d, clocks, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync((char*)save + clocks, plan->dt_d, clocks, hipMemcpyDeviceToDevice, s);
   const int keep = plan->tile;
+  const bool keep_set = plan->tile_set;
+  plan->tile_set = true;
   int pick = keep;
   float best_ms = 0.f;
   for (int t = 0; t < kNumTiles && e == hipSuccess && rc == TENOM_OK; ++t) {
@@ -428,6 +446,7 @@ int tenom_batch_autotune(tenom_batch_plan* plan, int scheme, int limiter, double
     }
   }
   plan->tile = (e == hipSuccess && !rc) ? pick : keep;
+  plan->tile_set = (e == hipSuccess && !rc) || keep_set;
   if (save) {
     hipMemcpyAsync(plan->t_d, save, clocks, hipMemcpyDeviceToDevice, s);
     hipMemcpyAsync(plan->dt_d, (char*)save + clocks, clocks, hipMemcpyDeviceToDevice, s);

@@ -84,5 +84,13 @@ hipError_t TENOM_EXPAND_FIELDS(TENOM_NF, TENOM_K)(int lim, int adapt, const Swee
     return launch_sweep_fields<TENOM_K, decltype(L)::value, decltype(A)::value>(x);
   });
 }
+
+#define TENOM_UNIT_BATCH_FIELDS(nf, k) TENOM_NAME(batch_fields, nf, k)
+#define TENOM_EXPAND_BATCH_FIELDS(nf, k) TENOM_UNIT_BATCH_FIELDS(nf, k)
+hipError_t TENOM_EXPAND_BATCH_FIELDS(TENOM_NF, TENOM_K)(int lim, int adapt, const BatchLaunch& a) {
+  return by_scheme(lim, adapt, a, [](auto L, auto A, const BatchLaunch& x) {
+    return launch_batch_fields<TENOM_K, decltype(L)::value, decltype(A)::value>(x);
+  });
+}
 #endif
 #endif

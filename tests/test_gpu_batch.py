@@ -432,3 +432,44 @@ def test_constant_runs_against_the_single_grid_step(T, scheme, lim, C_T, bc):
     finally:
         T.set_sweep_kernel(T.SWEEP_AUTO)
     plan.close()
+
+
+# The sweep of a small batch whose tile nobody chose (one wavefront per field, at
+# most 1536 segments of 63 cells; a periodic problem of at most 64 cells is
+# one), and batches on both sides of that count.
+@pytest.mark.parametrize("sizes", [SIZES + [126, 190, 2000], [63] * 1536, [63] * 1536 + [8]],
+                         ids=["ragged", "1536", "1537"])
+@pytest.mark.parametrize("scheme,lim,C_T", [(6, 1, 1e-5), (6, 7, 1e-5), (8, 2, 1e-7), (8 | 0x100, 1, 0.0)])
+@pytest.mark.parametrize("bc", [0, 1])
+def test_small_batches_agree_with_a_chosen_tile(T, sizes, scheme, lim, C_T, bc):
+    U, dx, _ = ragged_batch(sizes, seed0=300)
+    for p, b in enumerate(np.cumsum([0] + sizes[:-1])):  # the rest flat, extreme or rough
+        if p % 3 == 1:
+            left, right = FLAT_STATES[(p // 3) % 5]
+            U[:, b:b + sizes[p]] = W.riemann_problem(sizes[p], left, right, gamma=GAMMA)[0]
+        elif p % 3 == 2:
+            U[:, b:b + sizes[p]] *= 1 + 1e-3 * np.random.default_rng(p).standard_normal((3, sizes[p]))
+    print(f"[small batch] {len(sizes)} problems {scheme} {lim} bc={bc}", flush=True)
+    plan, chosen = T.BatchPlan(sizes, dx, bc), T.BatchPlan(sizes, dx, bc)
+    chosen.tile = 3
+    assert plan.tile == 3
+    want = to_host(chosen.rk3(to_dev(U), scheme, lim, C_T, GAMMA, CFL, steps=2))
+    half = len(sizes) // 2
+    Ud = to_dev(U)
+    plan.rk3(Ud, scheme, lim, C_T, GAMMA, CFL, steps=2, first=0, count=half)
+    plan.rk3(Ud, scheme, lim, C_T, GAMMA, CFL, steps=2, first=half)
+    Ug = to_dev(U)
+    plan.reset_times()
+    plan.rk3_graph(Ug, scheme, lim, C_T, GAMMA, CFL, steps=2)
+    for got in (to_host(Ud), to_host(Ug)):
+        assert np.array_equal(got, want, equal_nan=True)
+        finite = np.isfinite(want)
+        assert np.array_equal(np.signbit(got[finite]), np.signbit(want[finite]))
+    assert all(np.array_equal(a, b, equal_nan=True) for a, b in zip(plan.times(), chosen.times()))
+    # a tile chosen later takes the tile's kernel, with the same bits
+    plan.tile = 0
+    Ug = to_dev(U)
+    plan.rk3_graph(Ug, scheme, lim, C_T, GAMMA, CFL, steps=2)
+    assert np.array_equal(to_host(Ug), want, equal_nan=True)
+    plan.close()
+    chosen.close()
