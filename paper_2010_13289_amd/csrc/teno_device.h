@@ -608,10 +608,12 @@ __device__ __forceinline__ void roe_frame(P& prov, double gamma, RoeFrame<NF>& f
   fr.b2 = 0.5 * q2 * fr.b1;
 }
 
-// Characteristic flux of field Q alone, by the expressions of euler_face (the
-// same bits): a face's fields can be taken by different wavefronts.
-template <int NF, int K, int LIM, bool ADAPT, int Q, class P>
-__device__ __forceinline__ double euler_field(P& prov, const RoeFrame<NF>& fr, const TenoParams& tp) {
+// Characteristic flux of field Q alone (and, with FLAGS, the smoothness bits of
+// its two reconstructions), by the expressions of euler_face (the same bits): a
+// face's fields can be taken by different wavefronts.
+template <int NF, int K, int LIM, bool FLAGS, bool ADAPT, int Q, class P>
+__device__ __forceinline__ double euler_field(P& prov, const RoeFrame<NF>& fr, const TenoParams& tp,
+                                              uint32_t (&bits)[2]) {
   constexpr int SC = (Q == 0 || Q == NF - 1) ? 4 : 2;
   double alpha = 0.0;
 #pragma unroll
@@ -625,9 +627,18 @@ __device__ __forceinline__ double euler_field(P& prov, const RoeFrame<NF>& fr, c
     fr.project(F, g);
     lf_split2(g[Q], alpha, w[Q], vp[m], vm[K - 1 - m]);
   }
-  uint32_t bits = 0u;
-  return (1.0 / SC) * (teno_m<K, LIM, false, ADAPT, true, SC>(vp, tp, bits) +
-                       teno_m<K, LIM, false, ADAPT, true, SC>(vm, tp, bits));
+  return (1.0 / SC) * (teno_m<K, LIM, FLAGS, ADAPT, true, SC>(vp, tp, bits[0]) +
+                       teno_m<K, LIM, FLAGS, ADAPT, true, SC>(vm, tp, bits[1]));
+}
+
+// The same for a field known at run time (one per wavefront).
+template <int NF, int K, int LIM, bool FLAGS, bool ADAPT, int Q = 0, class P>
+__device__ __forceinline__ double field_by_index(int q, P& prov, const RoeFrame<NF>& fr, const TenoParams& tp,
+                                                 uint32_t (&bits)[2]) {
+  if constexpr (Q < NF - 1) {
+    if (q != Q) return field_by_index<NF, K, LIM, FLAGS, ADAPT, Q + 1>(q, prov, fr, tp, bits);
+  }
+  return euler_field<NF, K, LIM, FLAGS, ADAPT, Q>(prov, fr, tp, bits);
 }
 
 // ---------------------------------------------------------------------------

@@ -547,6 +547,76 @@ void k_faces(FacesParams<NF> p) {
   if (j0 + f == 0 && nfl == n) store(n);
 }
 
+// The same for grids that leave the chip part empty, where the time is one
+// workgroup's chain: one wavefront per characteristic field takes 64 faces (64 /
+// TX of TX lines), wave q stores component q.  288 cells at eight points 11.8 ->
+// 7.5 us, 128x128 14.7 -> 8.6, 20x20x20 16.0 -> 9.8.
+template <int NF, int K, int LIM, bool ADAPT, int TX, bool FLAGS>
+__global__ __launch_bounds__(64 * NF) void k_faces_fields(FacesParams<NF> p) {
+  constexpr int FJ = 64 / TX;
+  constexpr int ROWS = FJ + K - 1, NC = ROWS * TX;
+  __shared__ double stage[RowStage<NF>::NE * NC];
+  __shared__ double fcs[NF * 64];
+  const int n = p.axis == 0 ? p.nx : (p.axis == 1 ? p.ny : p.nz);
+  const int across = p.axis == 0 ? p.ny : p.nx;
+  const int nfl = p.bc == 0 ? n : n + 1;  // a periodic line's face n is its face 0
+  const int ncg = (across + TX - 1) / TX, nch = (nfl + FJ - 1) / FJ;
+  const int b = (int)blockIdx.x;
+  const int o = b / ncg / nch;  // z of an x or y line, y of a z line
+  const int j0 = (b / ncg % nch) * FJ;
+  const int c0 = (b % ncg) * TX;
+  const int nfk = min(FJ, nfl - j0);
+  const long N = (long)p.nx * p.ny * p.nz;
+  const int t = threadIdx.x, q = threadIdx.y, col = t % TX, f = t / TX;
+  // lines beyond the grid stage a real line and store nothing
+  auto line = [&](int cc) {
+    const int cs = min(c0 + cc, across - 1);
+    if (p.axis == 0) return Line{(cs + (long)p.ny * o) * p.nx, 1, n, p.bc};
+    if (p.axis == 1) return Line{cs + (long)p.nx * p.ny * o, p.nx, n, p.bc};
+    return Line{cs + (long)p.nx * o, (long)p.nx * p.ny, n, p.bc};
+  };
+  for (int c = q * 64 + t; c < (nfk + K - 1) * TX; c += 64 * NF)
+    stage_cell<NF>(stage, NC, c, p.U, p.fld, p.fp.gamma, N, cell_at(line(c % TX), j0 - K / 2 + c / TX));
+  __syncthreads();
+  StagedCells<NF, K, TX, true> prov{stage, NC, min(f, nfk - 1) * TX + col};
+  RoeFrame<NF> fr;
+  uint32_t bits[2] = {0u, 0u};
+  roe_frame<NF>(prov, p.fp.gamma, fr);
+  fcs[q * 64 + t] = field_by_index<NF, K, LIM, FLAGS, ADAPT>(q, prov, fr, p.fp.tp, bits);
+  __syncthreads();
+  double fc[NF], Fh[NF];
+#pragma unroll
+  for (int i = 0; i < NF; ++i) fc[i] = fcs[i * 64 + t];
+  fr.back_project(fc, Fh);
+  double F = Fh[0];
+#pragma unroll
+  for (int i = 1; i < NF; ++i) F = q == i ? Fh[i] : F;
+  const int c = c0 + col;
+  if (f >= nfk || c >= across) return;
+  long face, fstride;  // index of the line's face 0, step along the axis
+  if (p.axis == 0) {
+    face = (c + (long)p.ny * o) * (p.nx + 1);
+    fstride = 1;
+  } else if (p.axis == 1) {
+    face = c + (long)p.nx * (p.ny + 1) * o;
+    fstride = p.nx;
+  } else {
+    face = c + (long)p.nx * o;
+    fstride = (long)p.nx * p.ny;
+  }
+  const long nfaces = N / n * (n + 1);
+  auto store = [&](int j) {
+    const long at = face + (long)j * fstride;
+    p.Fhat[(long)p.fld[q] * nfaces + at] = F;
+    if constexpr (FLAGS) {
+      p.flags[(long)q * nfaces + at] = (uint8_t)bits[0];
+      p.flags[(long)(NF + q) * nfaces + at] = (uint8_t)bits[1];
+    }
+  };
+  store(j0 + f);
+  if (j0 + f == 0 && nfl == n) store(n);
+}
+
 // ---------------------------------------------------------------------------
 // March sweep (axis 1 or 2).  blockDim = (64, LINES): x = lane, y = line.
 // Each lane keeps the K cell states of its current face in an LDS ring
@@ -728,6 +798,13 @@ struct SweepLaunch {
   hipStream_t stream;
 };
 
+// Wavefronts up to which the faces run with one per field (four per SIMD).  us,
+// one per field and all fields in one, at six (eight) points: 128x128, 1024
+// wavefronts, 9.6 and 12.3 (8.6 and 14.7); 256x256, 4096, 11.7 and 11.7 (13.0 and
+// 15.3); 36x31x37, 3600, 11.8 and 17.3 (17.0 and 23.2); 40x40x40, 5000, 15.9 and
+// 16.7 (24.4 and 22.9); 50x50x50, 12250, 30 and 23 (46 and 31).
+constexpr long kFieldsFaces = 4096;
+
 template <int NF, int K, int LIM, bool ADAPT, int TX>
 hipError_t launch_faces_tx(const FacesLaunch& a) {
   FacesParams<NF> p;
@@ -741,11 +818,24 @@ hipError_t launch_faces_tx(const FacesLaunch& a) {
   p.bc = a.bc;
   p.fp = a.fp;
   for (int q = 0; q < NF; ++q) p.fld[q] = a.fld[q];
-  constexpr int FJ = 256 / TX;
+  constexpr int FJ = 256 / TX, FJ1 = 64 / TX;
   const int n = a.axis == 0 ? a.nx : (a.axis == 1 ? a.ny : a.nz);
   const long across = a.axis == 0 ? a.ny : a.nx, others = a.axis == 2 ? a.ny : a.nz;
   const int nfl = a.bc == 0 ? n : n + 1;
-  const long blocks = others * ((across + TX - 1) / TX) * ((nfl + FJ - 1) / FJ);
+  const long groups = others * ((across + TX - 1) / TX);
+  const long blocks = groups * ((nfl + FJ - 1) / FJ);
+  if constexpr (NF > 1) {
+    const long blocks1 = groups * ((nfl + FJ1 - 1) / FJ1);
+    if (blocks1 * NF <= kFieldsFaces) {
+      if (a.flags)
+        hipLaunchKernelGGL((k_faces_fields<NF, K, LIM, ADAPT, TX, true>), dim3((unsigned)blocks1), dim3(64, NF), 0,
+                           a.stream, p);
+      else
+        hipLaunchKernelGGL((k_faces_fields<NF, K, LIM, ADAPT, TX, false>), dim3((unsigned)blocks1), dim3(64, NF), 0,
+                           a.stream, p);
+      return hipGetLastError();
+    }
+  }
   if (a.flags)
     hipLaunchKernelGGL((k_faces<NF, K, LIM, ADAPT, TX, true>), dim3((unsigned)blocks), dim3(256), 0, a.stream, p);
   else

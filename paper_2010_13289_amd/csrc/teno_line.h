@@ -21,15 +21,6 @@ namespace tenom {
 // ---------------------------------------------------------------------------
 // One sweep, one wavefront per field
 // ---------------------------------------------------------------------------
-template <int K, int LIM, bool ADAPT, class P>
-__device__ __forceinline__ double field_by_index(int q, P& prov, const RoeFrame<3>& fr, const TenoParams& tp) {
-  switch (q) {
-    case 0: return euler_field<3, K, LIM, ADAPT, 0>(prov, fr, tp);
-    case 1: return euler_field<3, K, LIM, ADAPT, 1>(prov, fr, tp);
-    default: return euler_field<3, K, LIM, ADAPT, 2>(prov, fr, tp);
-  }
-}
-
 // Bound by latency: a load, the cell physics, one field's two reconstructions,
 // the exchange of the fields' values, a store.  4096 cells at eight points
 // (TVD): 7.4 us a sweep, 10.6 by the row sweep.  Wave q also closes component q
@@ -56,8 +47,9 @@ __global__ __launch_bounds__(192) void k_sweep_fields(SweepParams<3> p) {
   __syncthreads();
   StagedCells<NF, K, 1, true> prov{stage, NC, min(t, nface - 1)};
   RoeFrame<NF> fr;
+  uint32_t bits[2] = {0u, 0u};
   roe_frame<NF>(prov, p.fp.gamma, fr);
-  fcs[q * FW + t] = field_by_index<K, LIM, ADAPT>(q, prov, fr, p.fp.tp);
+  fcs[q * FW + t] = field_by_index<NF, K, LIM, false, ADAPT>(q, prov, fr, p.fp.tp, bits);
   __syncthreads();
   double fc[NF], Fh[NF];
 #pragma unroll
@@ -110,8 +102,9 @@ __global__ __launch_bounds__(192) void k_batch_fields(BatchParams<3> p) {
   __syncthreads();
   StagedCells<NF, K, 1, true> prov{stage, NC, min(t, nface - 1)};
   RoeFrame<NF> fr;
+  uint32_t bits[2] = {0u, 0u};
   roe_frame<NF>(prov, p.fp.gamma, fr);
-  fcs[q * FW + t] = field_by_index<K, LIM, ADAPT>(q, prov, fr, p.fp.tp);
+  fcs[q * FW + t] = field_by_index<NF, K, LIM, false, ADAPT>(q, prov, fr, p.fp.tp, bits);
   __syncthreads();
   double fc[NF], Fh[NF];
 #pragma unroll
@@ -214,8 +207,9 @@ __global__ __launch_bounds__(3 * kLineEuler) void k_step_line_euler(LineStep p) 
     __syncthreads();
     StagedCells<NF, K, 1, true> prov{stage, NC, min(t, nface - 1)};
     RoeFrame<NF> fr;
+    uint32_t bits[2] = {0u, 0u};
     roe_frame<NF>(prov, gamma, fr);
-    fcs[q * W + t] = field_by_index<K, LIM, ADAPT>(q, prov, fr, p.fp.tp);
+    fcs[q * W + t] = field_by_index<NF, K, LIM, false, ADAPT>(q, prov, fr, p.fp.tp, bits);
     __syncthreads();
     double fc[NF], Fh[NF];
 #pragma unroll
@@ -269,7 +263,7 @@ __global__ __launch_bounds__(kLineScalar) void k_step_line_scalar(LineStep p) {
     if (t < n) sU[t] = us;
     __syncthreads();
     double F;
-    uint32_t bits[2];
+    uint32_t bits[2] = {0u, 0u};
     LineCells<K> prov{sU, L, min(t, nface - 1)};
     scalar_face<K, LIM, false, ADAPT>(prov, p.fp.adv, p.fp.tp, F, bits);
     Fs[t] = F;

@@ -242,3 +242,55 @@ def test_line_steps_in_a_captured_graph(T, n, system):
             T.rk3_step_cfl(Ue, *args, workspace=wse)
         torch.cuda.synchronize()
         assert np.array_equal(to_host(Ug), to_host(Ue)), f"replay {replay}"
+
+
+# Face fluxes of grids small enough for one wavefront per field (NF wavefronts of
+# 64 faces, at most 4096 in all: 8 lines by 8 faces; 64 of a single line) against
+# the same cells repeated along another axis until the grid takes the other face
+# kernel; in 1D against the row sweep's divergence.  z, y, x order; the repeated
+# axis is the first that is not the face's.
+SMALL_FACES = [((m, 8), [b, 1 - b], K) for m in (8, 9, 15, 17) for b in (0, 1) for K in (6, 8, 8 | 0x100)]
+SMALL_FACES += [((9, 23, 8), [0, 1, 0], 6), ((8, 9, 17), [1, 0, 1], 8), ((12, 8, 9), [0, 0, 0], 8 | 0x100)]
+
+
+@pytest.mark.parametrize("lim", [1, 2])
+@pytest.mark.parametrize("shape,bc,K", SMALL_FACES, ids=[f"{'x'.join(map(str, s))}-{''.join(map(str, b))}-{k}"
+                                                         for s, b, k in SMALL_FACES])
+def test_small_faces_agree_with_repeated_cells(T, shape, bc, K, lim):
+    C_T = 0.0 if K & 0x100 else (1e-5 if K == 6 else 1e-7)
+    nd = len(shape)
+    U = W.random_euler_state(shape, seed=sum(shape) + K, kind="mixed")
+    print(f"[small faces] {shape} {bc} {K}", flush=True)
+    for axis in range(nd):
+        along = nd - 1 - axis  # the face's axis among z, y, x
+        other = next(a for a in range(nd) if a != along)
+        copies = 1 + (4096 * 64) // int(np.prod(shape))
+        big = list(shape)
+        big[other] *= copies
+        out = []
+        for s, V in ((shape, U), (tuple(big), np.concatenate([U] * copies, axis=1 + other))):
+            grid = dict(ndim=nd, n=list(reversed(s)), dx=[0.05, 0.07, 0.06][:nd], bc=bc, system=1)
+            for flags in (False, True):
+                r = T.reconstruct_faces(to_dev(V), grid, K, lim, C_T, GAMMA, axis, return_flags=flags)
+                out.append([to_host(x) for x in r] if flags else [to_host(r)])
+        assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[2][0], out[3][0])
+        for k, small, large in ((0, out[1][0], out[3][0]), (1, out[1][1], out[3][1])):
+            ax = small.ndim - nd + other
+            for piece in np.split(large, copies, axis=ax):
+                assert np.array_equal(piece, small), (axis, "flux" if k == 0 else "flags")
+
+
+@pytest.mark.parametrize("n", [8, 63, 64, 65, 128, 87360, 87424])
+@pytest.mark.parametrize("bc", [0, 1])
+def test_line_faces_agree_with_the_row_sweep(T, n, bc):
+    grid, U = line_case(n, bc, 1, seed=n)
+    print(f"[line faces] {n} {bc}", flush=True)
+    for K, lim in ((6, 1), (8, 3)):
+        F = T.reconstruct_faces(to_dev(U), grid, K, lim, 1e-5, GAMMA, 0)
+        F = to_host(F[0] if isinstance(F, tuple) else F)
+        T.set_sweep_kernel(T.SWEEP_MARCH)
+        try:
+            D = to_host(T.flux_divergence(to_dev(U), grid, K, lim, 1e-5, GAMMA))
+        finally:
+            T.set_sweep_kernel(T.SWEEP_AUTO)
+        assert np.array_equal((F[:, :-1] - F[:, 1:]) * (1.0 / grid["dx"][0]), D)
