@@ -319,8 +319,8 @@ int tenom_batch_tile_shape(int tile, int* threads, int* faces_per_thread);
  * bc: TENOM_BC_PERIODIC or TENOM_BC_TRANSMISSIVE for every problem.
  * Allocates the plan's device memory (about 48 * total bytes plus small
  * tables); clocks start at 0; the tile is 3 until set or autotuned,
- * and until then calls on at most 1536 segments of 63 cells run one wavefront
- * per field instead of a tile (the same bits).
+ * and until then each call runs the kernel that suits its number of segments
+ * (one wavefront per field, tile 0 or tile 2; the same bits).
  * Errors: EINVAL for bad arguments (no allocation), EHIP if an allocation
  * fails.
  */

@@ -77,13 +77,20 @@ using RowFn = hipError_t (*)(int, int, int, const BatchLaunch&);
 const RowFn kRow[kNumTiles] = {tenom_batch_row_tile0, tenom_batch_row_tile1, tenom_batch_row_tile2,
                                tenom_batch_row_tile3, tenom_batch_row_tile4, tenom_batch_row_tile5};
 
-// Segments of 63 cells up to which a batch whose tile nobody chose runs with one
-// wavefront per field.  us a graph step, that and tile 3, Riemann problems at
-// eight points (MP; rough data in brackets): 172 segments 24.0 and 36.5 (24.4
-// and 36.8), 598 29.5 and 36.9 (33.2 and 37.6), 1300 37.3 and 46.3 (45.5 and
-// 50.4), 2530 53.0 and 50.2 (67.0 and 66.0), 5100 83 and 64 (115 and 110); six
-// points cross between the same counts.
+// The kernel of a batch whose tile nobody chose, by its number of segments of 63
+// cells.  Up to kFieldsSegments one wavefront per field: us a graph step, that
+// and tile 3, Riemann problems at eight points (MP; rough data in brackets):
+// 172 segments 24.0 and 36.5 (24.4 and 36.8), 598 29.5 and 36.9 (33.2 and 37.6),
+// 1300 37.3 and 46.3 (45.5 and 50.4), 2530 53.0 and 50.2 (67.0 and 66.0), 5100 83
+// and 64 (115 and 110); six points cross between the same counts.  Up to
+// kSmallTileSegments tile 0, whose small segments leave the constant states to
+// themselves and fill the last round: 24,990 segments 128.6 us, tile 2 145.3,
+// tile 3 170.5 (367, 416, 375).  Above, the pass is bound by HBM where the states
+// are constant, and tile 2 has twice the loads in flight per wavefront: 189,559
+// segments 613 us, tile 0 713, tile 3 768 (rough everywhere 2792, 2622, 2587; a
+// caller with such data asks for tile 3 or the autotuner).
 constexpr int kFieldsSegments = 1536;
+constexpr int kSmallTileSegments = 65536;
 
 // Segments of one tile: (problem, first cell).  A segment covers FACES - 1
 // cells; a periodic problem of at most FACES cells is one wrapped segment
@@ -167,10 +174,10 @@ int check_call(const tenom_batch_plan* P, int scheme, int limiter, double C_T, d
 int enqueue(tenom_batch_plan* P, const Method& m, double cfl, int steps, int first, int cnt, double* U,
             hipStream_t s) {
   if (cnt <= 0 || steps <= 0) return TENOM_OK;
-  // few segments leave the chip part empty: one wavefront per field, unless a
-  // tile was asked for
-  const bool fields = !P->tile_set && P->tiling[0].first[first + cnt] - P->tiling[0].first[first] <= kFieldsSegments;
-  const auto& T = P->tiling[fields ? 0 : P->tile];
+  const int seg63 = P->tiling[0].first[first + cnt] - P->tiling[0].first[first];
+  const bool fields = !P->tile_set && seg63 <= kFieldsSegments;
+  const int tile = P->tile_set ? P->tile : (seg63 <= kSmallTileSegments ? 0 : 2);
+  const auto& T = P->tiling[tile];
   const int sb = T.first[first], se = T.first[first + cnt];
   BatchLaunch L;
   L.off = P->off_d;
@@ -207,7 +214,7 @@ int enqueue(tenom_batch_plan* P, const Method& m, double cfl, int steps, int fir
         if (fields)
           e = (m.K == 6 ? tenom_batch_fields_nf3_k6 : tenom_batch_fields_nf3_k8)(m.kind, m.adapt ? 1 : 0, L);
         else
-          e = kRow[P->tile](m.K, m.kind, m.adapt ? 1 : 0, L);
+          e = kRow[tile](m.K, m.kind, m.adapt ? 1 : 0, L);
       }
       if (e != hipSuccess) return hip_fail(e, "batched sweep launch");
     }
