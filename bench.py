@@ -75,11 +75,11 @@ BYTES_PER_CELL_STEP = O.rk3_bytes_per_cell(5)
 # by 2.0 and WRITE_SIZE by 1.0, the factors a plain 1 GiB device copy reads
 # as).  They describe the kernels built from the sources whose digest is
 # TRAFFIC_SOURCE_DIGEST and are reported as null for any other build.
-TRAFFIC_SOURCE_DIGEST = "1af54b998de4687b11c56218fb72441ef32ccbc249d679660a48fd7e8136fe72"
-MEASURED_TRAFFIC = {"sweep_x": 1.4719e+09, "sweep_y": 2.0330e+09, "sweep_z": 2.5889e+09}
+TRAFFIC_SOURCE_DIGEST = "f1ad81795e2bae43e32b2d8bd0cd5ce94b071b5a0e37fbbadc665001cc3664a1"
+MEASURED_TRAFFIC = {"sweep_x": 1.4676e+09, "sweep_y": 2.0386e+09, "sweep_z": 2.6432e+09}
 # batched sweep, 4096 problems, averaged over the stages, per tile shape
 # (64x1, 128x1, 128x2, 256x1, 256x2, 512x1): smaller tiles re-read more halo
-MEASURED_TRAFFIC_BATCH = (1.2754e9, 1.1488e9, 1.0866e9, 1.0863e9, 1.0554e9, 1.0551e9)
+MEASURED_TRAFFIC_BATCH = (1.2804e9, 1.1552e9, 1.1387e9, 1.0948e9, 1.1285e9, 1.0553e9)
 TRAFFIC_NOTE = ("recorded, not measured in this run: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE of this benchmark "
                 "on the kernel sources whose digest is TRAFFIC_SOURCE_DIGEST (null for any other build); "
                 "see the profiles directory")
@@ -408,7 +408,7 @@ def run_batched(args):
     dt_n, dt_ms = prof["batch_dt"]
     avg_s = sweep_ms / 1e3 / max(sweep_n, 1)
     flops_launch = O.face_vector_ops("euler", 1, 8, O.LIM_MP, rough=rough, nonsmooth=nonsm) * faces_per_stage
-    achieved = flops_launch / avg_s / 1e12
+    alg_bytes = 64.0 * plan.total
     sec_per_step = graph_ms / 1e3 / steps
     # one launch per problem: the same kernels with first = p, count = 1
     pp = args.per_problem_steps
@@ -460,12 +460,16 @@ def run_batched(args):
             "autotune_ms_per_step": tile_ms,
         },
         "roofline": {
-            "bound": "alu",
+            # segments of one constant state skip the faces' arithmetic, so the
+            # bound is the state's traffic: 24 B per cell read and written, and
+            # U^n read in two stages of three
+            "bound": "hbm",
             "kernel": "batch_sweep",
-            "achieved": achieved,
-            "peak": PEAK_FP64_TFLOPS,
-            "unit": "TFLOP/s",
-            "frac": achieved / PEAK_FP64_TFLOPS,
+            "achieved": alg_bytes / avg_s / 1e9,
+            "peak": PEAK_HBM_GBS,
+            "unit": "GB/s",
+            "frac": alg_bytes / avg_s / 1e9 / PEAK_HBM_GBS,
+            "alg_bytes_per_launch": alg_bytes,
             "traffic": (MEASURED_TRAFFIC_BATCH[best] if kernel_source_digest() == TRAFFIC_SOURCE_DIGEST
                         else None),
             "traffic_source": TRAFFIC_NOTE,
