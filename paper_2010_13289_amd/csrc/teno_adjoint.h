@@ -1103,9 +1103,15 @@ struct VjpOut {
 
 // Occupancy the tile kernel is compiled for: 3 wavefronts per SIMD (at most
 // 168 VGPRs; three 4-wavefront blocks of 46 KB LDS per CU), measured 20%
-// faster than 2 without spills.
+// faster than 2 although four fields then spill 20 to 36 bytes; the 5-field
+// tile (65 KB LDS, two blocks per CU) cannot reach 3 and keeps 256 VGPRs.
+template <int NF>
+struct VjpOccupancy {
+  static constexpr int WAVES = NF >= 5 ? 2 : 3;
+};
+
 template <int NF, int K, int LIM, bool ADAPT>
-__global__ __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(3))) void k_vjp_tile(const double* __restrict__ U,
+__global__ __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(VjpOccupancy<NF>::WAVES))) void k_vjp_tile(const double* __restrict__ U,
                                                        const double* __restrict__ Lbar, VjpOut vo,
                                                        VjpAxis ax, VjpTiles tl, int fld0, int fld1, int fld2,
                                                        int fld3, int fld4, FaceParams fp) {
@@ -1744,22 +1750,28 @@ hipError_t launch_vjp(const VjpLaunch& a) {
     const long ntile = (a.ax.n + tl.own - 1) / tl.own;
     // One wavefront per tile does far less work, but takes its rough fields one
     // after the other: it wins once the tiles fill the chip (the fields of a
-    // tile otherwise run side by side in their own wavefronts).  Measured per
-    // axis, us (a wavefront per field, per tile): six points 256^2 (1,280
-    // tiles) 28, 42; 512^2 (4,608) 82, 84; 768^2 (10,752) 174, 144; 1024^2 277,
-    // 198; eight points 256^2 48, 54; 1024^2 498, 249.  In 3D always: 32^3 50,
-    // 38; 72x64x56 319, 141.
-    if (NF == 5 || tl.nlines * ntile >= (K == 6 ? 5120 : 2048)) {
+    // tile otherwise run side by side in their own wavefronts).  The line lies
+    // where the two cross on the state a rollout reaches (60 steps of a density
+    // wave, half of its fields rough by rounding noise).  Both axes or all three,
+    // us, a wavefront per field and a wavefront per tile, on that state (and on a
+    // smooth one; rough in every cell), six points: 384^2 (2,688 tiles an axis)
+    // 92, 98 (86, 39; 94, 118); 768^2 (10,752) 316, 312 (294, 99; 325, 385);
+    // 1024^2 531, 499 (492, 154; 545, 620); eight points 384^2 153, 138 (150, 44;
+    // 163, 169); 1024^2 879, 686 (864, 188; 952, 843).  3D, six points: 16^3 (256
+    // tiles) 38, 89 (36, 52; 38, 104); 20^3 (400) 72, 91 (68, 48; 72, 107); 24^3
+    // (576) 105, 94 (99, 51; 105, 111); 32^3 139, 97 (132, 53; 140, 113).  1D,
+    // eight points: 200,000 cells (3,509) 50, 51 (46, 18; 52, 67); 310,000 (5,439)
+    // 74, 75 (68, 26; 77, 97); 1,000,000 220, 211 (201, 70; 229, 272).
+    if (tl.nlines * ntile >= (NF == 5 ? 512 : (NF == 4 && K == 8 ? 2048 : 5120))) {
       if (a.ax.bc == 0 && a.ax.n <= FW) tl.own = a.ax.n;
       const long tiles = tl.nlines * ((a.ax.n + tl.own - 1) / tl.own);
       hipLaunchKernelGGL((k_vjp_wave<NF, K, LIM, ADAPT>), dim3((unsigned)tiles), dim3(FW), 0, a.stream, a.U, a.Lbar,
                          a.out, a.ax, tl, a.fld[0], a.fld[1], a.fld[2], a.fld[3], a.fld[4], a.fp);
-      return hipGetLastError();
-    }
-    if constexpr (NF < 5)
+    } else {
       hipLaunchKernelGGL((k_vjp_tile<NF, K, LIM, ADAPT>), dim3((unsigned)(tl.nlines * ntile)), dim3(FW, NF), 0,
                          a.stream, a.U, a.Lbar, a.out, a.ax, tl, a.fld[0], a.fld[1], a.fld[2], a.fld[3], a.fld[4],
                          a.fp);
+    }
   }
   return hipGetLastError();
 }

@@ -97,9 +97,9 @@ def test_vjp_on_smooth_data_matches_reference(T, orc, K, lim, C_T):
     assert_close_fields(got, ref, exclude=excl, what=f"smooth 2D VJP K={K} lim={lim}")
 
 
-# one wavefront per tile: 3D lines that wrap in one tile (up to 64 cells,
-# periodic), fill it (59 cells at six points, 57 at eight), and leave one cell
-# for a second or third; 2D grids with enough tiles along one axis
+# small 3D grids whose lines fill one tile (59 cells at six points, 57 at eight),
+# just miss it, and leave one cell for a second or third; 2D grids with enough
+# tiles along one axis for one wavefront per tile
 WAVE_CASES = [((64, 8, 8), [0, 0, 0], 6, 1), ((8, 65, 8), [0, 0, 1], 6, 1), ((8, 8, 63), [0, 1, 1], 6, 3),
               ((59, 6, 8), [1, 0, 1], 6, 2), ((60, 6, 8), [0, 0, 1], 6, 0), ((8, 119, 6), [0, 1, 0], 6, 4),
               ((64, 8, 8), [1, 1, 0], 8, 1), ((8, 58, 8), [0, 0, 0], 8 | 0x100, 1), ((8, 8, 58), [1, 0, 0], 8, 3),
@@ -128,6 +128,27 @@ def test_wave_tiles_match_reference(T, orc, shape, bc, K, lim, kind):
     excl = band_cells(orc, U, grid, K, lim, C_T, K & 0xFF)
     assert excl.sum() <= excl.size // 10
     assert_close_fields(got, ref, exclude=excl, what="wave VJP")
+
+
+# 3D axes of at least 512 tiles run with one wavefront per tile, below that with
+# one per field: lines that wrap in one tile, fill it, and leave one cell for a
+# second or third, each with 512 lines or a few more across; 511 and 512 tiles
+# along z and x; and 1D lines on both sides of 5120 tiles (of 59 cells at six
+# points, 57 at eight).
+TILE_COUNTS = [((64, 16, 32), [0, 0, 1], 6, 1), ((32, 65, 16), [0, 0, 1], 6, 1), ((16, 32, 63), [0, 1, 1], 6, 3),
+               ((59, 24, 22), [1, 0, 1], 6, 2), ((22, 119, 24), [0, 1, 0], 6, 4), ((24, 22, 58), [1, 0, 0], 8, 3),
+               ((32, 58, 16), [0, 0, 0], 8 | 0x100, 1), ((8, 7, 73), [0, 1, 0], 6, 1), ((8, 8, 64), [0, 1, 0], 6, 1),
+               ((9, 64, 8), [1, 0, 1], 8, 1),
+               ((5119 * 59,), [1], 6, 1), ((5119 * 59 + 1,), [0], 6, 3), ((5119 * 57,), [0], 8, 1),
+               ((5119 * 57 + 1,), [1], 8, 2), ((5120 * 57,), [0], 8 | 0x100, 1)]
+
+
+@pytest.mark.parametrize("kind", ["mixed", "smooth"])
+@pytest.mark.parametrize("shape,bc,K,lim", TILE_COUNTS,
+                         ids=[f"{'x'.join(map(str, c[0]))}-{''.join(map(str, c[1]))}-{c[2]}-{c[3]}" for c in TILE_COUNTS])
+def test_vjp_on_both_sides_of_the_tile_count(T, orc, shape, bc, K, lim, kind):
+    test_wave_tiles_match_reference(T, orc, shape, bc, K, lim, kind)
+
 
 
 def test_vjp_scale_accumulate_and_determinism(T):
