@@ -32,7 +32,10 @@
 // from their LDS copy of the cell instead of reading HBM again.
 #pragma once
 
+#include <type_traits>
+
 #include "teno_device.h"
+#include "teno_split.h"
 
 namespace tenom {
 
@@ -110,7 +113,8 @@ struct RowStage {
 };
 
 // CS: staging-index step between consecutive cells of the sweep axis (1 in
-// the row sweep, the tile width in the tile sweep).  REREAD: the Euler face
+// the row sweep, the tile width in the tile sweep; 0: known at run time, cs).
+// REREAD: the Euler face
 // projects its stencil group by group of fields from fresh reads of the
 // cells and lets wavefronts whose candidates are all smooth skip the limiter
 // (worth it where most wavefronts see only smooth data: the tile sweep's
@@ -124,16 +128,18 @@ struct StagedCells {
   const double* s;  // LDS: [NE][NC]
   int nc;           // row pitch of the staging array
   int c0;           // staging index of window cell 0
+  int cs = CS;      // run-time step where CS is 0
+  __device__ __forceinline__ int step() const { return CS ? CS : cs; }
   __device__ __forceinline__ double at(int e, int c) const { return s[e * nc + c]; }
   // the same provider, its position hidden from the compiler, so that reads
   // through it are not merged with earlier reads of the same cells
   __device__ __forceinline__ StagedCells fresh() const {
     int c = c0;
     asm volatile("" : "+v"(c));
-    return StagedCells<NF, K, CS, REREAD>{s, nc, c};
+    return StagedCells<NF, K, CS, REREAD>{s, nc, c, cs};
   }
   __device__ __forceinline__ void state_flux(int m, double (&X)[NF], double (&F)[NF]) const {
-    const int c = c0 + m * CS;
+    const int c = c0 + m * step();
 #pragma unroll
     for (int q = 0; q < NF; ++q) {
       X[q] = at(q, c);
@@ -153,9 +159,9 @@ struct StagedCells {
     }
     return __builtin_amdgcn_ballot_w64(differ) == 0 && __popcll(__builtin_amdgcn_ballot_w64(true)) >= K - 2;
   }
-  __device__ __forceinline__ double speed(int m) const { return at(2 * NF, c0 + m * CS); }
+  __device__ __forceinline__ double speed(int m) const { return at(2 * NF, c0 + m * step()); }
   __device__ __forceinline__ void cell(int m, double (&X)[NF], double (&F)[NF], double& lam) const {
-    const int c = c0 + m * CS;
+    const int c = c0 + m * step();
 #pragma unroll
     for (int q = 0; q < NF; ++q) {
       X[q] = at(q, c);
@@ -164,13 +170,13 @@ struct StagedCells {
     lam = at(2 * NF, c);
   }
   __device__ __forceinline__ void roe(int sd, RoeIn<NF>& r) const {
-    const int c = c0 + (K / 2 - 1 + sd) * CS;
+    const int c = c0 + (K / 2 - 1 + sd) * step();
     r.rs = at(2 * NF + 1, c);
 #pragma unroll
     for (int d = 0; d < NF - 2; ++d) r.u[d] = at(2 * NF + 2 + d, c);
     r.H = at(3 * NF, c);
   }
-  __device__ __forceinline__ double value(int m) const { return at(0, c0 + m * CS); }
+  __device__ __forceinline__ double value(int m) const { return at(0, c0 + m * step()); }
 };
 
 // Stage a cell of state X at staging index c: its state and, for the Euler
@@ -203,11 +209,6 @@ __device__ __forceinline__ void stage_cell(double* stage, int nc, int c, const d
   for (int q = 0; q < NF; ++q) X[q] = U[fld[q] * N + cell];
   stage_put<NF>(stage, nc, c, X, gamma);
 }
-
-// Waves per SIMD the face, row and tile kernels are compiled for: at most 168
-// VGPRs, which the face fits (the adaptive eight-point MP face spills 12
-// bytes), and three tiles fit in a CU's LDS.
-constexpr int kFaceWaves = 3;
 
 template <int NF, int K, int LIM, bool ADAPT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFaceWaves)))
@@ -283,8 +284,6 @@ void k_sweep_row(SweepParams<NF> p) {
 // far less often than a strip of 64 faces along one line: most wavefronts
 // then skip the limiter (StagedCells with REREAD).
 // ---------------------------------------------------------------------------
-constexpr int kTileColumns = 8;  // columns (lines side by side) per tile-sweep workgroup
-
 // Whole-line workgroups of a tile sweep along `axis`: the lines of the other
 // axis times the column groups (x columns for y and z, y rows for x).
 inline long tile_count(int axis, int nx, int ny, int nz) {
@@ -466,12 +465,14 @@ void k_sweep_tile(SweepParams<NF> p, int axis) {
 
 // ---------------------------------------------------------------------------
 // Face fluxes of one axis (and, with FLAGS, the smoothness bytes).  A
-// 256-thread workgroup takes 256 / TX faces of TX adjacent lines, staged as one
-// chunk of the tile sweep: the cell physics once per cell instead of K times,
-// and wavefronts whose faces are all smooth skip cutoff and limiter.  Bound by
-// VALU issue like the sweeps.  TX = 1 serves single lines (1D).  64^3 Euler
-// with flags at eight points: 50 us from global memory, one thread per face,
-// 25 staged.
+// 256-thread workgroup takes fj faces of tx lines (face_split), staged as one
+// chunk of the tile sweep is: the cell physics once per cell instead of K times,
+// and wavefronts whose faces are all smooth skip cutoff and limiter.  Thread t
+// takes face t / tx of line t % tx and its window cell m sits at t + m tx: the
+// stores of a strided axis join, and no two lanes meet in an LDS bank.  Bound by
+// VALU issue like the sweeps.  1D (NF = 3) is one line, a step of one cell.
+// 64^3 Euler with flags at eight points: 50 us from global memory, one thread per
+// face, 25 staged.
 // ---------------------------------------------------------------------------
 template <int NF>
 struct FacesParams {
@@ -479,59 +480,111 @@ struct FacesParams {
   double* Fhat;
   uint8_t* flags;
   int axis, nx, ny, nz, bc;
+  int fj, tx;
+  int width;  // lines of a row of workgroups (those of a plane, or all)
+  int ncg;    // workgroups side by side in a row
+  int nch;    // workgroups along a line
   int fld[NF];
   FaceParams fp;
 };
 
-template <int NF, int K, int LIM, bool ADAPT, int TX, bool FLAGS>
+// Row, lines [l0, end) and chunk of workgroup b: side by side along a row, then its
+// chunks, then the rows, so that workgroups that share cache lines and halo rows
+// run close together (128^3 along y 100 us with the chunks first, 90 so).
+template <int NF>
+__device__ __forceinline__ void faces_block(const FacesParams<NF>& p, int b, int tx, int& row, int& l0, int& end,
+                                            int& chunk) {
+  row = b / (p.ncg * p.nch);
+  const int r = b - row * (p.ncg * p.nch);
+  chunk = r / p.ncg;
+  l0 = row * p.width + (r - chunk * p.ncg) * tx;
+  end = (row + 1) * p.width;
+}
+
+// Line l of the faces' axis, in row `row`, and the index of its face 0 with the
+// step along the axis.
+template <int NF>
+__device__ __forceinline__ Line faces_line(const FacesParams<NF>& p, int row, int l, long& face, long& fstride) {
+  const int n = p.axis == 0 ? p.nx : (p.axis == 1 ? p.ny : p.nz);
+  if (p.axis == 0) {
+    face = (long)l * (p.nx + 1);
+    fstride = 1;
+    return Line{(long)l * p.nx, 1, n, p.bc};
+  }
+  const long plane = (long)p.nx * p.ny;
+  if (p.axis == 2) {
+    face = l;
+    fstride = plane;
+    return Line{l, plane, n, p.bc};
+  }
+  long z = row;
+  int x = l - row * p.width;
+  if (p.width != p.nx) {  // a row of all lines
+    z = l / p.nx;
+    x = l - (int)z * p.nx;
+  }
+  face = x + (plane + p.nx) * z;
+  fstride = p.nx;
+  return Line{x + plane * z, p.nx, n, p.bc};
+}
+
+// Staged cells of a workgroup of k_faces: three of the largest fit in a CU's LDS.
+template <int NF, int K>
+constexpr int kFacesCells = NF == 3 ? 256 + K - 1 : 416;
+
+// CS: lines side by side, 0 where known at run time
+template <int NF, int K, int LIM, bool ADAPT, bool FLAGS, int CS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFaceWaves)))
 void k_faces(FacesParams<NF> p) {
-  constexpr int FJ = 256 / TX;
-  constexpr int ROWS = FJ + K - 1, NC = ROWS * TX;
+  constexpr int NC = kFacesCells<NF, K>;
   __shared__ double stage[RowStage<NF>::NE * NC];
   const int n = p.axis == 0 ? p.nx : (p.axis == 1 ? p.ny : p.nz);
-  const int across = p.axis == 0 ? p.ny : p.nx;  // the lines side by side
   const int nfl = p.bc == 0 ? n : n + 1;  // a periodic line's face n is its face 0
-  const int ncg = (across + TX - 1) / TX, nch = (nfl + FJ - 1) / FJ;
-  const int b = (int)blockIdx.x;
-  const int o = b / ncg / nch;  // z of an x or y line, y of a z line
-  const int j0 = (b / ncg % nch) * FJ;
-  const int nfk = min(FJ, nfl - j0);
-  const long N = (long)p.nx * p.ny * p.nz;
-  const int t = threadIdx.x, col = t % TX, f = t / TX;
-  const int c = (b % ncg) * TX + col;
-  const int cs = min(c, across - 1);  // lines beyond the grid stage a real line and store nothing
-  Line L;
-  long face, fstride;  // index of the line's face 0, step along the axis
-  if (p.axis == 0) {
-    const long r = cs + (long)p.ny * o;
-    L = Line{r * p.nx, 1, n, p.bc};
-    face = r * (p.nx + 1);
-    fstride = 1;
-  } else if (p.axis == 1) {
-    L = Line{cs + (long)p.nx * p.ny * o, p.nx, n, p.bc};
-    face = cs + (long)p.nx * (p.ny + 1) * o;
-    fstride = p.nx;
-  } else {
-    L = Line{cs + (long)p.nx * o, (long)p.nx * p.ny, n, p.bc};
-    face = cs + (long)p.nx * o;
-    fstride = (long)p.nx * p.ny;
-  }
+  int row, l0, end, chunk;
+  faces_block(p, (int)blockIdx.x, CS ? CS : p.tx, row, l0, end, chunk);
+  const int j0 = chunk * p.fj;
+  const int nfk = min(p.fj, nfl - j0);
+  // This thread's place, formed anew before and after the face (an opaque copy
+  // of the thread index): held across it would be spilled.
+  struct Where {
+    int tx, t, f, col;
+  };
+  auto where = [&]() {
+    Where w;
+    int tt = threadIdx.x;
+    asm volatile("" : "+v"(tt));
+    w.tx = CS ? CS : p.tx;
+    w.t = tt;
+    w.f = tt / w.tx;
+    w.col = tt - w.f * w.tx;
+    return w;
+  };
+  long face, fstride;
   __builtin_amdgcn_s_setprio(3);  // high while loads and stores issue, as in the sweeps
-  for (int r = f; r < nfk + K - 1; r += FJ)
-    stage_cell<NF>(stage, NC, r * TX + col, p.U, p.fld, p.fp.gamma, N, cell_at(L, j0 - K / 2 + r));
+  {
+    const Where w = where();
+    const Line L = faces_line<NF>(p, row, min(l0 + w.col, end - 1), face, fstride);  // beyond the row: its last line
+    const long N = (long)p.nx * p.ny * p.nz;
+    const int frows = 256 / w.tx;
+    if (w.f < frows)
+      for (int r = w.f; r < nfk + K - 1; r += frows)
+        stage_cell<NF>(stage, NC, r * w.tx + w.col, p.U, p.fld, p.fp.gamma, N, cell_at(L, j0 - K / 2 + r));
+  }
   __syncthreads();
   __builtin_amdgcn_s_setprio(0);
-  if (f >= nfk) return;
   double F[NF];
   uint32_t bits[2][NF];
   {
-    StagedCells<NF, K, TX, true> prov{stage, NC, f * TX + col};
+    const Where w = where();
+    if (w.f >= nfk) return;
+    StagedCells<NF, K, CS, true> prov{stage, NC, w.t, w.tx};
     face_flux<NF, K, LIM, ADAPT, FLAGS>(prov, p.fp, F, bits);
   }
-  if (c >= across) return;
   __builtin_amdgcn_s_setprio(3);
-  const long nfaces = N / n * (n + 1);
+  const Where w = where();
+  if (l0 + w.col >= end) return;
+  faces_line<NF>(p, row, l0 + w.col, face, fstride);
+  const long nfaces = (long)p.nx * p.ny * p.nz / n * (n + 1);
   auto store = [&](int j) {
     const long at = face + (long)j * fstride;
 #pragma unroll
@@ -543,40 +596,32 @@ void k_faces(FacesParams<NF> p) {
       }
     }
   };
-  store(j0 + f);
-  if (j0 + f == 0 && nfl == n) store(n);
+  store(j0 + w.f);
+  if (j0 + w.f == 0 && nfl == n) store(n);
 }
 
 // The same for grids that leave the chip part empty, where the time is one
 // workgroup's chain: one wavefront per characteristic field takes 64 faces (64 /
 // TX of TX lines), wave q stores component q.  288 cells at eight points 11.8 ->
 // 7.5 us, 128x128 14.7 -> 8.6, 20x20x20 16.0 -> 9.8.
-template <int NF, int K, int LIM, bool ADAPT, int TX, bool FLAGS>
+template <int NF, int K, int LIM, bool ADAPT, bool FLAGS, int TX>
 __global__ __launch_bounds__(64 * NF) void k_faces_fields(FacesParams<NF> p) {
-  constexpr int FJ = 64 / TX;
-  constexpr int ROWS = FJ + K - 1, NC = ROWS * TX;
+  constexpr int FJ = 64 / TX, NC = (FJ + K - 1) * TX;
   __shared__ double stage[RowStage<NF>::NE * NC];
   __shared__ double fcs[NF * 64];
   const int n = p.axis == 0 ? p.nx : (p.axis == 1 ? p.ny : p.nz);
-  const int across = p.axis == 0 ? p.ny : p.nx;
   const int nfl = p.bc == 0 ? n : n + 1;  // a periodic line's face n is its face 0
-  const int ncg = (across + TX - 1) / TX, nch = (nfl + FJ - 1) / FJ;
-  const int b = (int)blockIdx.x;
-  const int o = b / ncg / nch;  // z of an x or y line, y of a z line
-  const int j0 = (b / ncg % nch) * FJ;
-  const int c0 = (b % ncg) * TX;
-  const int nfk = min(FJ, nfl - j0);
   const long N = (long)p.nx * p.ny * p.nz;
+  int row, l0, end, chunk;
+  faces_block(p, (int)blockIdx.x, TX, row, l0, end, chunk);
+  const int j0 = chunk * FJ;
+  const int nfk = min(FJ, nfl - j0);
   const int t = threadIdx.x, q = threadIdx.y, col = t % TX, f = t / TX;
-  // lines beyond the grid stage a real line and store nothing
-  auto line = [&](int cc) {
-    const int cs = min(c0 + cc, across - 1);
-    if (p.axis == 0) return Line{(cs + (long)p.ny * o) * p.nx, 1, n, p.bc};
-    if (p.axis == 1) return Line{cs + (long)p.nx * p.ny * o, p.nx, n, p.bc};
-    return Line{cs + (long)p.nx * o, (long)p.nx * p.ny, n, p.bc};
-  };
-  for (int c = q * 64 + t; c < (nfk + K - 1) * TX; c += 64 * NF)
-    stage_cell<NF>(stage, NC, c, p.U, p.fld, p.fp.gamma, N, cell_at(line(c % TX), j0 - K / 2 + c / TX));
+  long face, fstride;
+  for (int c = q * 64 + t; c < (nfk + K - 1) * TX; c += 64 * NF) {
+    const Line L = faces_line<NF>(p, row, min(l0 + c % TX, end - 1), face, fstride);
+    stage_cell<NF>(stage, NC, c, p.U, p.fld, p.fp.gamma, N, cell_at(L, j0 - K / 2 + c / TX));
+  }
   __syncthreads();
   StagedCells<NF, K, TX, true> prov{stage, NC, min(f, nfk - 1) * TX + col};
   RoeFrame<NF> fr;
@@ -591,19 +636,8 @@ __global__ __launch_bounds__(64 * NF) void k_faces_fields(FacesParams<NF> p) {
   double F = Fh[0];
 #pragma unroll
   for (int i = 1; i < NF; ++i) F = q == i ? Fh[i] : F;
-  const int c = c0 + col;
-  if (f >= nfk || c >= across) return;
-  long face, fstride;  // index of the line's face 0, step along the axis
-  if (p.axis == 0) {
-    face = (c + (long)p.ny * o) * (p.nx + 1);
-    fstride = 1;
-  } else if (p.axis == 1) {
-    face = c + (long)p.nx * (p.ny + 1) * o;
-    fstride = p.nx;
-  } else {
-    face = c + (long)p.nx * o;
-    fstride = (long)p.nx * p.ny;
-  }
+  if (f >= nfk || l0 + col >= end) return;
+  faces_line<NF>(p, row, l0 + col, face, fstride);
   const long nfaces = N / n * (n + 1);
   auto store = [&](int j) {
     const long at = face + (long)j * fstride;
@@ -805,8 +839,8 @@ struct SweepLaunch {
 // 16.7 (24.4 and 22.9); 50x50x50, 12250, 30 and 23 (46 and 31).
 constexpr long kFieldsFaces = 4096;
 
-template <int NF, int K, int LIM, bool ADAPT, int TX>
-hipError_t launch_faces_tx(const FacesLaunch& a) {
+template <int NF, int K, int LIM, bool ADAPT>
+hipError_t launch_faces(const FacesLaunch& a) {
   FacesParams<NF> p;
   p.U = a.U;
   p.Fhat = a.Fhat;
@@ -818,38 +852,53 @@ hipError_t launch_faces_tx(const FacesLaunch& a) {
   p.bc = a.bc;
   p.fp = a.fp;
   for (int q = 0; q < NF; ++q) p.fld[q] = a.fld[q];
-  constexpr int FJ = 256 / TX, FJ1 = 64 / TX;
   const int n = a.axis == 0 ? a.nx : (a.axis == 1 ? a.ny : a.nz);
-  const long across = a.axis == 0 ? a.ny : a.nx, others = a.axis == 2 ? a.ny : a.nz;
   const int nfl = a.bc == 0 ? n : n + 1;
-  const long groups = others * ((across + TX - 1) / TX);
-  const long blocks = groups * ((nfl + FJ - 1) / FJ);
+  const long nlines = (long)a.nx * a.ny * a.nz / n;
+  if (NF == 3 && nlines != 1) return hipErrorInvalidValue;
+  const int across = a.axis == 0 ? a.ny : a.nx;
+  auto take = [&](int width, int fj, int tx) {  // workgroups of fj faces of tx lines of a row
+    p.width = width;
+    p.fj = fj;
+    p.tx = tx;
+    p.ncg = (width + tx - 1) / tx;
+    p.nch = (nfl + fj - 1) / fj;
+    return nlines / width * p.ncg * p.nch;
+  };
   if constexpr (NF > 1) {
-    const long blocks1 = groups * ((nfl + FJ1 - 1) / FJ1);
-    if (blocks1 * NF <= kFieldsFaces) {
+    constexpr int TX = NF == 3 ? 1 : kTileColumns;
+    // rows of all lines where a plane's leave more than 8 % of the columns empty
+    const long rows = nlines / across * ((across + TX - 1) / TX) * TX;
+    const long blocks = take(rows > 1.08 * nlines ? (int)nlines : across, 64 / TX, TX);
+    if (blocks * NF <= kFieldsFaces) {
+      const dim3 gr((unsigned)blocks), bl(64, NF);
       if (a.flags)
-        hipLaunchKernelGGL((k_faces_fields<NF, K, LIM, ADAPT, TX, true>), dim3((unsigned)blocks1), dim3(64, NF), 0,
-                           a.stream, p);
+        hipLaunchKernelGGL((k_faces_fields<NF, K, LIM, ADAPT, true, TX>), gr, bl, 0, a.stream, p);
       else
-        hipLaunchKernelGGL((k_faces_fields<NF, K, LIM, ADAPT, TX, false>), dim3((unsigned)blocks1), dim3(64, NF), 0,
-                           a.stream, p);
+        hipLaunchKernelGGL((k_faces_fields<NF, K, LIM, ADAPT, false, TX>), gr, bl, 0, a.stream, p);
       return hipGetLastError();
     }
   }
-  if (a.flags)
-    hipLaunchKernelGGL((k_faces<NF, K, LIM, ADAPT, TX, true>), dim3((unsigned)blocks), dim3(256), 0, a.stream, p);
-  else
-    hipLaunchKernelGGL((k_faces<NF, K, LIM, ADAPT, TX, false>), dim3((unsigned)blocks), dim3(256), 0, a.stream, p);
+  const FaceSplit sp = face_split(nfl, across, nlines, K, kFacesCells<NF, K>);
+  const long blocks = take(sp.width, sp.fj, sp.tx);
+  if (blocks >= 1l << 24) return hipErrorInvalidValue;  // 2^32 threads; the split keeps 2^31 cells below
+  const dim3 gr((unsigned)blocks);
+  auto go = [&](auto cs) {
+    constexpr int CS = decltype(cs)::value;
+    if (a.flags)
+      hipLaunchKernelGGL((k_faces<NF, K, LIM, ADAPT, true, CS>), gr, dim3(256), 0, a.stream, p);
+    else
+      hipLaunchKernelGGL((k_faces<NF, K, LIM, ADAPT, false, CS>), gr, dim3(256), 0, a.stream, p);
+  };
+  if constexpr (NF == 3) {
+    go(std::integral_constant<int, 1>());
+  } else {
+    if (p.tx == kTileColumns)
+      go(std::integral_constant<int, kTileColumns>());
+    else
+      go(std::integral_constant<int, 0>());
+  }
   return hipGetLastError();
-}
-
-template <int NF, int K, int LIM, bool ADAPT>
-hipError_t launch_faces(const FacesLaunch& a) {
-  // single lines fill a workgroup with 256 faces of one line
-  if constexpr (NF == 3) return launch_faces_tx<NF, K, LIM, ADAPT, 1>(a);
-  if constexpr (NF == 1)
-    if (a.ny == 1 && a.nz == 1) return launch_faces_tx<NF, K, LIM, ADAPT, 1>(a);
-  if constexpr (NF != 3) return launch_faces_tx<NF, K, LIM, ADAPT, kTileColumns>(a);
 }
 
 // what every sweep kernel takes over from the launch

@@ -1,0 +1,66 @@
+// How the tile kernels split a grid into workgroups: plain host arithmetic.
+#pragma once
+
+#include <initializer_list>
+
+namespace tenom {
+
+// Waves per SIMD the face, row and tile kernels are compiled for: at most 168
+// VGPRs, and three tiles fit in a CU's LDS.
+constexpr int kFaceWaves = 3;
+
+// Workgroups of 256 threads the chip holds at kFaceWaves (256 CUs, one
+// wavefront of a workgroup per SIMD).
+constexpr double kFaceSlots = 256.0 * kFaceWaves;
+
+// Lines side by side in a workgroup's tile, as a rule: a wavefront then holds 8 x
+// 8 faces, which lie whole in smooth regions more often than strips.
+constexpr int kTileColumns = 8;
+
+// Split of the face kernel: a workgroup of 256 threads takes fj faces of tx lines;
+// its lines are side by side in rows of `width` lines.
+struct FaceSplit {
+  int width, fj, tx;
+};
+
+// Estimated time of a split, in rounds of full workgroups: a workgroup whose
+// threads are partly idle costs half its place and half its share of wavefronts;
+// 0.7 is the last round; each staged cell costs a tenth of a face, and wavefronts
+// that are not square skip the limiter less often.
+inline double face_split_time(int nfl, long nlines, int K, const FaceSplit& s) {
+  const int full = nfl / s.fj, rest = nfl - full * s.fj;
+  auto cost = [&](int f) { return 0.5 + 0.125 * ((f * s.tx + 63) / 64); };
+  const double groups = (double)(nlines / s.width) * ((s.width + s.tx - 1) / s.tx);
+  const double work = 1.0 + 0.1 * (s.fj + K - 1) * s.tx / 256.0 + 0.005 * (s.tx + 64.0 / s.tx - 16.0);
+  return work * (groups * (full * cost(s.fj) + (rest ? cost(rest) : 0.0)) / kFaceSlots + 0.7);
+}
+
+// The split of nlines lines of nfl faces each, `across` of them in a plane, at K
+// points and at most nc staged cells a workgroup.  A single line fills the
+// workgroup.  Else 32 faces of 8 lines of a plane, unless they fill the chunks so
+// badly that chunks of equal length, with as many of all lines side by side as
+// fit, promise 8 %.  us, 32 x 8 and the other, Euler at eight points, smooth (rough)
+// data: 72x72x33 along the transmissive z (34 faces: 17 x 15) 33 and 24 (43 and
+// 34); 100x100x12 along z (12 x 21) 34 and 26 (39 and 30); 65x65x65 (22 x 11) 44 and
+// 36 (55 and 45); 50x50x50 (50 x 5) 25 and 22 (29 and 26); where they promise less
+// they lose up to 15 % (1394x130, 300x300, 1024x1024 transmissive).
+inline FaceSplit face_split(int nfl, int across, long nlines, int K, int nc) {
+  if (nlines == 1) return FaceSplit{1, nfl < 256 ? nfl : 256, 1};
+  FaceSplit best{across, 32, kTileColumns};
+  double best_t = face_split_time(nfl, nlines, K, best) / 1.08;
+  for (const int f : {6, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 56, 64}) {
+    const int chunks = (nfl + f - 1) / f, fj = (nfl + chunks - 1) / chunks;
+    int tx = 256 / fj;
+    if (tx > nc / (fj + K - 1)) tx = nc / (fj + K - 1);
+    if (tx > nlines) tx = (int)nlines;
+    const FaceSplit s{(int)nlines, fj, tx};
+    const double t = face_split_time(nfl, nlines, K, s);
+    if (t < best_t) {
+      best_t = t;
+      best = s;
+    }
+  }
+  return best;
+}
+
+}  // namespace tenom

@@ -294,3 +294,68 @@ def test_line_faces_agree_with_the_row_sweep(T, n, bc):
         finally:
             T.set_sweep_kernel(T.SWEEP_AUTO)
         assert np.array_equal((F[:, :-1] - F[:, 1:]) * (1.0 / grid["dx"][0]), D)
+
+
+# Face fluxes of grids above the one-wavefront-per-field kernel, whose lines the
+# 32-face chunks of 8 lines fill badly (whole short lines, or equal chunks of many
+# lines, side by side) or well: the fluxes along an axis do not depend on the
+# other axes' extents, so blocks of lines taken as grids of their own (the other
+# kernel) give the same bits.  z, y, x order.
+FACE_SPLITS = [((12, 100, 101), 6, 1), ((50, 49, 50), 8, 1), ((33, 72, 73), 8 | 0x100, 3), ((33, 72, 73), 6, 2),
+               ((64, 64, 61), 8, 4), ((7, 160, 201), 6, 1), ((300, 401), 8, 1), ((1394, 130), 6, 7), ((8, 20000), 8, 2)]
+
+
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("shape,K,lim", FACE_SPLITS, ids=["x".join(map(str, c[0])) + f"-{c[1]}-{c[2]}" for c in FACE_SPLITS])
+def test_face_splits_agree_with_blocks_of_lines(T, shape, K, lim, bc):
+    C_T = 0.0 if K & 0x100 else (1e-5 if K == 6 else 1e-7)
+    nd = len(shape)
+    U = W.random_euler_state(shape, seed=sum(shape) + K, kind="mixed")
+    print(f"[face split] {shape} {K} {lim} bc={bc}", flush=True)
+
+    def faces(V, axis):
+        grid = dict(ndim=nd, n=list(reversed(V.shape[1:])), dx=[0.05, 0.07, 0.06][:nd], bc=[bc] * nd, system=1)
+        return [to_host(a) for a in T.reconstruct_faces(to_dev(V), grid, K, lim, C_T, GAMMA, axis, return_flags=True)]
+
+    for axis in range(nd):
+        along = nd - 1 - axis
+        whole = faces(U, axis)
+        across = [a for a in range(nd) if a != along]
+        # blocks of at most 16 x 16 lines in 3D, 24 in 2D; the first, a middle and the last
+        step = 16 if nd == 3 else 24
+        starts = [sorted({0, max(0, (shape[a] // step // 2) * step), max(0, shape[a] - step)}) for a in across]
+        for at in np.ndindex(*[len(s) for s in starts]):
+            cut = [slice(None)] * (nd + 1)
+            for a, s, i in zip(across, starts, at):
+                cut[1 + a] = slice(s[i], s[i] + step)
+            part = faces(np.ascontiguousarray(U[tuple(cut)]), axis)
+            assert np.array_equal(part[0], whole[0][tuple(cut)]), (axis, at, "flux")
+            assert np.array_equal(part[1], whole[1][(slice(None),) + tuple(cut)]), (axis, at, "flags")
+
+
+def test_faces_of_the_most_short_lines(T):
+    """300 million scalar lines of 7 cells: a launch of chunks of 32 faces each
+    would have more than 2^32 threads."""
+    import torch
+    nx, ny, nz = 32768, 9300, 7
+    if torch.cuda.mem_get_info()[0] < 60 << 30:
+        pytest.skip("needs 60 GB of device memory")
+    print(f"[many lines] {nx}x{ny}x{nz}", flush=True)
+    U = torch.empty((1, nz, ny, nx), dtype=torch.float64, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    for z in range(nz):
+        U[0, z].uniform_(-1.0, 1.0, generator=gen)
+
+    def grid(V):
+        return dict(ndim=3, n=list(reversed(V.shape[1:])), dx=[0.1] * 3, bc=[0, 0, 0], system=0, adv=[0.3, -0.2, 0.7])
+
+    F = T.reconstruct_faces(U, grid(U), 6, 1, 1e-5, GAMMA, 2)
+    F = F[0] if isinstance(F, tuple) else F
+    for y in (0, 4095, 8191, ny - 16):
+        for x in (0, 16000, nx - 64):
+            V = U[:, :, y:y + 16, x:x + 64].contiguous()
+            f = T.reconstruct_faces(V, grid(V), 6, 1, 1e-5, GAMMA, 2)
+            f = f[0] if isinstance(f, tuple) else f
+            assert torch.equal(f, F[:, :, y:y + 16, x:x + 64]), (y, x)
+    del U, F
+    torch.cuda.empty_cache()
