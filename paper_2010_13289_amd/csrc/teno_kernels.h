@@ -284,43 +284,6 @@ void k_sweep_row(SweepParams<NF> p) {
 // far less often than a strip of 64 faces along one line: most wavefronts
 // then skip the limiter (StagedCells with REREAD).
 // ---------------------------------------------------------------------------
-// Whole-line workgroups of a tile sweep along `axis`: the lines of the other
-// axis times the column groups (x columns for y and z, y rows for x).
-inline long tile_count(int axis, int nx, int ny, int nz) {
-  const long lines = (axis == 2) ? ny : nz;
-  const int across = (axis == 0) ? ny : nx;
-  return lines * ((across + kTileColumns - 1) / kTileColumns);
-}
-
-// Cells per segment of a tile sweep.  Segments of 32 c - 1 cells take c
-// chunks (one redundant face each); a whole line hands its faces on instead.
-// More segments fill the chip and shorten the last round, fewer save the
-// redundant faces and halo rows.  The c with the smallest estimate of
-//   workgroups (chunks + 0.15) / slots + 0.7 (chunks of one workgroup + 0.15),
-// slots = workgroups the chip holds, is taken; the estimate's order agreed
-// with the measured sweeps (Euler, six points unless stated; one chunk, two,
-// four, in us): 1024^2 y 67, 71, 79; 2048^2 y 236, 229, 235; 187x150x93 y at
-// eight points 313, 302, 316 (the last whole lines).
-inline int tile_segment(int axis, int n, int nx, int ny, int nz, int bc) {
-  const double lines = (double)tile_count(axis, nx, ny, nz);
-  const double slots = 256.0 * kFaceWaves;  // 256 CUs, one wavefront of a workgroup per SIMD
-  constexpr double start = 0.15;
-  int best = n;
-  double best_t = 0.0;
-  for (int c = 1;; ++c) {
-    const int seg = 32 * c - 1;
-    const bool whole = seg >= n || (bc == 0 && seg + 1 == n);
-    const int nseg = whole ? 1 : (n + seg - 1) / seg;
-    const double chunks = (n + (whole && bc == 0 ? 0 : nseg)) / (32.0 * nseg);
-    const double t = lines * nseg * (chunks + start) / slots + 0.7 * (c + start);
-    if (c == 1 || t < best_t) {
-      best_t = t;
-      best = whole ? n : seg;
-    }
-    if (whole) return best;
-  }
-}
-
 template <int NF, int K>
 struct SweepTile {
   static constexpr int TX = kTileColumns;

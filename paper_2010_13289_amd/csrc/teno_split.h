@@ -17,6 +17,50 @@ constexpr double kFaceSlots = 256.0 * kFaceWaves;
 // 8 faces, which lie whole in smooth regions more often than strips.
 constexpr int kTileColumns = 8;
 
+// Whole-line workgroups of a tile sweep along `axis`: the lines of the other
+// axis times the column groups (x columns for y and z, y rows for x).
+inline long tile_count(int axis, int nx, int ny, int nz) {
+  const long lines = (axis == 2) ? ny : nz;
+  const int across = (axis == 0) ? ny : nx;
+  return lines * ((across + kTileColumns - 1) / kTileColumns);
+}
+
+// Cells per segment of a tile sweep.  Segments of 32 c - 1 cells take c
+// chunks (one redundant face each); a whole line hands its faces on instead.
+// More segments fill the chip and shorten the last round, fewer save the
+// redundant faces and halo rows.  The c with the smallest estimate of
+//   workgroups (chunks + 0.15) / slots + 0.7 (chunks of one workgroup + 0.15),
+// slots = workgroups the chip holds, is taken; the estimate's order agreed
+// with the measured sweeps (Euler, six points unless stated; one chunk, two,
+// four, in us): 1024^2 y 67, 71, 79; 2048^2 y 236, 229, 235; 187x150x93 y at
+// eight points 313, 302, 316 (the last whole lines).  The search ends
+// where the second term alone exceeds the best, so that enqueuing a long thin
+// grid's sweep does not take longer than the sweep (every c took 158 us for 10^6
+// cells).
+inline double tile_segment_time(double lines, int n, int bc, int c, bool whole) {
+  constexpr double start = 0.15;
+  const long seg = 32l * c - 1, nseg = whole ? 1 : (n + seg - 1) / seg;
+  const double chunks = (n + (whole && bc == 0 ? 0 : nseg)) / (32.0 * nseg);
+  return lines * nseg * (chunks + start) / kFaceSlots + 0.7 * (c + start);
+}
+
+inline int tile_segment(int axis, int n, int nx, int ny, int nz, int bc) {
+  const double lines = (double)tile_count(axis, nx, ny, nz);
+  // chunks of the whole line: the first c whose segment holds it
+  const int last = (bc == 0 && n % 32 == 0) ? n / 32 : n / 32 + 1;
+  int best = n;
+  double best_t = 0.0;
+  for (int c = 1; c < last; ++c) {
+    const double t = tile_segment_time(lines, n, bc, c, false);
+    if (c == 1 || t < best_t) {
+      best_t = t;
+      best = 32 * c - 1;
+    }
+    if (0.7 * c > best_t) break;
+  }
+  return last == 1 || tile_segment_time(lines, n, bc, last, true) < best_t ? n : best;
+}
+
 // Split of the face kernel: a workgroup of 256 threads takes fj faces of tx lines;
 // its lines are side by side in rows of `width` lines.
 struct FaceSplit {

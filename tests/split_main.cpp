@@ -3,10 +3,12 @@
 #include "teno_split.h"
 
 #include <cstdio>
+#include <ctime>
 
 using namespace tenom;
 
 static int bad = 0;
+static volatile long check_thin = 0;  // keeps the timed choices
 
 static void check_faces(int nfl, int across, long nlines, int K) {
   const int nc = 416;
@@ -21,7 +23,51 @@ static void check_faces(int nfl, int across, long nlines, int K) {
   }
 }
 
+// tile_segment by trying every chunk count up to the whole line
+static int segment_by_all(int axis, int n, int nx, int ny, int nz, int bc) {
+  const double lines = (double)tile_count(axis, nx, ny, nz);
+  int best = n;
+  double best_t = 0.0;
+  for (int c = 1;; ++c) {
+    const int seg = 32 * c - 1;
+    const bool whole = seg >= n || (bc == 0 && seg + 1 == n);
+    const double t = tile_segment_time(lines, n, bc, c, whole);
+    if (c == 1 || t < best_t) {
+      best_t = t;
+      best = whole ? n : seg;
+    }
+    if (whole) return best;
+  }
+}
+
+static void check_segment(int axis, int n, int across, int others, int bc) {
+  const int nx = axis == 0 ? n : across, ny = axis == 0 ? across : (axis == 1 ? n : others);
+  const int nz = axis == 2 ? n : others;
+  const int got = tile_segment(axis, n, nx, ny, nz, bc), want = segment_by_all(axis, n, nx, ny, nz, bc);
+  if (got != want) {
+    std::printf("tile_segment(%d, %d, %d x %d x %d, %d): %d, not %d\n", axis, n, nx, ny, nz, bc, got, want);
+    ++bad;
+  }
+}
+
 int main() {
+  for (int axis = 0; axis < 3; ++axis)
+    for (int bc = 0; bc < 2; ++bc)
+      for (int across : {6, 9, 64, 500, 5000})
+        for (int others : {1, 6, 100, 1000}) {
+          if (axis == 2 && others == 1) continue;
+          for (int n = 6; n <= 700; ++n) check_segment(axis, n, across, others, bc);
+          for (int n : {1023, 1024, 1025, 9999, 10016, 65536, 200000, 1000000})
+            if ((long)n * across * others < 0x7fffffffl) check_segment(axis, n, across, others, bc);
+        }
+  // a long thin grid: a thousand choices of 0.65 ms each by trying every count
+  const std::clock_t t0 = std::clock();
+  for (int i = 0; i < 1000; ++i) check_thin = check_thin + tile_segment(0, 4000000 + i, 4000000 + i, 9, 1, 1);
+  const double ms = 1e3 * (double)(std::clock() - t0) / CLOCKS_PER_SEC;
+  if (ms > 100.0) {
+    std::printf("tile_segment of a line of 4,000,000 cells: %.1f us\n", ms);
+    ++bad;
+  }
   for (int K = 6; K <= 8; K += 2) {
     for (int n = K; n <= 3000; ++n)
       for (int open = 0; open < 2; ++open)
