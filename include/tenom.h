@@ -407,8 +407,9 @@ int tenom_version(void);
  * TENOM_SWEEP_TILE: a workgroup stages tiles of 8 adjacent lines (x columns
  * for y and z, y rows for x) by a chunk of the line in LDS and walks a segment
  * of the lines, or the lines whole.  TENOM_SWEEP_AUTO (the default): the tile
- * kernel in 2D and 3D, except along x where the rows fill at most 512
- * workgroups of the line kernel.  In 1D it is a whole step in one launch where
+ * kernel in 2D and 3D, except along x where the rows are at least 128 cells and
+ * fill at most 512 workgroups of the line kernel, or fill its workgroups better
+ * than the tiles.  In 1D it is a whole step in one launch where
  * the line is one workgroup (256 faces of the Euler equations, 1024 of the
  * scalar equation), one wavefront per field on Euler lines of at most 40,960
  * cells, and the line kernel otherwise.

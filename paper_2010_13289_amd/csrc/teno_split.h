@@ -61,6 +61,17 @@ inline int tile_segment(int axis, int n, int nx, int ny, int nz, int bc) {
   return last == 1 || tile_segment_time(lines, n, bc, last, true) < best_t ? n : best;
 }
 
+// Whether the row sweep takes the x sweep of a 2D or 3D grid, instead of the tile
+// sweep: its workgroups (256 faces of one row) are at most two per CU, or the rows
+// fill them better than rows and columns fill the tiles.
+inline bool row_sweep_x(int nx, int ny, int nz, int bc) {
+  if ((long)((nx + 254) / 255) * ny * nz <= 512 && nx >= 128) return true;
+  const int cells = (bc == 0 && nx <= 256) ? 256 : 255;
+  const double row = (double)nx / ((double)cells * ((nx + cells - 1) / cells));
+  const double tile = (double)nx / (32.0 * ((nx + 31) / 32)) * ny / (kTileColumns * (double)((ny + kTileColumns - 1) / kTileColumns));
+  return row > tile;
+}
+
 // Split of the face kernel: a workgroup of 256 threads takes fj faces of tx lines;
 // its lines are side by side in rows of `width` lines.
 struct FaceSplit {

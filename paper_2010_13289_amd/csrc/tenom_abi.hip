@@ -276,9 +276,13 @@ int sweep(const tenom_grid* g, int scheme, int limiter, double C_T, double gamma
   // 128^3 x at eight points 372 (row) -> 273).  The row sweep serves 1D, and x
   // rows that fill its workgroups where those are at most two per CU: with the
   // chip part empty the shorter pass through one workgroup counts (256^2 x
-  // 11.4 us against 15.4).
-  const long row_blocks = (long)((d.nx + 254) / 255) * d.ny * d.nz;
-  const bool few_rows = axis == 0 && (g->ndim == 1 || (row_blocks <= 512 && d.nx >= 128));
+  // 11.4 us against 15.4); and x rows that fill its workgroups better than the
+  // tiles' (us, row and tile, six points, smooth and rough data: 200,000 x 9 67 and
+  // 130, 110 and 204; 20,000 x 17 22 and 26, 32 and 38; 500x10x100 29 and 44, 45 and
+  // 70; 20,000 x 90 72 and 80, 119 and 124; row over tile where both fill, 256^3:
+  // 0.86 smooth to 1.03 mixed; where the rows fill worse: 300x1200 1.27 to 1.48,
+  // 187x93x150 0.98 to 1.15, 1024^2 0.99 to 1.12).
+  const bool few_rows = axis == 0 && (g->ndim == 1 || row_sweep_x(d.nx, d.ny, d.nz, g->bc[0]));
   const int choice = g_sweep_kernel.load(std::memory_order_relaxed);
   const bool tile = choice == TENOM_SWEEP_TILE || (choice == TENOM_SWEEP_AUTO && !few_rows);
   field_map(g, axis, L.fld);

@@ -60,6 +60,16 @@ int main() {
           for (int n : {1023, 1024, 1025, 9999, 10016, 65536, 200000, 1000000})
             if ((long)n * across * others < 0x7fffffffl) check_segment(axis, n, across, others, bc);
         }
+  // x sweeps by the row sweep: few rows, or rows that fill its workgroups better
+  struct { int nx, ny, nz, bc; bool row; } xs[] = {{256, 256, 1, 0, true},   {200000, 9, 1, 1, true},
+      {20000, 17, 1, 0, true}, {500, 10, 100, 0, true},  {255, 255, 9, 1, true}, {20000, 90, 1, 0, true},
+      {256, 256, 256, 0, false}, {256, 256, 256, 1, false}, {256, 41, 30, 1, false}, {256, 41, 30, 0, true}, {300, 1200, 1, 0, false},
+      {1024, 1024, 1, 0, false}, {187, 93, 150, 0, false}, {64, 9, 9, 0, false}, {8, 100000, 1, 0, false}};
+  for (const auto& x : xs)
+    if (row_sweep_x(x.nx, x.ny, x.nz, x.bc) != x.row) {
+      std::printf("row_sweep_x(%d, %d, %d, %d) is %d\n", x.nx, x.ny, x.nz, x.bc, !x.row);
+      ++bad;
+    }
   // a long thin grid: a thousand choices of 0.65 ms each by trying every count
   const std::clock_t t0 = std::clock();
   for (int i = 0; i < 1000; ++i) check_thin = check_thin + tile_segment(0, 4000000 + i, 4000000 + i, 9, 1, 1);
