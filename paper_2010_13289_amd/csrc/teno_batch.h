@@ -164,7 +164,7 @@ __device__ __forceinline__ void batch_segment(const SegIn& g, const FaceParams& 
   for (int f = 0; f < FPT; ++f) {
     const int j = t + f * TPB;
     if (j < nface) {
-      StagedCells<NF, K, 1, true> prov{stage, NC, j};
+      StagedCells<NF, K, 1, true, (FPT > 1)> prov{stage, NC, j};
       uint32_t bits[2][NF];
       double F[NF];
       face_flux<NF, K, LIM, ADAPT, false>(prov, fp, F, bits);

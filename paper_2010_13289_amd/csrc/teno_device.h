@@ -721,7 +721,14 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
       // the acoustic pair is one group and every other field alone: the sweeps
       // then fit three wavefronts per SIMD instead of two (256^3 Euler x 1573 ->
       // 1394 us, y 1322 -> 1175, z 1412 -> 1243).
-      if constexpr (NF == 3 || K == 8) {
+      // In 1D at six points all three fields are one group (150 to 166 VGPRs) except
+      // where the smaller groups leave four wavefronts per SIMD (at most 128 VGPRs:
+      // one face a thread with TENO, minmod or VA), which constant states need more:
+      // 119,661 batched segments, us for four steps, MP rough 4833 -> 4608, smooth
+      // 3460 -> 3230; minmod rough 4147 -> 4051, but constant 1554 -> 1762.
+      if constexpr (NF == 3 && K == 6 && (P::kOneGroup || LIM == LIM_MP || LIM == LIM_MP_MM || LIM == LIM_TVD5)) {
+        group(7u);
+      } else if constexpr (NF == 3 || K == 8) {
         group(1u | (1u << (NF - 1)));
 #pragma unroll
         for (int q = 1; q < NF - 1; ++q) group(1u << q);

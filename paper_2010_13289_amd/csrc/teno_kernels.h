@@ -120,10 +120,12 @@ struct RowStage {
 // (worth it where most wavefronts see only smooth data: the tile sweep's
 // 8 x 8 patches of faces, which a discontinuity crosses far less often than
 // the row sweep's strips of 64, and the batched 1D problems' constant
-// states).
-template <int NF, int K, int CS = 1, bool REREAD = false>
+// states).  ONE: a 1D face at six points takes its fields as one group whatever
+// the limiter (see euler_face).
+template <int NF, int K, int CS = 1, bool REREAD = false, bool ONE = false>
 struct StagedCells {
   static constexpr bool kReread = REREAD;  // the face reads the cells again per group of fields
+  static constexpr bool kOneGroup = ONE;
   static constexpr bool kUniform = REREAD && NF == 3 && CS == 1;  // 1D: constant states skip the face
   const double* s;  // LDS: [NE][NC]
   int nc;           // row pitch of the staging array
@@ -136,7 +138,7 @@ struct StagedCells {
   __device__ __forceinline__ StagedCells fresh() const {
     int c = c0;
     asm volatile("" : "+v"(c));
-    return StagedCells<NF, K, CS, REREAD>{s, nc, c, cs};
+    return StagedCells<NF, K, CS, REREAD, ONE>{s, nc, c, cs};
   }
   __device__ __forceinline__ void state_flux(int m, double (&X)[NF], double (&F)[NF]) const {
     const int c = c0 + m * step();
@@ -238,7 +240,7 @@ void k_sweep_row(SweepParams<NF> p) {
   double F[NF];
   __builtin_amdgcn_s_setprio(0);
   if (t < nface) {
-    StagedCells<NF, K, 1, true> prov{stage, NC, t};
+    StagedCells<NF, K, 1, true, true> prov{stage, NC, t};
     uint32_t bits[2][NF];
     face_flux<NF, K, LIM, ADAPT, false>(prov, p.fp, F, bits);
   }
