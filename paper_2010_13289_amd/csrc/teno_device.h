@@ -670,9 +670,9 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
       // Every face of the wavefront sees K equal cells (the constant states
       // of a Riemann problem, which most wavefronts of the batched problems
       // hold: 97 % of them in the first hundred steps).  All differences are
-      // zero, so each reconstruction is its split value, bit for bit, whatever
-      // the cutoff and the limiter: one projection instead of K and no
-      // reconstruction.
+      // zero (of finite values), so each reconstruction is its split value, bit
+      // for bit, whatever the cutoff and the limiter: one projection instead of
+      // K and no reconstruction.
       alpha = fmax(alpha, prov.speed(0));
       double X[NF], F[NF], w[NF], g[NF];
       prov.state_flux(0, X, F);
@@ -682,8 +682,16 @@ __device__ __forceinline__ void euler_face(P& prov, double gamma, const TenoPara
       for (int q = 0; q < NF; ++q) {
         double vp, vm;
         lf_split2(g[q], alpha, w[q], vp, vm);
-        fc[q] = ((q == 0 || q == NF - 1) ? 0.25 : 0.5) * ((vp + 0.0) + (vm + 0.0));
-        bits[0][q] = bits[1][q] = FLAGS ? teno_flat_bits<K, ADAPT>(tp) : 0u;
+        // the differences: 0, or NaN where the value is not finite, which no
+        // candidate fails
+        const double dp = vp - vp, dm = vm - vm;
+        fc[q] = ((q == 0 || q == NF - 1) ? 0.25 : 0.5) * ((vp + dp) + (vm + dm));
+        bits[0][q] = bits[1][q] = 0u;
+        if constexpr (FLAGS) {
+          const uint32_t all = (1u << (K - 2)) - 1u, flat = teno_flat_bits<K, ADAPT>(tp);
+          bits[0][q] = dp == 0.0 ? flat : all;
+          bits[1][q] = dm == 0.0 ? flat : all;
+        }
       }
     } else {
 #pragma unroll

@@ -359,3 +359,24 @@ def test_faces_of_the_most_short_lines(T):
             assert torch.equal(f, F[:, :, y:y + 16, x:x + 64]), (y, x)
     del U, F
     torch.cuda.empty_cache()
+
+
+# Runs of one state whose faces are not finite (negative pressure, vacuum, NaN,
+# overflow) or extreme, with a cutoff that no constant stencil passes: a long line,
+# whose wavefronts take constant states at once, against a short one, which does
+# not look for them.
+@pytest.mark.parametrize("K,lim,C_T", [(8, 1, 0.3), (6, 2, 0.3), (6, 7, 1e-5), (8 | 0x100, 3, 0.0)])
+def test_faces_of_constant_lines_that_are_not_finite(T, K, lim, C_T):
+    states = [(1.0, 0.0, -1.0), (1.0, -1.0, 0.2), (0.0, 0.0, 1.0), (np.nan, 0.0, 1.0), (1.0, np.nan, 1.0),
+              (1.0, 0.5, np.inf), (1e290, 1e293, 5.0000001e295), (1.0, 1e120, 1e240), (1e-300, 0.0, 1e10), (1.0, 0.3, 2.0)]
+    print(f"[constant line] {K} {lim} {C_T}", flush=True)
+    for state in states:
+        out = []
+        for n in (88, 90112):
+            grid = dict(ndim=1, n=[n], dx=[0.1], bc=[0], system=1)
+            U = np.repeat(np.array(state)[:, None], n, axis=1)
+            F, flags = T.reconstruct_faces(to_dev(U), grid, K, lim, C_T, GAMMA, 0, return_flags=True)
+            out.append((to_host(F), to_host(flags)))
+        (F0, f0), (F1, f1) = out
+        assert np.array_equal(np.broadcast_to(F0[:, :1], F1.shape), F1, equal_nan=True), state
+        assert np.array_equal(np.broadcast_to(f0[:, :, :1], f1.shape), f1), state
