@@ -331,7 +331,15 @@ int tenom_batch_destroy(tenom_batch_plan* plan);
 int64_t tenom_batch_cells(const tenom_batch_plan* plan);
 /* Select the tile shape of later calls (0 .. TENOM_BATCH_TILES-1). */
 int tenom_batch_set_tile(tenom_batch_plan* plan, int tile);
+/* The tile of later calls, or of the persistent launch's size (3) while none
+ * is chosen (-1 for NULL). */
 int tenom_batch_get_tile(const tenom_batch_plan* plan);
+/* Whether a tile is chosen (1), or each call runs the kernel that suits it (0);
+ * -1 for NULL.  A caller that sets a tile for a while puts back what was there
+ * with tenom_batch_set_tile if this said 1, else with tenom_batch_reset_tile. */
+int tenom_batch_tile_chosen(const tenom_batch_plan* plan);
+/* Undo the choice of a tile: the plan is again as tenom_batch_create left it. */
+int tenom_batch_reset_tile(tenom_batch_plan* plan);
 
 /*
  * Enqueue `steps` SSP-RK3 steps (Sec. 4) of problems first .. first+count-1

@@ -34,7 +34,8 @@ SYMBOLS = (
     "tenom_workspace_bytes", "tenom_max_wave_speed", "tenom_check_finite", "tenom_strerror",
     "tenom_last_error", "tenom_version", "tenom_profile_enable", "tenom_profile_read",
     "tenom_batch_tile_shape", "tenom_batch_create", "tenom_batch_destroy", "tenom_batch_cells",
-    "tenom_batch_set_tile", "tenom_batch_get_tile", "tenom_batch_rk3", "tenom_batch_rk3_graph",
+    "tenom_batch_set_tile", "tenom_batch_get_tile", "tenom_batch_tile_chosen", "tenom_batch_reset_tile",
+    "tenom_batch_rk3", "tenom_batch_rk3_graph",
     "tenom_batch_autotune", "tenom_batch_times", "tenom_batch_reset_times", "tenom_batch_rk3_persistent",
     "tenom_vjp_workspace_bytes", "tenom_flux_divergence_vjp", "tenom_rk3_vjp_workspace_bytes",
     "tenom_rk3_step_vjp", "tenom_rk3_step_stages", "tenom_rk3_step_vjp_stages", "tenom_rk3_step_cfl",
@@ -138,6 +139,8 @@ def lib() -> C.CDLL:
         L.tenom_batch_cells.restype = C.c_int64
         L.tenom_batch_set_tile.argtypes = [vp, ip]
         L.tenom_batch_get_tile.argtypes = [vp]
+        L.tenom_batch_tile_chosen.argtypes = [vp]
+        L.tenom_batch_reset_tile.argtypes = [vp]
         L.tenom_batch_rk3.argtypes = [vp, ip, ip, dp, dp, dp, ip, ip, ip, vp, vp]
         L.tenom_batch_rk3_graph.argtypes = [vp, ip, ip, dp, dp, dp, ip, vp, vp]
         L.tenom_batch_rk3_persistent.argtypes = [vp, ip, ip, dp, dp, dp, ip, vp, vp]
@@ -406,6 +409,15 @@ class BatchPlan:
     @tile.setter
     def tile(self, t: int):
         _check(lib().tenom_batch_set_tile(self._h, int(t)))
+
+    @property
+    def tile_chosen(self) -> bool:
+        """Whether a tile was set or autotuned (else each call runs the kernel that suits it)."""
+        return bool(lib().tenom_batch_tile_chosen(self._h))
+
+    def reset_tile(self):
+        """Undo the choice of a tile."""
+        _check(lib().tenom_batch_reset_tile(self._h))
 
     def rk3(self, U, scheme, limiter, C_T, gamma, cfl, steps=1, first=0, count=None, stream=None):
         """Enqueue `steps` RK3 steps of problems [first, first + count)."""

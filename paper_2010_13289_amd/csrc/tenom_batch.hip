@@ -323,6 +323,16 @@ int tenom_batch_set_tile(tenom_batch_plan* plan, int tile) {
 
 int tenom_batch_get_tile(const tenom_batch_plan* plan) { return plan ? plan->tile : -1; }
 
+int tenom_batch_tile_chosen(const tenom_batch_plan* plan) { return plan ? (plan->tile_set ? 1 : 0) : -1; }
+
+int tenom_batch_reset_tile(tenom_batch_plan* plan) {
+  g_err[0] = 0;
+  if (!plan) return fail(TENOM_EINVAL, "plan is NULL");
+  plan->tile = tenom_batch_plan().tile;
+  plan->tile_set = false;
+  return TENOM_OK;
+}
+
 int tenom_batch_rk3(tenom_batch_plan* plan, int scheme, int limiter, double C_T, double gamma, double cfl, int steps,
                     int first, int count, double* U, void* stream) {
   g_err[0] = 0;

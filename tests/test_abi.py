@@ -204,6 +204,11 @@ def test_batch_arguments_fail_before_allocation(lib):
     assert lib.tenom_batch_destroy(None) == T.OK
 
 
+def test_batch_tile_choice_of_no_plan(lib):
+    assert lib.tenom_batch_tile_chosen(None) == -1
+    assert lib.tenom_batch_reset_tile(None) == T.EINVAL
+
+
 def test_batch_tile_shapes(lib):
     shapes = [T.batch_tile_shape(t) for t in range(T.BATCH_TILES)]
     assert len(set(shapes)) == T.BATCH_TILES

@@ -473,3 +473,24 @@ def test_small_batches_agree_with_a_chosen_tile(T, sizes, scheme, lim, C_T, bc):
     assert np.array_equal(to_host(Ug), want, equal_nan=True)
     plan.close()
     chosen.close()
+
+
+def test_a_chosen_tile_can_be_undone(T):
+    """Setting a tile is seen and can be undone; the automatic choice, the tile and
+    the automatic choice again give the same bits, in the captured graph too."""
+    sizes = [70, 300, 1000]
+    U, dx, _ = ragged_batch(sizes, seed0=40)
+    print("[tile reset]", flush=True)
+    plan = T.BatchPlan(sizes, dx, 1)
+    assert not plan.tile_chosen
+    outs = []
+    for tile in (None, 5, None):
+        if tile is not None:
+            plan.tile = tile
+        else:
+            plan.reset_tile()
+        assert plan.tile_chosen == (tile is not None) and plan.tile == (3 if tile is None else tile)
+        for call in (plan.rk3, plan.rk3_graph):
+            outs.append(to_host(call(to_dev(U), 8, T.LIM_MP, 1e-7, GAMMA, CFL, steps=2)))
+    assert all(np.array_equal(o, outs[0]) for o in outs)
+    plan.close()
