@@ -331,8 +331,8 @@ int tenom_batch_destroy(tenom_batch_plan* plan);
 int64_t tenom_batch_cells(const tenom_batch_plan* plan);
 /* Select the tile shape of later calls (0 .. TENOM_BATCH_TILES-1). */
 int tenom_batch_set_tile(tenom_batch_plan* plan, int tile);
-/* The tile of later calls, or of the persistent launch's size (3) while none
- * is chosen (-1 for NULL). */
+/* The tile of later calls; while none is chosen 3, or the fastest of the tiles
+ * where the autotuner found the automatic choice faster; -1 for NULL. */
 int tenom_batch_get_tile(const tenom_batch_plan* plan);
 /* Whether a tile is chosen (1), or each call runs the kernel that suits it (0);
  * -1 for NULL.  A caller that sets a tile for a while puts back what was there
@@ -381,7 +381,9 @@ int tenom_batch_rk3_persistent(tenom_batch_plan* plan, int scheme, int limiter, 
 /*
  * Autotuner of the tile shape: time `steps` steps (after one untimed step)
  * of every tile on a copy of U, for this scheme and limiter, select the
- * fastest for later calls and return it in *best (nullable).
+ * fastest for later calls and return it in *best (nullable).  Batches small
+ * enough for one wavefront per field time that too; where it is the fastest
+ * no tile is chosen (tenom_batch_tile_chosen), and *best is the fastest tile.
  * ms_per_step: nullable HOST array of TENOM_BATCH_TILES entries.  U and the
  * plan's clocks are left as they were.  Allocates one temporary state copy
  * and synchronises `stream`.  Every tile gives the same bits, so the choice

@@ -440,11 +440,14 @@ int tenom_batch_autotune(tenom_batch_plan* plan, int scheme, int limiter, double
   if (e == hipSuccess) e = hipMemcpyAsync((char*)save + clocks, plan->dt_d, clocks, hipMemcpyDeviceToDevice, s);
   const int keep = plan->tile;
   const bool keep_set = plan->tile_set;
-  plan->tile_set = true;
   int pick = keep;
+  bool free_best = false;  // the automatic choice beats every tile
   float best_ms = 0.f;
-  for (int t = 0; t < kNumTiles && e == hipSuccess && rc == TENOM_OK; ++t) {
-    plan->tile = t;
+  // every tile, then the automatic choice where that is not one of them
+  const bool fields = plan->tiling[0].first[plan->count] <= kFieldsSegments;
+  for (int t = 0; t < kNumTiles + (fields ? 1 : 0) && e == hipSuccess && rc == TENOM_OK; ++t) {
+    plan->tile_set = t < kNumTiles;
+    if (t < kNumTiles) plan->tile = t;
     // one untimed step, then `steps` timed steps from the same state
     e = hipMemcpyAsync(tmp, U, state, hipMemcpyDeviceToDevice, s);
     if (e == hipSuccess) rc = enqueue(plan, m, cfl, 1, 0, plan->count, tmp, s);
@@ -456,14 +459,18 @@ int tenom_batch_autotune(tenom_batch_plan* plan, int scheme, int limiter, double
     float ms = 0.f;
     if (e == hipSuccess && !rc) e = hipEventElapsedTime(&ms, a, b);
     ms /= (float)steps;
-    if (ms_per_step) ms_per_step[t] = ms;
+    if (ms_per_step && t < kNumTiles) ms_per_step[t] = ms;
     if (e == hipSuccess && !rc && (t == 0 || ms < best_ms)) {
       best_ms = ms;
-      pick = t;
+      if (t < kNumTiles)
+        pick = t;
+      else
+        free_best = true;
     }
   }
-  plan->tile = (e == hipSuccess && !rc) ? pick : keep;
-  plan->tile_set = (e == hipSuccess && !rc) || keep_set;
+  const bool ok = e == hipSuccess && !rc;
+  plan->tile = ok ? pick : keep;
+  plan->tile_set = ok ? !free_best : keep_set;
   if (save) {
     hipMemcpyAsync(plan->t_d, save, clocks, hipMemcpyDeviceToDevice, s);
     hipMemcpyAsync(plan->dt_d, (char*)save + clocks, clocks, hipMemcpyDeviceToDevice, s);

@@ -494,3 +494,25 @@ def test_a_chosen_tile_can_be_undone(T):
             outs.append(to_host(call(to_dev(U), 8, T.LIM_MP, 1e-7, GAMMA, CFL, steps=2)))
     assert all(np.array_equal(o, outs[0]) for o in outs)
     plan.close()
+
+
+@pytest.mark.parametrize("sizes", [[300, 700, 1500, 2000, 900, 600, 2500, 1300], [4000] * 30], ids=["few", "many"])
+def test_autotuning_keeps_the_faster_automatic_choice(T, sizes):
+    """Few segments: one wavefront per field is a third faster than any tile, so
+    autotuning leaves the tile unchosen, whatever was set before; many: a tile is
+    chosen.  The reported tile is the fastest of the tiles, and all give the same
+    bits."""
+    U, dx, _ = ragged_batch(sizes, seed0=41)
+    print(f"[autotune] {len(sizes)} problems", flush=True)
+    plan, ref = T.BatchPlan(sizes, dx, 1), T.BatchPlan(sizes, dx, 1)
+    plan.tile = 4
+    Ud = to_dev(U)
+    best, ms = plan.autotune(Ud, 8, T.LIM_MP, 1e-7, GAMMA, CFL, steps=20)
+    few = sum((n + 62) // 63 for n in sizes) <= 1536
+    assert plan.tile == best and ms[best] == min(ms)
+    assert plan.tile_chosen == (not few)
+    plan.rk3(Ud, 8, T.LIM_MP, 1e-7, GAMMA, CFL, steps=3)
+    want = ref.rk3(to_dev(U), 8, T.LIM_MP, 1e-7, GAMMA, CFL, steps=3)
+    assert np.array_equal(to_host(Ud), to_host(want))
+    plan.close()
+    ref.close()
