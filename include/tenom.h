@@ -384,6 +384,8 @@ int tenom_batch_rk3_persistent(tenom_batch_plan* plan, int scheme, int limiter, 
  * fastest for later calls and return it in *best (nullable).  Batches small
  * enough for one wavefront per field time that too; where it is the fastest
  * no tile is chosen (tenom_batch_tile_chosen), and *best is the fastest tile.
+ * The tile chosen for a larger batch is not used by calls on few of its
+ * problems (tenom_batch_rk3 with a small count).
  * ms_per_step: nullable HOST array of TENOM_BATCH_TILES entries.  U and the
  * plan's clocks are left as they were.  Allocates one temporary state copy
  * and synchronises `stream`.  Every tile gives the same bits, so the choice

@@ -36,7 +36,8 @@ struct tenom_batch_plan {
     std::vector<int> first;  // [count + 1] first segment of each problem
   } tiling[kNumTiles];
   int tile = 3;
-  bool tile_set = false;  // by the caller or the autotuner
+  bool tile_set = false;    // by the caller or the autotuner
+  bool tile_tuned = false;  // by the autotuner, which timed all problems at once
   // persistent path: the problems longest first, and the queue counters
   int nblk = 0;
   int* order_d = nullptr;
@@ -84,11 +85,12 @@ const RowFn kRow[kNumTiles] = {tenom_batch_row_tile0, tenom_batch_row_tile1, ten
 // 1300 37.3 and 46.3 (45.5 and 50.4), 2530 53.0 and 50.2 (67.0 and 66.0), 5100 83
 // and 64 (115 and 110); six points cross between the same counts.  Up to
 // kSmallTileSegments tile 0, whose small segments leave the constant states to
-// themselves and fill the last round: 24,990 segments 128.6 us, tile 2 145.3,
-// tile 3 170.5 (367, 416, 375).  Above, the pass is bound by HBM where the states
-// are constant, and tile 2 has twice the loads in flight per wavefront: 189,559
-// segments 613 us, tile 0 713, tile 3 768 (rough everywhere 2792, 2622, 2587; a
-// caller with such data asks for tile 3 or the autotuner).
+// themselves and fill the last round: 35,421 segments 137 us, tile 2 137, tile 3
+// 152 (478, 520, 479).  Above, the pass is bound by HBM where the states are
+// constant, and tile 2 has twice the loads in flight per wavefront: 119,661
+// segments 396 us, tile 0 435, tile 3 470 (rough everywhere 1690, 1640, 1600, and
+// 1690 by tile 3 before constant states had a path of their own; smooth moving
+// states 1140, 1080, 1110): a caller with such data asks the autotuner.
 constexpr int kFieldsSegments = 1536;
 constexpr int kSmallTileSegments = 65536;
 
@@ -175,8 +177,13 @@ int enqueue(tenom_batch_plan* P, const Method& m, double cfl, int steps, int fir
             hipStream_t s) {
   if (cnt <= 0 || steps <= 0) return TENOM_OK;
   const int seg63 = P->tiling[0].first[first + cnt] - P->tiling[0].first[first];
-  const bool fields = !P->tile_set && seg63 <= kFieldsSegments;
-  const int tile = P->tile_set ? P->tile : (seg63 <= kSmallTileSegments ? 0 : 2);
+  // The autotuner's tile is the fastest for all problems at once.  Few of a large
+  // batch's run one wavefront per field all the same: a problem of 16384 cells
+  // alone, us a step, Riemann (rough) data: that 31 (35), tile 2 47 (63), tile 3 42 (44).
+  const bool few = seg63 <= kFieldsSegments;
+  const bool chosen = P->tile_set && !(P->tile_tuned && few && P->tiling[0].first[P->count] > kFieldsSegments);
+  const bool fields = !chosen && few;
+  const int tile = chosen ? P->tile : (seg63 <= kSmallTileSegments ? 0 : 2);
   const auto& T = P->tiling[tile];
   const int sb = T.first[first], se = T.first[first + cnt];
   BatchLaunch L;
@@ -318,6 +325,7 @@ int tenom_batch_set_tile(tenom_batch_plan* plan, int tile) {
   if (tile < 0 || tile >= kNumTiles) return fail(TENOM_EINVAL, "tile %d not in [0, %d)", tile, kNumTiles);
   plan->tile = tile;
   plan->tile_set = true;
+  plan->tile_tuned = false;
   return TENOM_OK;
 }
 
@@ -329,7 +337,7 @@ int tenom_batch_reset_tile(tenom_batch_plan* plan) {
   g_err[0] = 0;
   if (!plan) return fail(TENOM_EINVAL, "plan is NULL");
   plan->tile = tenom_batch_plan().tile;
-  plan->tile_set = false;
+  plan->tile_set = plan->tile_tuned = false;
   return TENOM_OK;
 }
 
@@ -439,7 +447,7 @@ int tenom_batch_autotune(tenom_batch_plan* plan, int scheme, int limiter, double
   if (e == hipSuccess) e = hipMemcpyAsync(save, plan->t_d, clocks, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync((char*)save + clocks, plan->dt_d, clocks, hipMemcpyDeviceToDevice, s);
   const int keep = plan->tile;
-  const bool keep_set = plan->tile_set;
+  const bool keep_set = plan->tile_set, keep_tuned = plan->tile_tuned;
   int pick = keep;
   bool free_best = false;  // the automatic choice beats every tile
   float best_ms = 0.f;
@@ -447,6 +455,7 @@ int tenom_batch_autotune(tenom_batch_plan* plan, int scheme, int limiter, double
   const bool fields = plan->tiling[0].first[plan->count] <= kFieldsSegments;
   for (int t = 0; t < kNumTiles + (fields ? 1 : 0) && e == hipSuccess && rc == TENOM_OK; ++t) {
     plan->tile_set = t < kNumTiles;
+    plan->tile_tuned = false;
     if (t < kNumTiles) plan->tile = t;
     // one untimed step, then `steps` timed steps from the same state
     e = hipMemcpyAsync(tmp, U, state, hipMemcpyDeviceToDevice, s);
@@ -471,6 +480,7 @@ int tenom_batch_autotune(tenom_batch_plan* plan, int scheme, int limiter, double
   const bool ok = e == hipSuccess && !rc;
   plan->tile = ok ? pick : keep;
   plan->tile_set = ok ? !free_best : keep_set;
+  plan->tile_tuned = ok ? !free_best : keep_tuned;
   if (save) {
     hipMemcpyAsync(plan->t_d, save, clocks, hipMemcpyDeviceToDevice, s);
     hipMemcpyAsync(plan->dt_d, (char*)save + clocks, clocks, hipMemcpyDeviceToDevice, s);

@@ -514,5 +514,10 @@ def test_autotuning_keeps_the_faster_automatic_choice(T, sizes):
     plan.rk3(Ud, 8, T.LIM_MP, 1e-7, GAMMA, CFL, steps=3)
     want = ref.rk3(to_dev(U), 8, T.LIM_MP, 1e-7, GAMMA, CFL, steps=3)
     assert np.array_equal(to_host(Ud), to_host(want))
+    # one problem of the batch at a time: the same bits again
+    Us = to_dev(U)
+    for p in range(len(sizes)):
+        plan.rk3(Us, 8, T.LIM_MP, 1e-7, GAMMA, CFL, steps=3, first=p, count=1)
+    assert np.array_equal(to_host(Us), to_host(want))
     plan.close()
     ref.close()
