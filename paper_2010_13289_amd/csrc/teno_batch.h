@@ -153,10 +153,6 @@ __device__ __forceinline__ void batch_segment(const SegIn& g, const FaceParams& 
   __syncthreads();
   __builtin_amdgcn_s_setprio(0);
 
-  // Two faces a thread at eight points, one after the other: side by side they
-  // spill (119,661 segments of 63 cells, tile 2, us for four steps, smooth and
-  // rough data: 4740 -> 4634, 7136 -> 6928; constant states 1562 -> 1592).
-  constexpr int kUnroll = K == 8 ? 1 : FPT;
   int nface, ncell;
   {
     const int n = g.n;
@@ -164,7 +160,7 @@ __device__ __forceinline__ void batch_segment(const SegIn& g, const FaceParams& 
     ncell = wrap ? n : min(SEG - 1, n - g.c_begin);
     nface = wrap ? n : ncell + 1;
   }
-#pragma unroll kUnroll
+#pragma unroll
   for (int f = 0; f < FPT; ++f) {
     const int j = t + f * TPB;
     if (j < nface) {
