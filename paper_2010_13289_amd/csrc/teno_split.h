@@ -25,23 +25,32 @@ inline long tile_count(int axis, int nx, int ny, int nz) {
   return lines * ((across + kTileColumns - 1) / kTileColumns);
 }
 
+// Places a workgroup's chunk takes whose tile has f of 32 faces a line: half its
+// place, and half its share of wavefronts (of 8 faces of 8 lines).
+inline double chunk_cost(int f) { return 0.5 + 0.125 * ((f + 7) / 8); }
+
 // Cells per segment of a tile sweep.  Segments of 32 c - 1 cells take c
 // chunks (one redundant face each); a whole line hands its faces on instead.
 // More segments fill the chip and shorten the last round, fewer save the
-// redundant faces and halo rows.  The c with the smallest estimate of
-//   workgroups (chunks + 0.15) / slots + 0.7 (chunks of one workgroup + 0.15),
-// slots = workgroups the chip holds, is taken; the estimate's order agreed
-// with the measured sweeps (Euler, six points unless stated; one chunk, two,
-// four, in us): 1024^2 y 67, 71, 79; 2048^2 y 236, 229, 235; 187x150x93 y at
-// eight points 313, 302, 316 (the last whole lines).  The search ends
-// where the second term alone exceeds the best, so that enqueuing a long thin
-// grid's sweep does not take longer than the sweep (every c took 158 us for 10^6
-// cells).
+// redundant faces, halo rows and partly filled chunks.  The c with the smallest
+// estimate of
+//   workgroups (chunks + 0.05) / slots + 0.4 (chunks of one workgroup + 0.05),
+// slots = workgroups the chip holds, is taken; it agrees within 3 % with the best
+// of the measured sweeps (Euler, six points, y and z, smooth (rough) data, us; one
+// chunk, two, three, whole periodic lines): 64^3 51, 47, -, 46 (75, 65, -, 63);
+// 96^3 113, 114, -, 102 (179, 178, -, 162); 100^3 129, 129, 142, 144 (198, 199, 233,
+// 236); 128^3 216, 225, 228, 200 (351, 373, 371, 320); 187x150x93 257, 260, 271, 272
+// (411, 426, 433, 433); 1024^2 52, 53, 52, 162 (80, 83, 82, 225); 2048^2 166, 159,
+// 161, 312 (261, 256, 255, 443).  The search ends where the second term alone
+// exceeds the best, so that enqueuing a long thin grid's sweep does not take longer
+// than the sweep (every c took 158 us for 10^6 cells).
 inline double tile_segment_time(double lines, int n, int bc, int c, bool whole) {
-  constexpr double start = 0.15;
-  const long seg = 32l * c - 1, nseg = whole ? 1 : (n + seg - 1) / seg;
-  const double chunks = (n + (whole && bc == 0 ? 0 : nseg)) / (32.0 * nseg);
-  return lines * nseg * (chunks + start) / kFaceSlots + 0.7 * (c + start);
+  constexpr double start = 0.05;
+  auto chunks = [](long faces) { return (double)(faces / 32) + (faces % 32 ? chunk_cost((int)(faces % 32)) : 0.0); };
+  const long seg = whole ? n : 32l * c - 1, nseg = whole ? 1 : (n + seg - 1) / seg;
+  const double one = chunks(whole && bc == 0 ? n : seg + 1) + start;
+  const double last = chunks(whole && bc == 0 ? n : n - (nseg - 1) * seg + 1) + start;
+  return lines * ((nseg - 1) * one + last) / kFaceSlots + 0.4 * one;
 }
 
 inline int tile_segment(int axis, int n, int nx, int ny, int nz, int bc) {
@@ -56,7 +65,7 @@ inline int tile_segment(int axis, int n, int nx, int ny, int nz, int bc) {
       best_t = t;
       best = 32 * c - 1;
     }
-    if (0.7 * c > best_t) break;
+    if (0.4 * c > best_t) break;
   }
   return last == 1 || tile_segment_time(lines, n, bc, last, true) < best_t ? n : best;
 }
@@ -84,7 +93,7 @@ struct FaceSplit {
 // that are not square skip the limiter less often.
 inline double face_split_time(int nfl, long nlines, int K, const FaceSplit& s) {
   const int full = nfl / s.fj, rest = nfl - full * s.fj;
-  auto cost = [&](int f) { return 0.5 + 0.125 * ((f * s.tx + 63) / 64); };
+  auto cost = [&](int f) { return 0.5 + 0.125 * ((f * s.tx + 63) / 64); };  // as chunk_cost
   const double groups = (double)(nlines / s.width) * ((s.width + s.tx - 1) / s.tx);
   const double work = 1.0 + 0.1 * (s.fj + K - 1) * s.tx / 256.0 + 0.005 * (s.tx + 64.0 / s.tx - 16.0);
   return work * (groups * (full * cost(s.fj) + (rest ? cost(rest) : 0.0)) / kFaceSlots + 0.7);
