@@ -444,53 +444,67 @@ struct FacesParams {
   const double* U;
   double* Fhat;
   uint8_t* flags;
-  int axis, nx, ny, nz, bc;
+  int n, nfl, bc;  // cells and faces of a line; a periodic line's face n is its face 0
   int fj, tx;
   int width;  // lines of a row of workgroups (those of a plane, or all)
   int ncg;    // workgroups side by side in a row
   int nch;    // workgroups along a line
+  int div;    // y lines in one row: the lines of a plane, else 0
+  long step;          // between cells and between faces of a line
+  long crow, cline;   // first cell of a line: per row, per line of the row
+  long frow, fline;   // its face 0
+  long cdiv, fdiv;    // per plane before the line (div)
+  long N, nfaces;
   int fld[NF];
   FaceParams fp;
 };
 
-// Row, lines [l0, end) and chunk of workgroup b: side by side along a row, then its
-// chunks, then the rows, so that workgroups that share cache lines and halo rows
-// run close together (128^3 along y 100 us with the chunks first, 90 so).
+// Row, first line l0 of the row and chunk of workgroup b: side by side along a
+// row, then its chunks, then the rows, so that workgroups that share cache lines
+// and halo rows run close together (128^3 along y 100 us with the chunks first, 90
+// so).
 template <int NF>
-__device__ __forceinline__ void faces_block(const FacesParams<NF>& p, int b, int tx, int& row, int& l0, int& end,
-                                            int& chunk) {
+__device__ __forceinline__ void faces_block(const FacesParams<NF>& p, int b, int tx, int& row, int& l0, int& chunk) {
   row = b / (p.ncg * p.nch);
   const int r = b - row * (p.ncg * p.nch);
   chunk = r / p.ncg;
-  l0 = row * p.width + (r - chunk * p.ncg) * tx;
-  end = (row + 1) * p.width;
+  l0 = (r - chunk * p.ncg) * tx;
 }
 
-// Line l of the faces' axis, in row `row`, and the index of its face 0 with the
-// step along the axis.
+// Line l of row `row`, and the index of its face 0.
 template <int NF>
-__device__ __forceinline__ Line faces_line(const FacesParams<NF>& p, int row, int l, long& face, long& fstride) {
-  const int n = p.axis == 0 ? p.nx : (p.axis == 1 ? p.ny : p.nz);
-  if (p.axis == 0) {
-    face = (long)l * (p.nx + 1);
-    fstride = 1;
-    return Line{(long)l * p.nx, 1, n, p.bc};
+__device__ __forceinline__ Line faces_line(const FacesParams<NF>& p, int row, int l, long& face) {
+  long cell = row * p.crow + l * p.cline;
+  face = row * p.frow + l * p.fline;
+  if (p.div) {
+    const int z = l / p.div;
+    cell += z * p.cdiv;
+    face += z * p.fdiv;
   }
-  const long plane = (long)p.nx * p.ny;
-  if (p.axis == 2) {
-    face = l;
-    fstride = plane;
-    return Line{l, plane, n, p.bc};
+  return Line{cell, p.step, p.n, p.bc};
+}
+
+// What the host forms of the grid for the kernels (set_lines: rows of `width`
+// lines).
+template <int NF>
+void set_lines(FacesParams<NF>& p, int axis, int nx, int ny, int width) {
+  const long plane = (long)nx * ny;
+  p.width = width;
+  p.step = axis == 0 ? 1 : (axis == 1 ? nx : plane);
+  p.cline = axis == 0 ? nx : 1;
+  p.fline = axis == 0 ? nx + 1 : 1;
+  p.crow = width * p.cline;
+  p.frow = width * p.fline;
+  p.div = 0;
+  p.cdiv = p.fdiv = 0;
+  if (axis == 1 && width == nx) {
+    p.crow = plane;
+    p.frow = plane + nx;
+  } else if (axis == 1) {
+    p.div = nx;
+    p.cdiv = plane - nx;
+    p.fdiv = plane;
   }
-  long z = row;
-  int x = l - row * p.width;
-  if (p.width != p.nx) {  // a row of all lines
-    z = l / p.nx;
-    x = l - (int)z * p.nx;
-  }
-  face = x + (plane + p.nx) * z;
-  fstride = p.nx;
-  return Line{x + plane * z, p.nx, n, p.bc};
 }
 
 // Staged cells of a workgroup of k_faces: three of the largest fit in a CU's LDS.
@@ -503,37 +517,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFaceWaves)
 void k_faces(FacesParams<NF> p) {
   constexpr int NC = kFacesCells<NF, K>;
   __shared__ double stage[RowStage<NF>::NE * NC];
-  const int n = p.axis == 0 ? p.nx : (p.axis == 1 ? p.ny : p.nz);
-  const int nfl = p.bc == 0 ? n : n + 1;  // a periodic line's face n is its face 0
-  int row, l0, end, chunk;
-  faces_block(p, (int)blockIdx.x, CS ? CS : p.tx, row, l0, end, chunk);
+  int row, l0, chunk;
+  faces_block(p, (int)blockIdx.x, CS ? CS : p.tx, row, l0, chunk);
   const int j0 = chunk * p.fj;
-  const int nfk = min(p.fj, nfl - j0);
+  const int nfk = min(p.fj, p.nfl - j0);
   // This thread's place, formed anew before and after the face (an opaque copy
-  // of the thread index): held across it would be spilled.
+  // of the thread index): held across it would be spilled (a scalar face holds it).
   struct Where {
     int tx, t, f, col;
   };
   auto where = [&]() {
     Where w;
     int tt = threadIdx.x;
-    asm volatile("" : "+v"(tt));
+    if constexpr (NF > 1) asm volatile("" : "+v"(tt));
     w.tx = CS ? CS : p.tx;
     w.t = tt;
     w.f = tt / w.tx;
     w.col = tt - w.f * w.tx;
     return w;
   };
-  long face, fstride;
+  long face;
   __builtin_amdgcn_s_setprio(3);  // high while loads and stores issue, as in the sweeps
   {
     const Where w = where();
-    const Line L = faces_line<NF>(p, row, min(l0 + w.col, end - 1), face, fstride);  // beyond the row: its last line
-    const long N = (long)p.nx * p.ny * p.nz;
+    const Line L = faces_line<NF>(p, row, min(l0 + w.col, p.width - 1), face);  // beyond the row: its last line
     const int frows = 256 / w.tx;
     if (w.f < frows)
       for (int r = w.f; r < nfk + K - 1; r += frows)
-        stage_cell<NF>(stage, NC, r * w.tx + w.col, p.U, p.fld, p.fp.gamma, N, cell_at(L, j0 - K / 2 + r));
+        stage_cell<NF>(stage, NC, r * w.tx + w.col, p.U, p.fld, p.fp.gamma, p.N, cell_at(L, j0 - K / 2 + r));
   }
   __syncthreads();
   __builtin_amdgcn_s_setprio(0);
@@ -547,11 +558,11 @@ void k_faces(FacesParams<NF> p) {
   }
   __builtin_amdgcn_s_setprio(3);
   const Where w = where();
-  if (l0 + w.col >= end) return;
-  faces_line<NF>(p, row, l0 + w.col, face, fstride);
-  const long nfaces = (long)p.nx * p.ny * p.nz / n * (n + 1);
+  if (l0 + w.col >= p.width) return;
+  faces_line<NF>(p, row, l0 + w.col, face);
+  const long nfaces = p.nfaces;
   auto store = [&](int j) {
-    const long at = face + (long)j * fstride;
+    const long at = face + j * p.step;
 #pragma unroll
     for (int q = 0; q < NF; ++q) {
       p.Fhat[(long)p.fld[q] * nfaces + at] = F[q];
@@ -562,7 +573,7 @@ void k_faces(FacesParams<NF> p) {
     }
   };
   store(j0 + w.f);
-  if (j0 + w.f == 0 && nfl == n) store(n);
+  if (j0 + w.f == 0 && p.nfl == p.n) store(p.n);
 }
 
 // The same for grids that leave the chip part empty, where the time is one
@@ -574,19 +585,16 @@ __global__ __launch_bounds__(64 * NF) void k_faces_fields(FacesParams<NF> p) {
   constexpr int FJ = 64 / TX, NC = (FJ + K - 1) * TX;
   __shared__ double stage[RowStage<NF>::NE * NC];
   __shared__ double fcs[NF * 64];
-  const int n = p.axis == 0 ? p.nx : (p.axis == 1 ? p.ny : p.nz);
-  const int nfl = p.bc == 0 ? n : n + 1;  // a periodic line's face n is its face 0
-  const long N = (long)p.nx * p.ny * p.nz;
-  int row, l0, end, chunk;
-  faces_block(p, (int)blockIdx.x, TX, row, l0, end, chunk);
+  int row, l0, chunk;
+  faces_block(p, (int)blockIdx.x, TX, row, l0, chunk);
   const int j0 = chunk * FJ;
-  const int nfk = min(FJ, nfl - j0);
+  const int nfk = min(FJ, p.nfl - j0);
   const int t = threadIdx.x, q = threadIdx.y, col = t % TX, f = t / TX;
-  long face, fstride;
-  for (int c = q * 64 + t; c < (nfk + K - 1) * TX; c += 64 * NF) {
-    const Line L = faces_line<NF>(p, row, min(l0 + c % TX, end - 1), face, fstride);
-    stage_cell<NF>(stage, NC, c, p.U, p.fld, p.fp.gamma, N, cell_at(L, j0 - K / 2 + c / TX));
-  }
+  // every c of a thread is one column's: 64 NF is a multiple of TX
+  long face;
+  const Line L = faces_line<NF>(p, row, min(l0 + col, p.width - 1), face);
+  for (int c = q * 64 + t; c < (nfk + K - 1) * TX; c += 64 * NF)
+    stage_cell<NF>(stage, NC, c, p.U, p.fld, p.fp.gamma, p.N, cell_at(L, j0 - K / 2 + c / TX));
   __syncthreads();
   StagedCells<NF, K, TX, true> prov{stage, NC, min(f, nfk - 1) * TX + col};
   RoeFrame<NF> fr;
@@ -601,11 +609,10 @@ __global__ __launch_bounds__(64 * NF) void k_faces_fields(FacesParams<NF> p) {
   double F = Fh[0];
 #pragma unroll
   for (int i = 1; i < NF; ++i) F = q == i ? Fh[i] : F;
-  if (f >= nfk || l0 + col >= end) return;
-  faces_line<NF>(p, row, l0 + col, face, fstride);
-  const long nfaces = N / n * (n + 1);
+  if (f >= nfk || l0 + col >= p.width) return;
+  const long nfaces = p.nfaces;
   auto store = [&](int j) {
-    const long at = face + (long)j * fstride;
+    const long at = face + j * p.step;
     p.Fhat[(long)p.fld[q] * nfaces + at] = F;
     if constexpr (FLAGS) {
       p.flags[(long)q * nfaces + at] = (uint8_t)bits[0];
@@ -613,7 +620,7 @@ __global__ __launch_bounds__(64 * NF) void k_faces_fields(FacesParams<NF> p) {
     }
   };
   store(j0 + f);
-  if (j0 + f == 0 && nfl == n) store(n);
+  if (j0 + f == 0 && p.nfl == p.n) store(p.n);
 }
 
 // ---------------------------------------------------------------------------
@@ -810,20 +817,20 @@ hipError_t launch_faces(const FacesLaunch& a) {
   p.U = a.U;
   p.Fhat = a.Fhat;
   p.flags = a.flags;
-  p.axis = a.axis;
-  p.nx = a.nx;
-  p.ny = a.ny;
-  p.nz = a.nz;
   p.bc = a.bc;
   p.fp = a.fp;
   for (int q = 0; q < NF; ++q) p.fld[q] = a.fld[q];
   const int n = a.axis == 0 ? a.nx : (a.axis == 1 ? a.ny : a.nz);
   const int nfl = a.bc == 0 ? n : n + 1;
   const long nlines = (long)a.nx * a.ny * a.nz / n;
+  p.n = n;
+  p.nfl = nfl;
+  p.N = nlines * n;
+  p.nfaces = nlines * (n + 1);
   if (NF == 3 && nlines != 1) return hipErrorInvalidValue;
   const int across = a.axis == 0 ? a.ny : a.nx;
   auto take = [&](int width, int fj, int tx) {  // workgroups of fj faces of tx lines of a row
-    p.width = width;
+    set_lines(p, a.axis, a.nx, a.ny, width);
     p.fj = fj;
     p.tx = tx;
     p.ncg = (width + tx - 1) / tx;
@@ -844,7 +851,14 @@ hipError_t launch_faces(const FacesLaunch& a) {
       return hipGetLastError();
     }
   }
-  const FaceSplit sp = face_split(nfl, across, nlines, K, kFacesCells<NF, K>);
+  FaceSplit sp = face_split(nfl, across, nlines, K, kFacesCells<NF, K>);
+  if constexpr (NF == 1) {
+    // a scalar face is a few loads and stores, which other widths only scatter
+    // (80x70x60 along y 8.0 us, 6.6 by 32 x 8): the split only where the launch
+    // would be too large
+    const FaceSplit plain{across, 32, kTileColumns};
+    if (nlines > 1 && take(plain.width, plain.fj, plain.tx) < 1l << 24) sp = plain;
+  }
   const long blocks = take(sp.width, sp.fj, sp.tx);
   if (blocks >= 1l << 24) return hipErrorInvalidValue;  // 2^32 threads; the split keeps 2^31 cells below
   const dim3 gr((unsigned)blocks);
@@ -860,6 +874,8 @@ hipError_t launch_faces(const FacesLaunch& a) {
   } else {
     if (p.tx == kTileColumns)
       go(std::integral_constant<int, kTileColumns>());
+    else if (NF == 1 && nlines == 1)
+      go(std::integral_constant<int, NF == 1 ? 1 : 0>());
     else
       go(std::integral_constant<int, 0>());
   }
