@@ -2,7 +2,8 @@
 //
 //  k_faces         face fluxes (and optionally the smoothness flags) of one
 //                  axis from staged tiles.  The unit the reconstruct_faces
-//                  call exposes.
+//                  call exposes, with k_faces_direct (from global memory) and
+//                  k_faces_fields (one wavefront per field) on smaller grids.
 //  k_sweep_row     sweep along x (unit stride).  A 256-thread workgroup owns
 //                  one row segment: the segment's cells are staged in LDS
 //                  with their flux, signal speed and Roe inputs, each thread
@@ -576,6 +577,66 @@ void k_faces(FacesParams<NF> p) {
   if (j0 + w.f == 0 && p.nfl == p.n) store(p.n);
 }
 
+// The cells of face j of a line straight from global memory.
+template <int NF, int K>
+struct GridCells {
+  static constexpr bool kReread = false;  // again from memory
+  const double* __restrict__ U;
+  long N;
+  const int* fld;
+  Line L;
+  int j;
+  double gamma;
+  __device__ __forceinline__ void load(int pos, double (&X)[NF]) const {
+    const long cell = cell_at(L, pos);
+#pragma unroll
+    for (int q = 0; q < NF; ++q) X[q] = U[fld[q] * N + cell];
+  }
+  __device__ __forceinline__ void cell(int m, double (&X)[NF], double (&F)[NF], double& lam) const {
+    load(j - K / 2 + m, X);
+    cell_physics<NF>(X, gamma, F, lam);
+  }
+  __device__ __forceinline__ void roe(int s, RoeIn<NF>& r) const {
+    double X[NF];
+    load(j - 1 + s, X);
+    roe_input<NF>(X, gamma, r);
+  }
+};
+
+// The same, one thread per face straight from global memory, for grids of at most
+// two wavefronts per SIMD (faces_direct): no staging, no barrier and no branch, so
+// that one wavefront's operations overlap, and the time does not depend on the
+// data.  Threads run along x, or along the line on axis 0.  Bound by the latency of
+// a face; at eight points compiled for one wavefront per SIMD where there is one
+// (40x40x39 12.1 us, 13.4 by the 256 registers of two).  40x40x39, transmissive, us at six (eight) points: staged 12 to 16 (19 to
+// 21), so 8.3 (12.1); 100x100x12 along z 17.4 to 19.9 (24.5 to 27) and 13.8 (23.5).
+template <int NF, int K, int LIM, bool ADAPT, bool FLAGS, int WAVES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_faces_direct(FacesParams<NF> p) {
+  const int t = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (t >= p.nch) return;  // the faces of all lines
+  const int r = t / p.width, row = r / p.nfl, j = r - row * p.nfl;
+  long face;
+  const Line L = faces_line<NF>(p, row, t - r * p.width, face);
+  GridCells<NF, K> prov{p.U, p.N, p.fld, L, j, p.fp.gamma};
+  double F[NF];
+  uint32_t bits[2][NF];
+  face_flux<NF, K, LIM, ADAPT, FLAGS>(prov, p.fp, F, bits);
+  const long nfaces = p.nfaces;
+  auto store = [&](int jj) {
+    const long at = face + jj * p.step;
+#pragma unroll
+    for (int q = 0; q < NF; ++q) {
+      p.Fhat[(long)p.fld[q] * nfaces + at] = F[q];
+      if constexpr (FLAGS) {
+        p.flags[(long)q * nfaces + at] = (uint8_t)bits[0][q];
+        p.flags[(long)(NF + q) * nfaces + at] = (uint8_t)bits[1][q];
+      }
+    }
+  };
+  store(j);
+  if (j == 0 && p.nfl == p.n) store(p.n);
+}
+
 // The same for grids that leave the chip part empty, where the time is one
 // workgroup's chain: one wavefront per characteristic field takes 64 faces (64 /
 // TX of TX lines), wave q stores component q.  288 cells at eight points 11.8 ->
@@ -860,6 +921,25 @@ hipError_t launch_faces(const FacesLaunch& a) {
     if (nlines > 1 && take(plain.width, plain.fj, plain.tx) < 1l << 24) sp = plain;
   }
   const long blocks = take(sp.width, sp.fj, sp.tx);
+  if constexpr (NF > 3) {
+    if (faces_direct(a.axis, a.bc, nfl, nlines, K, a.flags != nullptr, sp)) {
+      set_lines(p, a.axis, a.nx, a.ny, a.axis == 0 ? 1 : (a.axis == 1 ? a.nx : (int)nlines));
+      p.nch = (int)(nlines * nfl);
+      const dim3 gr((unsigned)((nlines * nfl + 255) / 256));
+      auto go = [&](auto waves) {
+        constexpr int WAVES = decltype(waves)::value;
+        if (a.flags)
+          hipLaunchKernelGGL((k_faces_direct<NF, K, LIM, ADAPT, true, WAVES>), gr, dim3(256), 0, a.stream, p);
+        else
+          hipLaunchKernelGGL((k_faces_direct<NF, K, LIM, ADAPT, false, WAVES>), gr, dim3(256), 0, a.stream, p);
+      };
+      if (K == 8 && nlines * nfl <= kWaveFaces)
+        go(std::integral_constant<int, K == 8 ? 1 : 2>());
+      else
+        go(std::integral_constant<int, 2>());
+      return hipGetLastError();
+    }
+  }
   if (blocks >= 1l << 24) return hipErrorInvalidValue;  // 2^32 threads; the split keeps 2^31 cells below
   const dim3 gr((unsigned)blocks);
   auto go = [&](auto cs) {

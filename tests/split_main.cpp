@@ -70,6 +70,22 @@ int main() {
       std::printf("row_sweep_x(%d, %d, %d, %d) is %d\n", x.nx, x.ny, x.nz, x.bc, !x.row);
       ++bad;
     }
+  // faces straight from global memory: up to one wavefront per SIMD, and two where
+  // the split's lines are few or its chunks all touch a transmissive end
+  struct { int axis, n, bc; long nlines; int across, K; bool direct; } fs[] = {{0, 40, 0, 1600, 40, 6, true},
+      {2, 39, 1, 1600, 40, 8, true},   {0, 50, 0, 2500, 50, 6, false},  {1, 50, 0, 2500, 50, 6, true},
+      {1, 50, 0, 2500, 50, 8, false},  {2, 12, 1, 10000, 100, 6, true}, {2, 12, 1, 10000, 100, 8, true},
+      {0, 12, 1, 10000, 100, 8, false}, {2, 45, 1, 1892, 44, 6, true},  {2, 45, 1, 1892, 44, 8, false},
+      {1, 48, 0, 2304, 48, 6, false},  {1, 340, 1, 340, 340, 6, false}, {2, 64, 0, 4096, 64, 6, false},
+      {0, 60000, 1, 1, 1, 6, false},   {1, 20, 1, 100000, 1000, 6, false}};
+  for (const auto& x : fs) {
+    const int nfl = x.bc ? x.n + 1 : x.n;
+    const FaceSplit s = face_split(nfl, x.across, x.nlines, x.K, 416);
+    if (faces_direct(x.axis, x.bc, nfl, x.nlines, x.K, true, s) != x.direct) {
+      std::printf("faces_direct(%d, %d, %d, %ld, %d) is %d\n", x.axis, x.bc, nfl, x.nlines, x.K, !x.direct);
+      ++bad;
+    }
+  }
   // a long thin grid: a thousand choices of 0.65 ms each by trying every count
   const std::clock_t t0 = std::clock();
   for (int i = 0; i < 1000; ++i) check_thin = check_thin + tile_segment(0, 4000000 + i, 4000000 + i, 9, 1, 1);

@@ -361,6 +361,18 @@ def test_faces_of_the_most_short_lines(T):
     torch.cuda.empty_cache()
 
 
+# Grids whose faces run straight from global memory on some axis: just above the
+# one-wavefront-per-field kernel, on both sides of 65,536 and of 131,072 faces.
+DIRECT_FACES = [((39, 40, 40), 6, 3), ((40, 39, 40), 8 | 0x100, 1), ((250, 259), 8, 2), ((256, 257), 6, 4),
+                ((32, 41, 50), 6, 0), ((50, 51, 50), 6, 6), ((50, 49, 51), 8, 8), ((13, 94, 100), 8 | 0x100, 3)]
+
+
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("shape,K,lim", DIRECT_FACES, ids=["x".join(map(str, c[0])) + f"-{c[1]}-{c[2]}" for c in DIRECT_FACES])
+def test_direct_faces_agree_with_blocks_of_lines(T, shape, K, lim, bc):
+    test_face_splits_agree_with_blocks_of_lines(T, shape, K, lim, bc)
+
+
 # Runs of one state whose faces are not finite (negative pressure, vacuum, NaN,
 # overflow) or extreme, with a cutoff that no constant stencil passes: a long line,
 # whose wavefronts take constant states at once, against a short one, which does
