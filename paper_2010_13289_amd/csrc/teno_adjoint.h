@@ -1103,7 +1103,8 @@ struct VjpOut {
 
 // Occupancy the tile kernel is compiled for: 3 wavefronts per SIMD (at most
 // 168 VGPRs; three 4-wavefront blocks of 46 KB LDS per CU), measured 20%
-// faster than 2 although four fields then spill 20 to 36 bytes; the 5-field
+// faster than 2 at six points although four fields then spill 20 to 36 bytes a
+// lane (at eight points 164 to 188, three fields 12 to 28); the 5-field
 // tile (65 KB LDS, two blocks per CU) cannot reach 3 and keeps 256 VGPRs.
 template <int NF>
 struct VjpOccupancy {
@@ -1376,11 +1377,14 @@ __global__ __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(VjpOccu
 // Nothing crosses wavefronts, so there is no barrier, and the order of every
 // sum is fixed.  Blocks on one XCD (blockIdx mod 8) take consecutive lines, so
 // the lines of a strided axis that share cache lines meet in one L2.
-// Bound by VALU issue and, on smooth data, by the latency of the loads.  2D
-// 1024^2 at six points, both axes: one field per wavefront, every field
-// reversed in full, 519 us; this, 393 us on a
-// moving smooth state, 180 where the acoustic fields are flat; 72x64x56 318 -> 141 us
-// an axis.
+// Bound by VALU issue and, on smooth data, by the latency of the loads, at two
+// wavefronts per SIMD or fewer: in 3D by the LDS of a workgroup of one wavefront
+// (22.7 KB at six points, 7 workgroups per CU; 146 to 159 VGPRs would allow three
+// per SIMD), in 2D by the LDS (18.8 KB, 8 per CU) as much as by the registers (166
+// to 179; at eight points up to 256, MP spills 12 to 108 bytes a lane).  2D 1024^2
+// at six points, both axes: one field per wavefront, every field reversed in full,
+// 519 us; this, 393 us on a moving smooth state, 180 where the acoustic fields are
+// flat; 72x64x56 318 -> 141 us an axis.
 template <int NF, int K, int LIM, bool ADAPT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_vjp_wave(
     const double* __restrict__ U, const double* __restrict__ Lbar, VjpOut vo, VjpAxis ax, VjpTiles tl, int fld0,

@@ -606,10 +606,12 @@ struct GridCells {
 // The same, one thread per face straight from global memory, for grids of at most
 // two wavefronts per SIMD (faces_direct): no staging, no barrier and no branch, so
 // that one wavefront's operations overlap, and the time does not depend on the
-// data.  Threads run along x, or along the line on axis 0.  Bound by the latency of
-// a face; at eight points compiled for one wavefront per SIMD where there is one
-// (40x40x39 12.1 us, 13.4 by the 256 registers of two).  40x40x39, transmissive, us at six (eight) points: staged 12 to 16 (19 to
-// 21), so 8.3 (12.1); 100x100x12 along z 17.4 to 19.9 (24.5 to 27) and 13.8 (23.5).
+// data.  Threads run along x, or along the line on axis 0.  Bound by the latency
+// of a face; at eight points compiled for one wavefront per SIMD where there is
+// one (40x40x39 11.5 us, 13.4 by the 256 registers of two, which in 3D spill 12 to
+// 60 bytes a lane, TVD5 with flags 216).  40x40x39, transmissive, us at six
+// (eight) points: staged 12 to 16 (19 to 21), so 8.2 (11.5); 100x100x12 along z
+// 17.4 to 19.9 (24.5 to 27) and 13.7 (21.3).
 template <int NF, int K, int LIM, bool ADAPT, bool FLAGS, int WAVES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_faces_direct(FacesParams<NF> p) {
   const int t = (int)(blockIdx.x * 256 + threadIdx.x);
@@ -1007,7 +1009,8 @@ hipError_t launch_sweep(const SweepLaunch& a) {
   return hipGetLastError();
 }
 
-// Tile sweep of axis 1 or 2: one workgroup per (line, group of TX columns).
+// Tile sweep of any axis: one workgroup per segment (tile_segment) of TX adjacent
+// lines.
 template <int NF, int K, int LIM, bool ADAPT>
 hipError_t launch_tile(const SweepLaunch& a) {
   SweepParams<NF> p;

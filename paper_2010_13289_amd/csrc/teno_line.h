@@ -238,8 +238,9 @@ struct LineCells {
   __device__ __forceinline__ double value(int m) const { return s[cell_at(L, j - K / 2 + m)]; }
 };
 
-// Bound by latency.  A step of 200 cells at six points (MP): 7.0 us, 9.6 a call
-// where ten follow each other, 14.8 by three launches.
+// Bound by latency.  A step of 200 cells at six points (MP): 3.8 us in the kernel;
+// 9.3 a call where calls follow each other, which is the host's enqueue (14.8 by
+// three launches), 3.9 in a graph.
 template <int K, int LIM, bool ADAPT>
 __global__ __launch_bounds__(kLineScalar) void k_step_line_scalar(LineStep p) {
   __shared__ double sU[kLineScalar], Fs[kLineScalar];

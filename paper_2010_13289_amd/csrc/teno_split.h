@@ -6,7 +6,9 @@
 namespace tenom {
 
 // Waves per SIMD the face, row and tile kernels are compiled for: at most 168
-// VGPRs, and three tiles fit in a CU's LDS.
+// VGPRs, and three tiles fit in a CU's LDS.  None of them spills at six points; at
+// eight TVD5 and the adaptive cutoff do (12 to 44 bytes a lane; the 1D faces, most
+// with flags, 12 to 92), which still beats two wavefronts (256^3 x 1573 us, 1394 so).
 constexpr int kFaceWaves = 3;
 
 // Workgroups of 256 threads the chip holds at kFaceWaves (256 CUs, one
@@ -132,17 +134,19 @@ constexpr long kWaveFaces = 65536;
 
 // Whether one thread per face straight from global memory takes the Euler faces of
 // a 2D or 3D grid (which are too many for one wavefront per field) instead of the
-// split s.  It fills one wavefront per SIMD with kWaveFaces and costs as much below;
-// two with twice that.  us, that and the split, smooth (rough) data, with flags,
-// six points unless stated: one wavefront, 40^3 periodic 8.5 and 9.7 (8.5 and 14.7),
-// at eight points 12.4 and 14.5 (12.1 and 21).  Two, well filled, along y and z, where
-// the split's lines are few side by side and flags are stored: 50^3 13.8 and 14.1
-// (13.8 and 19.0), at eight points 22 and 17.6 (no), without flags 13.2 and 11.5 (no); or where every chunk has a face of a transmissive
-// end, which is rough as soon as the state has a slope there: 50^3 13.8 and 18.3
-// (13.8 and 19.0), at eight points 22 and 23.4 (22 and 24.1), 44x43x45 13.2 and 15.6
-// (13.1 and 16.0), at eight points 21.6 and 20.8 (no).  Elsewhere it loses on smooth
-// data what it gains on rough: 48^3 13.6 and 12.5 (13.6 and 19.2), 360x360 11.6 and
-// 10.4 (11.6 and 16.0), 1394x130 along y 16.4 and 16.0 (16.4 and 22.9).
+// split s.  It fills one wavefront per SIMD with kWaveFaces and costs as much
+// below; two with twice that.  us, that and the split, smooth (rough) data, with
+// flags, six points unless stated: one wavefront, 40^3 periodic 8.5 and 9.7 (8.5
+// and 14.7), at eight points 12.4 and 14.5 (12.1 and 21); 40x40x39 transmissive
+// 11.5 and 19.  Two, well filled, along y and z, where the split's lines are few
+// side by side and flags are stored: 50^3 13.8 and 14.1 (13.8 and 19.0), at eight
+// points 22 and 17.6 (no), without flags 13.2 and 11.5 (no); or where every chunk
+// has a face of a transmissive end, which is rough as soon as the state has a
+// slope there: 50^3 13.8 and 18.3 (13.8 and 19.0), at eight points 22 and 23.4 (22
+// and 24.1), 44x43x45 13.2 and 15.6 (13.1 and 16.0), at eight points 21.6 and 20.8
+// (no).  Elsewhere it loses on smooth data what it gains on rough: 48^3 13.6 and
+// 12.5 (13.6 and 19.2), 360x360 11.6 and 10.4 (11.6 and 16.0), 1394x130 along y
+// 16.4 and 16.0 (16.4 and 22.9).
 inline bool faces_direct(int axis, int bc, int nfl, long nlines, int K, bool flags, const FaceSplit& s) {
   const long faces = nlines * nfl;
   if (nlines == 1 || faces > 2 * kWaveFaces) return false;

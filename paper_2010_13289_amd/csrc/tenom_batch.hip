@@ -79,18 +79,19 @@ const RowFn kRow[kNumTiles] = {tenom_batch_row_tile0, tenom_batch_row_tile1, ten
                                tenom_batch_row_tile3, tenom_batch_row_tile4, tenom_batch_row_tile5};
 
 // The kernel of a batch whose tile nobody chose, by its number of segments of 63
-// cells.  Up to kFieldsSegments one wavefront per field: us a graph step, that
-// and tile 3, Riemann problems at eight points (MP; rough data in brackets):
-// 172 segments 24.0 and 36.5 (24.4 and 36.8), 598 29.5 and 36.9 (33.2 and 37.6),
-// 1300 37.3 and 46.3 (45.5 and 50.4), 2530 53.0 and 50.2 (67.0 and 66.0), 5100 83
-// and 64 (115 and 110); six points cross between the same counts.  Up to
+// cells.  Up to kFieldsSegments one wavefront per field: us a graph step, that and
+// tile 3, Riemann problems at eight points (MP; rough data in brackets): 172
+// segments 24.0 and 36.5 (24.4 and 36.8), 598 29.5 and 36.9 (33.2 and 37.6), 1300
+// 37.3 and 46.3 (45.5 and 50.4), 2530 53.0 and 50.2 (67.0 and 66.0), 5100 83 and
+// 64 (115 and 110); six points cross between the same counts.  Up to
 // kSmallTileSegments tile 0, whose small segments leave the constant states to
 // themselves and fill the last round: 35,421 segments 137 us, tile 2 137, tile 3
 // 152 (478, 520, 479).  Above, the pass is bound by HBM where the states are
-// constant, and tile 2 has twice the loads in flight per wavefront: 119,661
-// segments 396 us, tile 0 435, tile 3 470 (rough everywhere 1690, 1640, 1600, and
-// 1690 by tile 3 before constant states had a path of their own; smooth moving
-// states 1140, 1080, 1110): a caller with such data asks the autotuner.
+// constant, and tile 2 has twice the loads in flight per wavefront (at eight
+// points it spills 52 to 60 bytes a lane): 119,661 segments 396 us, tile 0 435,
+// tile 3 470 (rough everywhere 1690, 1640, 1600, and 1690 by tile 3 before
+// constant states had a path of their own; smooth moving states 1140, 1080, 1110):
+// a caller with such data asks the autotuner.
 constexpr int kFieldsSegments = 1536;
 constexpr int kSmallTileSegments = 65536;
 

@@ -11,7 +11,11 @@ on the method's work); given the measured share of the data, its bounds
 (or TVD flux) are counted once per reconstruction with a nonsmooth
 candidate (a fraction `rough` of the reconstructions) and the clamp once
 per nonsmooth candidate (`nonsmooth` per reconstruction on average).  The
-roofline fractions use the measured counts.
+roofline fractions use the measured counts.  They are rates of the method's
+work, not the utilisation of the units: a wavefront whose candidates are
+provably all smooth assembles one linear form and skips the weights and the
+cutoff, which are counted (256^3 x sweep, six points: 1,838 operations a face
+counted, about 1,480 executed).
 
 Every item is a formula in the structure of the scheme (number of points K,
 candidate stencil widths, fields, dimensions), written next to the step it
