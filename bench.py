@@ -75,11 +75,11 @@ BYTES_PER_CELL_STEP = O.rk3_bytes_per_cell(5)
 # by 2.0 and WRITE_SIZE by 1.0, the factors a plain 1 GiB device copy reads
 # as).  They describe the kernels built from the sources whose digest is
 # TRAFFIC_SOURCE_DIGEST and are reported as null for any other build.
-TRAFFIC_SOURCE_DIGEST = "f1ad81795e2bae43e32b2d8bd0cd5ce94b071b5a0e37fbbadc665001cc3664a1"
-MEASURED_TRAFFIC = {"sweep_x": 1.4676e+09, "sweep_y": 2.0386e+09, "sweep_z": 2.6432e+09}
+TRAFFIC_SOURCE_DIGEST = "ab4688ab6edd9d1ca0701cbc0f71d7f5e73afb6b48c0fef52e11fef02c97961b"
+MEASURED_TRAFFIC = {"sweep_x": 1.4672e+09, "sweep_y": 2.0386e+09, "sweep_z": 2.6410e+09}
 # batched sweep, 4096 problems, averaged over the stages, per tile shape
 # (64x1, 128x1, 128x2, 256x1, 256x2, 512x1): smaller tiles re-read more halo
-MEASURED_TRAFFIC_BATCH = (1.2804e9, 1.1552e9, 1.1387e9, 1.0948e9, 1.1285e9, 1.0553e9)
+MEASURED_TRAFFIC_BATCH = (1.2805e9, 1.1552e9, 1.1387e9, 1.0949e9, 1.1286e9, 1.0553e9)
 TRAFFIC_NOTE = ("recorded, not measured in this run: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE of this benchmark "
                 "on the kernel sources whose digest is TRAFFIC_SOURCE_DIGEST (null for any other build); "
                 "see the profiles directory")
