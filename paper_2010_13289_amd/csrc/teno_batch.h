@@ -69,7 +69,7 @@ __device__ __forceinline__ bool tame_state(const double (&X)[3], double gamma) {
 
 // One segment, staged in LDS (`stage`: at least RowStage<NF>::NE *
 // (TPB * FPT + K - 1) doubles; `Fs`: the faces' fluxes, NF * (TPB * FPT + 1)
-// doubles).  Every thread of the workgroup calls it; both arrays may be
+// doubles).  Every thread of the workgroup calls it; the arrays may be
 // rewritten once every thread has returned.  `g` may live in LDS: its fields
 // are read where they are used, so that nothing of it is held through the
 // face.
@@ -80,8 +80,17 @@ __device__ __forceinline__ bool tame_state(const double (&X)[3], double gamma) {
 // same bits, bound by HBM; the others are bound by VALU issue.  Batched graph,
 // 4096 problems of 256 to 16384 cells, 10 steps: 14.2 ->
 // 10.1 ms; persistent launch of 300: 6.5 -> 3.7.
-template <int NF, int K, int LIM, bool ADAPT, int TPB, int FPT>
-__device__ __forceinline__ void batch_segment(const SegIn& g, const FaceParams& fp, double* stage, double* Fs) {
+//
+// `votes` (TPB / 64 ints) holds which wavefronts found a differing cell; it may
+// be Fs unless EARLY.  With EARLY a wavefront that did stages its cells before
+// the barrier of the votes, so that a segment in which all did needs no further
+// one: the persistent launch, whose time is a chain of segments, 300 problems of
+// 256 to 16384 cells at eight points, four steps, Riemann 1422 -> 1360 us, smooth
+// 4907 -> 4798, rough 6724 -> 6534.  The sweeps, whose workgroups overlap, lose up
+// to 1 % on Riemann data by it (the graph of 4096 problems 3316 -> 3342).
+template <int NF, int K, int LIM, bool ADAPT, int TPB, int FPT, bool EARLY>
+__device__ __forceinline__ void batch_segment(const SegIn& g, const FaceParams& fp, double* stage, double* Fs,
+                                              int* votes) {
   constexpr int SEG = BatchTile<TPB, FPT>::FACES;  // faces per workgroup
   constexpr int NC = SEG + K - 1;                  // staged cells
   constexpr int NL = (NC + TPB - 1) / TPB;         // cells staged per thread
@@ -121,14 +130,21 @@ __device__ __forceinline__ void batch_segment(const SegIn& g, const FaceParams& 
 #pragma unroll
       for (int q = 0; q < NF; ++q) differ |= __double_as_longlong(X[i][q]) != __double_as_longlong(ref[q]);
     differ |= !tame_state(ref, fp.gamma);
-    double* votes = Fs;  // one per wavefront
     const bool any = __builtin_amdgcn_ballot_w64(differ) != 0;  // over the whole wavefront
-    if ((t & 63) == 0) votes[t >> 6] = any ? 1.0 : 0.0;
-    __syncthreads();
-    bool flat = true;
+    if ((t & 63) == 0) votes[t >> 6] = any ? 1 : 0;
+    auto put = [&]() {
 #pragma unroll
-    for (int w = 0; w < NW; ++w) flat &= votes[w] == 0.0;
-    if (flat) {
+      for (int i = 0; i < NL; ++i) {
+        const int c = t + i * TPB;
+        if (c < nstage) stage_put<NF>(stage, NC, c, X[i], fp.gamma);
+      }
+    };
+    if (EARLY && any) put();
+    __syncthreads();
+    int differing = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) differing += votes[w];
+    if (differing == 0) {
       const double b = g.b, dt = g.dt;
       double* Uout = g.Uout;
 #pragma unroll
@@ -144,13 +160,11 @@ __device__ __forceinline__ void batch_segment(const SegIn& g, const FaceParams& 
       }
       return;
     }
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int c = t + i * TPB;
-      if (c < nstage) stage_put<NF>(stage, NC, c, X[i], fp.gamma);
+    if (!EARLY || differing < NW) {  // uniform across the workgroup
+      if (!EARLY || !any) put();
+      __syncthreads();
     }
   }
-  __syncthreads();
   __builtin_amdgcn_s_setprio(0);
 
   int nface, ncell;
@@ -219,7 +233,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(3))) void k
   g.c_begin = sg.y;
   g.total = p.total;
   g.bc = p.bc;
-  batch_segment<NF, K, LIM, ADAPT, TPB, FPT>(g, p.fp, stage, Fs);
+  batch_segment<NF, K, LIM, ADAPT, TPB, FPT, false>(g, p.fp, stage, Fs, (int*)Fs);
 }
 
 // Signal rate (|u| + c)/dx of one 1D Euler cell (the CFL condition, Sec. 4).
@@ -313,6 +327,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   constexpr int NC = SEG + K - 1;
   __shared__ double stage[RowStage<NF>::NE * NC];
   __shared__ double Fs[NF * (SEG + 1)];
+  __shared__ int votes[TPB / 64];
   __shared__ unsigned long long rate;
   // The walk over (problem, step, stage, segment) is one loop; its four
   // counters are the only values carried from pass to pass (the arguments
@@ -385,7 +400,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     long off = 0;
     asm volatile("" : "+s"(off));
     const PersistParams& pe = *(const PersistParams*)((const char*)&p + off);
-    batch_segment<NF, K, LIM, ADAPT, TPB, FPT>(g, pe.fp, stage, Fs);
+    batch_segment<NF, K, LIM, ADAPT, TPB, FPT, true>(g, pe.fp, stage, Fs, votes);
     if (done && threadIdx.x == 0) take(pe);
     // the next pass rewrites g and the staging array, and when it begins a
     // new stage (or step, or problem) it reads what every thread of the
