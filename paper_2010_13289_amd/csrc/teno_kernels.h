@@ -914,17 +914,10 @@ hipError_t launch_faces(const FacesLaunch& a) {
       return hipGetLastError();
     }
   }
-  FaceSplit sp = face_split(nfl, across, nlines, K, kFacesCells<NF, K>);
-  if constexpr (NF == 1) {
-    // a scalar face is a few loads and stores, which other widths only scatter
-    // (80x70x60 along y 8.0 us, 6.6 by 32 x 8): the split only where the launch
-    // would be too large
-    const FaceSplit plain{across, 32, kTileColumns};
-    if (nlines > 1 && take(plain.width, plain.fj, plain.tx) < 1l << 24) sp = plain;
-  }
-  const long blocks = take(sp.width, sp.fj, sp.tx);
   if constexpr (NF > 3) {
-    if (faces_direct(a.axis, a.bc, nfl, nlines, K, a.flags != nullptr, sp)) {
+    if (nlines * nfl <= 2 * kWaveFaces &&
+        faces_direct(a.axis, a.bc, nfl, nlines, K, a.flags != nullptr,
+                     face_split(nfl, across, nlines, K, kFacesCells<NF, K>))) {
       set_lines(p, a.axis, a.nx, a.ny, a.axis == 0 ? 1 : (a.axis == 1 ? a.nx : (int)nlines));
       p.nch = (int)(nlines * nfl);
       const dim3 gr((unsigned)((nlines * nfl + 255) / 256));
@@ -942,6 +935,15 @@ hipError_t launch_faces(const FacesLaunch& a) {
       return hipGetLastError();
     }
   }
+  FaceSplit sp = face_split(nfl, across, nlines, K, kFacesCells<NF, K>, a.axis != 0);
+  if constexpr (NF == 1) {
+    // a scalar face is a few loads and stores, which other widths only scatter
+    // (80x70x60 along y 8.0 us, 6.6 by 32 x 8): the split only where the launch
+    // would be too large
+    const FaceSplit plain{across, 32, kTileColumns};
+    if (nlines > 1 && take(plain.width, plain.fj, plain.tx) < 1l << 24) sp = plain;
+  }
+  const long blocks = take(sp.width, sp.fj, sp.tx);
   if (blocks >= 1l << 24) return hipErrorInvalidValue;  // 2^32 threads; the split keeps 2^31 cells below
   const dim3 gr((unsigned)blocks);
   auto go = [&](auto cs) {

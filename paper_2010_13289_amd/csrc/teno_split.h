@@ -110,7 +110,10 @@ inline double face_split_time(int nfl, long nlines, int K, const FaceSplit& s) {
 // 34); 100x100x12 along z (12 x 21) 34 and 26 (39 and 30); 65x65x65 (22 x 11) 44 and
 // 36 (55 and 45); 50x50x50 (50 x 5) 25 and 22 (29 and 26); where they promise less
 // they lose up to 15 % (1394x130, 300x300, 1024x1024 transmissive).
-inline FaceSplit face_split(int nfl, int across, long nlines, int K, int nc) {
+// Fewer than 8 columns of x side by side (strided: faces along y and z) use less
+// than a 64-byte sector of each row, which costs 7 % more: 57x153x133 along y 51 x 5
+// 79 us, 32 x 8 74; 32x50x93 50 x 5 31.5, 28.6; 33x151x44 along z 39 x 6 40, 50.
+inline FaceSplit face_split(int nfl, int across, long nlines, int K, int nc, bool strided = false) {
   if (nlines == 1) return FaceSplit{1, nfl < 256 ? nfl : 256, 1};
   FaceSplit best{across, 32, kTileColumns};
   double best_t = face_split_time(nfl, nlines, K, best) / 1.08;
@@ -120,7 +123,7 @@ inline FaceSplit face_split(int nfl, int across, long nlines, int K, int nc) {
     if (tx > nc / (fj + K - 1)) tx = nc / (fj + K - 1);
     if (tx > nlines) tx = (int)nlines;
     const FaceSplit s{(int)nlines, fj, tx};
-    const double t = face_split_time(nfl, nlines, K, s);
+    const double t = face_split_time(nfl, nlines, K, s) * (strided && tx < kTileColumns ? 1.07 : 1.0);
     if (t < best_t) {
       best_t = t;
       best = s;
