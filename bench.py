@@ -75,11 +75,11 @@ BYTES_PER_CELL_STEP = O.rk3_bytes_per_cell(5)
 # by 2.0 and WRITE_SIZE by 1.0, the factors a plain 1 GiB device copy reads
 # as).  They describe the kernels built from the sources whose digest is
 # TRAFFIC_SOURCE_DIGEST and are reported as null for any other build.
-TRAFFIC_SOURCE_DIGEST = "ab4688ab6edd9d1ca0701cbc0f71d7f5e73afb6b48c0fef52e11fef02c97961b"
-MEASURED_TRAFFIC = {"sweep_x": 1.4672e+09, "sweep_y": 2.0386e+09, "sweep_z": 2.6410e+09}
+TRAFFIC_SOURCE_DIGEST = "49c33257cb5c9691c08d57468d613cefd444761efff9194154d4854885ee9f05"
+MEASURED_TRAFFIC = {"sweep_x": 1.4681e+09, "sweep_y": 2.0393e+09, "sweep_z": 2.6488e+09}
 # batched sweep, 4096 problems, averaged over the stages, per tile shape
 # (64x1, 128x1, 128x2, 256x1, 256x2, 512x1): smaller tiles re-read more halo
-MEASURED_TRAFFIC_BATCH = (1.2805e9, 1.1552e9, 1.1387e9, 1.0949e9, 1.1286e9, 1.0553e9)
+MEASURED_TRAFFIC_BATCH = (1.2804e9, 1.1553e9, 1.1388e9, 1.0947e9, 1.1210e9, 1.0553e9)
 TRAFFIC_NOTE = ("recorded, not measured in this run: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE of this benchmark "
                 "on the kernel sources whose digest is TRAFFIC_SOURCE_DIGEST (null for any other build); "
                 "see the profiles directory")
